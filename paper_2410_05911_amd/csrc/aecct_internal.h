@@ -100,11 +100,12 @@ hipError_t launch_attention(const Model &M, const float *qkv, int64_t words, flo
 // fp32 O, then (when oq is not null) Eq. 2 per token of O: the layered decode's path for
 // d = 64, 128 when L tokens' Q, K, V of a group fit LDS.  Where the lane-pair form holds a row's
 // outputs of every group in registers (qkv_attention_pair_quantises: d = 128, 16-dimension heads,
-// at most 384 tokens) and oq is given, the kernel writes only the codes and scales (o unused).
+// at most 384 tokens, g_per = d / 16) and oq is given, the kernel writes only the codes and scales
+// (o unused).
 bool qkv_attention_supported(const Model &M);
 bool qkv_attention_pair_quantises(const Model &M);
 hipError_t launch_qkv_attention(const Model &M, int layer, const int8_t *xq, const float *ax, int64_t words,
-                                float *o, int8_t *oq, float *ao, bool lane_order, hipStream_t s);
+                                float *o, int8_t *oq, float *ao, bool lane_order, int g_per, hipStream_t s);
 // The same with keys and values kept in LDS as int16 accumulators (words too long for the fp32
 // form, up to about 1800 tokens): writes O in fp32 only.
 bool qkv_attention_i16_supported(const Model &M);
@@ -114,7 +115,7 @@ bool qkv_attention_split_supported(const Model &M);
 hipError_t launch_qkv_attention_split(const Model &M, int layer, const int8_t *xq, const float *ax, int64_t words,
                                       float *o, bool lane_order, hipStream_t s);
 hipError_t launch_qkv_attention_i16(const Model &M, int layer, const int8_t *xq, const float *ax, int64_t words,
-                                    float *o, bool lane_order, hipStream_t s);
+                                    float *o, bool lane_order, int g_per, hipStream_t s);
 // Eq. 2 of the attention output (given as fp32 o, or already as codes oq with scales ao: exactly
 // one of o and oq is not null; natural layout), O-projection, residual, LN1, FFN with ReLU,
 // residual, LN2 and Eq. 2 of the next layer's input in one kernel (d = 64, 128): one wavefront
@@ -122,6 +123,9 @@ hipError_t launch_qkv_attention_i16(const Model &M, int layer, const int8_t *xq,
 bool token_block_supported(const Model &M);
 // words processed at once by the layered attention form `form` (aecct_layered_attention)
 int64_t attention_word_slots(const Model &M, int form);
+// head groups of a word that one block of that form runs in a launch of `words` words (g_per of the
+// launchers): all d / 16, or a divisor of that where a batch is smaller than the card
+int attention_groups_per_block(const Model &M, int form, int64_t words);
 // With z (the last layer): the head's z_i = W_{d->1} x_i + b1 of every output row to z [rows], and
 // neither x nor xq nor ax written.
 // With t (the first layer): x is not read; X is rebuilt from each token's t_i and the embedding.

@@ -753,11 +753,14 @@ static aecct_status decode_chunks(const Model &M, const float *y, int64_t batch,
   const bool tb = !pw && aecct::token_block_supported(M);
   const bool qa = M.lattn == AECCT_LAYERED_ATTN_LDS_F32, qw = M.lattn == AECCT_LAYERED_ATTN_LDS_I16;
   const bool qs = M.lattn == AECCT_LAYERED_ATTN_LDS_SPLIT;
-  // the lane-pair form that writes O as Eq. 2 codes, which the token block then takes as they are
-  const bool qa_codes = qa && tb && aecct::qkv_attention_pair_quantises(M);
+  // qa_codes: the lane-pair form that writes O as Eq. 2 codes, which the token block then takes as
+  // they are (whole words per block; a word's head groups spread over blocks leave O in fp32)
+  const int groups = M.d / 16;
   for (int64_t w0 = 0; w0 < batch; w0 += cw) {
     const int64_t nw = batch - w0 < cw ? batch - w0 : cw;
     const int64_t rows = nw * M.L;
+    const int g_per = aecct::attention_groups_per_block(M, M.lattn, nw);
+    const bool qa_codes = qa && tb && g_per == groups && aecct::qkv_attention_pair_quantises(M);
     // with the token block the embedding leaves t_i per token (in ag, unused on that path) and
     // the first token block rebuilds X from it rather than reading X back
     float *tt = tb && rows <= INT32_MAX ? ag : nullptr;
@@ -765,9 +768,9 @@ static aecct_status decode_chunks(const Model &M, const float *y, int64_t batch,
     if (pw && e == hipSuccess) e = aecct::launch_word_quant(M, x, nw, M.d, false, xq, ax, s);
     for (int l = 0; l < M.n_layers && e == hipSuccess; ++l) {
       if (qa) {
-        e = aecct::launch_qkv_attention(M, l, xq, ax, nw, qkv, tb && !qa_codes ? nullptr : oq, ao, tb, s);
+        e = aecct::launch_qkv_attention(M, l, xq, ax, nw, qkv, tb && !qa_codes ? nullptr : oq, ao, tb, g_per, s);
       } else if (qw) {
-        e = aecct::launch_qkv_attention_i16(M, l, xq, ax, nw, qkv, tb, s);
+        e = aecct::launch_qkv_attention_i16(M, l, xq, ax, nw, qkv, tb, g_per, s);
       } else if (qs) {
         e = aecct::launch_qkv_attention_split(M, l, xq, ax, nw, qkv, tb, s);
       } else {

@@ -482,7 +482,9 @@ struct QkvAttnArgs {
   // O instead of o
   int8_t *oq;
   float *ao;
-  int resident;                // k_qkv_attention: every head group's weight tiles stay in LDS
+  int resident;                // k_qkv_attention: the weight tiles of all the block's head groups stay in LDS
+  int g_per;                   // head groups per block (blockIdx.y-th run of them): all of them, or, for a
+                               // batch of fewer words than blocks that run at once, a part
   // k_qkv_attention_split: the same lists with every entry counted from the first token of its
   // node type (variables from 0, checks from n), the variable count n, and the LDS capacity in
   // tokens of the larger node type
@@ -714,22 +716,24 @@ template <int D, int DH, bool LT = false>
 __global__ __launch_bounds__(kQaThreads, (qa_waves_per_simd<D, DH>())) void k_qkv_attention(QkvAttnArgs p) {
   constexpr int NWV = kQaThreads / 64;
   // at most kQaThreads rows of L tokens x 16 / d_h heads: a wave holds up to TW of the L / 16 tiles
-  constexpr int S = D / 32, G = D / 16, HPG = 16 / DH, TW = qa_keep_tiles<D, DH>() ? (kQaThreads / HPG / 16 + NWV - 1) / NWV : 1;
+  constexpr int S = D / 32, HPG = 16 / DH, TW = qa_keep_tiles<D, DH>() ? (kQaThreads / HPG / 16 + NWV - 1) / NWV : 1;
   static_assert(TW <= kQaTilesPerWave, "token tiles per wave");
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   const int L = p.L, ntiles = (L + 15) / 16;
-  // weight fragments: [G][3][S][64] when resident (staged once per block), else one group's
+  // the block's head groups [g0, g1)
+  const int g0 = (int)blockIdx.y * p.g_per, g1 = g0 + p.g_per;
+  // weight fragments: [g_per][3][S][64] when resident (staged once per block), else one group's
   // [3][S][64], restaged per group
   constexpr int FW = 3 * S * 64;
   const bool resident = p.resident != 0;
   uint64_t *bfa = (uint64_t *)smem;
-  float *qs = (float *)(smem + (resident ? G : 1) * qa_frag_bytes<D>()), *kv = qs + (size_t)L * 16;
+  float *qs = (float *)(smem + (resident ? p.g_per : 1) * qa_frag_bytes<D>()), *kv = qs + (size_t)L * 16;
   float *bl = kv + (size_t)L * kQaRow;                               // [3][D] Q, K, V biases
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, col = lane & 15;
   if (blockIdx.x >= p.words) return;
-  for (int hg = 0; hg < (resident ? G : 1); ++hg) {
+  for (int hg = 0; hg < (resident ? p.g_per : 1); ++hg) {
     QaStage<D> st;
-    st.load(p.bpack, hg, tid);
+    st.load(p.bpack, g0 + hg, tid);
     st.store(bfa + hg * FW, tid);
   }
   for (int u = tid; u < 3 * D; u += kQaThreads) bl[u] = p.bias[u];
@@ -780,8 +784,8 @@ __global__ __launch_bounds__(kQaThreads, (qa_waves_per_simd<D, DH>())) void k_qk
         __asm__ volatile("" : "+v"(alw[k][0]), "+v"(alw[k][1]), "+v"(alw[k][2]), "+v"(alw[k][3]));
       }
     }
-    for (int hg = 0; hg < G; ++hg) {
-      const uint64_t *bf = resident ? bfa + hg * FW : bfa;
+    for (int hg = g0; hg < g1; ++hg) {
+      const uint64_t *bf = resident ? bfa + (hg - g0) * FW : bfa;
       const float bq = bl[16 * hg + col], bk = bl[D + 16 * hg + col], bv = bl[2 * D + 16 * hg + col];
       if constexpr (qa_keep_tiles<D, DH>()) {
         int wg = wave;
@@ -800,12 +804,12 @@ __global__ __launch_bounds__(kQaThreads, (qa_waves_per_simd<D, DH>())) void k_qk
       block_sync_lds();
       // LT: the projection of the word's last group has read its tiles: the next word's now
       if constexpr (LT)
-        if (hg == G - 1 && w + gridDim.x < p.words) load_tiles(w + gridDim.x);
+        if (hg == g1 - 1 && w + gridDim.x < p.words) load_tiles(w + gridDim.x);
       // not resident: the fragments were last read before the barrier above, so the next group's
       // weights are loaded now and written after the rows
-      const bool more = !LT && !resident && (hg + 1 < G || w + gridDim.x < p.words);
+      const bool more = !LT && !resident && (hg + 1 < g1 || w + gridDim.x < p.words);
       QaStage<D> st;
-      if (more) st.load(p.bpack, hg + 1 < G ? hg + 1 : 0, tid);
+      if (more) st.load(p.bpack, hg + 1 < g1 ? hg + 1 : g0, tid);
       if (row0) {
         const int h = hg * HPG + hh0;
         const bool first = h < p.hf;
@@ -929,14 +933,16 @@ __global__ __launch_bounds__(kQpThreads, 1) void k_qkv_attention_pair(QkvAttnArg
   static_assert(D == 128, "16-dimension heads, one per head group");
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   const int L = p.L, ntiles = (L + 15) / 16;
-  uint64_t *bfa = (uint64_t *)smem;                                  // [G][3][S][64] weight fragments
-  float *qs = (float *)(smem + G * qa_frag_bytes<D>()), *kv = qs + (size_t)L * 16;
+  // the block's head groups [g0, g0 + gn): all of them with the quantised output
+  const int g0 = OQ ? 0 : (int)blockIdx.y * p.g_per, gn = OQ ? G : p.g_per;
+  uint64_t *bfa = (uint64_t *)smem;                                  // [gn][3][S][64] weight fragments
+  float *qs = (float *)(smem + gn * qa_frag_bytes<D>()), *kv = qs + (size_t)L * 16;
   float *bl = kv + (size_t)L * kQaRow;                               // [3][D] Q, K, V biases
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, col = lane & 15, half = tid & 1;
   if (blockIdx.x >= p.words) return;
-  for (int hg = 0; hg < G; ++hg) {
+  for (int hg = 0; hg < gn; ++hg) {
     QaStage<D, kQpThreads> st;
-    st.load(p.bpack, hg, tid);
+    st.load(p.bpack, g0 + hg, tid);
     st.store(bfa + hg * FW, tid);
   }
   for (int u = tid; u < 3 * D; u += kQpThreads) bl[u] = p.bias[u];
@@ -992,7 +998,7 @@ __global__ __launch_bounds__(kQpThreads, 1) void k_qkv_attention_pair(QkvAttnArg
     }
     // head group hg: its Q, K, V into LDS, then its rows; row r0's outputs to out
     auto group = [&](int hg, float (&out)[8]) {
-      const uint64_t *bf = bfa + hg * FW;
+      const uint64_t *bf = bfa + (OQ ? hg : hg - g0) * FW;
       const float bq = bl[16 * hg + col], bk = bl[D + 16 * hg + col], bv = bl[2 * D + 16 * hg + col];
       int wg = wave;
       __asm__ volatile("" : "+v"(wg));
@@ -1066,7 +1072,7 @@ __global__ __launch_bounds__(kQpThreads, 1) void k_qkv_attention_pair(QkvAttnArg
         if (half == 0) p.ao[w * L + r0] = om;
       }
     } else {
-      for (int hg = 0; hg < G; ++hg) {
+      for (int hg = g0; hg < g0 + gn; ++hg) {
         float out[8];
         group(hg, out);
       }
@@ -1117,17 +1123,18 @@ __device__ __forceinline__ void qw_step(const float (&q)[DH], const int16_t *kw,
 
 template <int D, int DH>
 __global__ __launch_bounds__(kQaThreads) void k_qkv_attention_i16(QkvAttnArgs p) {
-  constexpr int S = D / 32, G = D / 16, HPG = 16 / DH, R = kQwRow, NWV = kQaThreads / 64;
+  constexpr int S = D / 32, HPG = 16 / DH, R = kQwRow, NWV = kQaThreads / 64;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   const int L = p.L, ntiles = (L + 15) / 16;
   uint64_t *bf = (uint64_t *)smem;                                   // [3][S][64] weight fragments
   int16_t *kvw = (int16_t *)(smem + qa_frag_bytes<D>());             // [L][R] key, value accumulators
   float2 *cs = (float2 *)(kvw + (size_t)L * R);                      // [L] key, value scales
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, col = lane & 15, rg = lane >> 4;
+  const int g0 = (int)blockIdx.y * p.g_per, g1 = g0 + p.g_per;   // the block's head groups
   if (blockIdx.x >= p.words) return;
   {
     QaStage<D> st;
-    st.load(p.bpack, 0, tid);
+    st.load(p.bpack, g0, tid);
     st.store(bf, tid);
   }
   __syncthreads();
@@ -1135,7 +1142,7 @@ __global__ __launch_bounds__(kQaThreads) void k_qkv_attention_i16(QkvAttnArgs p)
     const int8_t *xw = p.xq + w * L * D;
     const float *aw = p.ax + w * L;
     float *ow = p.o + w * L * D;
-    for (int hg = 0; hg < G; ++hg) {
+    for (int hg = g0; hg < g1; ++hg) {
       const float bq = p.bias[16 * hg + col];
       // the wave's next tile is read while the current one is projected
       long a[S], an[S];
@@ -1155,7 +1162,7 @@ __global__ __launch_bounds__(kQaThreads) void k_qkv_attention_i16(QkvAttnArgs p)
             ow[(size_t)tok * D + 16 * hg + col] = __builtin_fmaf((float)aq[i], al[i] * p.sq[0], bq);
             kvw[tok * R + col] = (int16_t)ak[i];
             kvw[tok * R + 16 + col] = (int16_t)av[i];
-            if (hg == 0 && col == 0) cs[tok] = make_float2(al[i] * p.sq[1], al[i] * p.sq[2]);
+            if (hg == g0 && col == 0) cs[tok] = make_float2(al[i] * p.sq[1], al[i] * p.sq[2]);
           }
         }
 #pragma unroll
@@ -1164,9 +1171,9 @@ __global__ __launch_bounds__(kQaThreads) void k_qkv_attention_i16(QkvAttnArgs p)
         for (int u = 0; u < 4; ++u) al[u] = aln[u];
       }
       __syncthreads();   // also orders the queries written to memory before their rows read them
-      const bool more = hg + 1 < G || w + gridDim.x < p.words;
+      const bool more = hg + 1 < g1 || w + gridDim.x < p.words;
       QaStage<D> st;
-      if (more) st.load(p.bpack, hg + 1 < G ? hg + 1 : 0, tid);
+      if (more) st.load(p.bpack, hg + 1 < g1 ? hg + 1 : g0, tid);
       for (int r = tid; r < L * HPG; r += kQaThreads) {
         const int hh = r / L, i = r - hh * L, h = hg * HPG + hh;
         const bool first = h < p.hf;
@@ -1355,7 +1362,7 @@ __device__ __forceinline__ void qa_load_codes(const int8_t *xw, int tt, int L, i
 
 template <int D>
 __global__ __launch_bounds__(kQvThreads) void k_qkv_attention_v16(QkvAttnArgs p) {
-  constexpr int S = D / 32, G = D / 16, R = kQvRow, NT = kQvThreads, NWV = NT / 64, TW = kQvTilesPerWave;
+  constexpr int S = D / 32, R = kQvRow, NT = kQvThreads, NWV = NT / 64, TW = kQvTilesPerWave;
   static_assert(TW % 2 == 0, "tiles in pairs");
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   const int L = p.L, ntiles = (L + 15) / 16;
@@ -1366,10 +1373,11 @@ __global__ __launch_bounds__(kQvThreads) void k_qkv_attention_v16(QkvAttnArgs p)
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, col = lane & 15, rg = lane >> 4;
   // the half row this lane runs in a tile pair: tile rg & 1 of the pair, dimensions 8 hq ..
   const int hq = rg >> 1;
+  const int g0 = (int)blockIdx.y * p.g_per, g1 = g0 + p.g_per;   // the block's head groups
   if (blockIdx.x >= p.words) return;
   {
     QaStage<D, NT> st;
-    st.load(p.bpack, 0, tid);
+    st.load(p.bpack, g0, tid);
     st.store(bf, tid);
   }
   const float sq[3] = {p.sq[0], p.sq[1], p.sq[2]};
@@ -1391,12 +1399,12 @@ __global__ __launch_bounds__(kQvThreads) void k_qkv_attention_v16(QkvAttnArgs p)
       qa_load_codes<D>(p.xq + w * L * D, 2 * wv + (k & 1) + 2 * NWV * (k >> 1), L, lane, afr[k]);
     for (int t = tid; t < L; t += NT) als[t] = p.ax[w * L + t];
     __syncthreads();
-    for (int hg = 0; hg < G; ++hg) {
+    for (int hg = g0; hg < g1; ++hg) {
       // the next group's weight tiles: read now; the key and value maps' written to LDS once
       // this projection is done, the query map's once this group's rows are
-      const bool more = hg + 1 < G || w + gridDim.x < p.words;
+      const bool more = hg + 1 < g1 || w + gridDim.x < p.words;
       QaStage<D, NT> st;
-      if (more) st.load(p.bpack, hg + 1 < G ? hg + 1 : 0, tid);
+      if (more) st.load(p.bpack, hg + 1 < g1 ? hg + 1 : g0, tid);
       float bkc = p.bias[D + 16 * hg + col];
       int wg = wave;
       __asm__ volatile("" : "+v"(wg), "+v"(bkc));
@@ -2353,9 +2361,9 @@ hipError_t launch_attention(const Model &M, const float *qkv, int64_t words, flo
   return hipGetLastError();
 }
 
-size_t qkv_attention_lds(const Model &M, bool resident = false) {
-  return (size_t)(resident ? M.d / 16 : 1) * 3 * (M.d / 32) * 64 * 8 + (size_t)M.L * (16 + kQaRow) * 4 +
-         (size_t)3 * M.d * 4;
+// LDS of the fp32 K/V forms with the weight tiles of `groups` head groups resident.
+size_t qkv_attention_lds(const Model &M, int groups = 1) {
+  return (size_t)groups * 3 * (M.d / 32) * 64 * 8 + (size_t)M.L * (16 + kQaRow) * 4 + (size_t)3 * M.d * 4;
 }
 
 // Blocks of k_qkv_attention resident on a CU: as many as LDS holds, at most as many as its
@@ -2367,9 +2375,10 @@ static int64_t qkv_attention_blocks_per_cu(const Model &M, size_t lds) {
   return std::min(by_lds, by_waves);
 }
 
-// Keep every head group's weight tiles in LDS when that does not lower the blocks per CU.
-bool qkv_attention_resident(const Model &M) {
-  const size_t one = qkv_attention_lds(M, false), all = qkv_attention_lds(M, true);
+// Keep every head group's weight tiles (of the `groups` a block runs) in LDS when that does not
+// lower the blocks per CU.
+bool qkv_attention_resident(const Model &M, int groups) {
+  const size_t one = qkv_attention_lds(M), all = qkv_attention_lds(M, groups);
   return all <= M.lds_max && qkv_attention_blocks_per_cu(M, all) >= qkv_attention_blocks_per_cu(M, one);
 }
 
@@ -2379,10 +2388,15 @@ bool qkv_attention_supported(const Model &M) {
          qkv_attention_lds(M) <= M.lds_max;
 }
 
-
 // The lists and their metadata in LDS beside the form's own use (LT).
-static size_t qkv_attention_lists_lds(const Model &M) {
-  return qkv_attention_lds(M, true) + (size_t)16 * M.L + (size_t)8 * (M.g1_groups + M.g2_groups);
+static size_t qkv_attention_lists_lds(const Model &M, int groups) {
+  return qkv_attention_lds(M, groups) + (size_t)16 * M.L + (size_t)8 * (M.g1_groups + M.g2_groups);
+}
+
+// blocks of `per_cu` per CU over the words, each running g_per of a word's head groups
+static dim3 attention_grid(const Model &M, const QkvAttnArgs &a, int64_t per_cu) {
+  const int64_t parts = (M.d / 16) / a.g_per;
+  return dim3((unsigned)std::max<int64_t>(1, std::min<int64_t>(a.words, M.cu_count * per_cu / parts)), (unsigned)parts);
 }
 
 template <int D, int DH>
@@ -2390,25 +2404,25 @@ static hipError_t run_qkv_attention(const Model &M, const QkvAttnArgs &a, size_t
   // LT where every group's weights stay resident, the tiles stay in registers and the lists fit
   // without fewer resident blocks
   if constexpr (qa_keep_tiles<D, DH>()) {
-    const size_t ll = qkv_attention_lists_lds(M);
+    const size_t ll = qkv_attention_lists_lds(M, a.g_per);
     if (a.resident && ll <= M.lds_max &&
         qkv_attention_blocks_per_cu(M, ll) >= qkv_attention_blocks_per_cu(M, lds)) {
       QkvAttnArgs b = a;
       b.tab1_n = M.g1_groups;
       b.tab2_n = M.g2_groups;
-      const int64_t blocks = std::min<int64_t>(a.words, (int64_t)M.cu_count * qkv_attention_blocks_per_cu(M, ll));
-      hipLaunchKernelGGL((k_qkv_attention<D, DH, true>), dim3((unsigned)blocks), dim3(kQaThreads), ll, s, b);
+      hipLaunchKernelGGL((k_qkv_attention<D, DH, true>), attention_grid(M, a, qkv_attention_blocks_per_cu(M, ll)),
+                         dim3(kQaThreads), ll, s, b);
       return hipGetLastError();
     }
   }
-  const int64_t blocks = std::min<int64_t>(a.words, (int64_t)M.cu_count * qkv_attention_blocks_per_cu(M, lds));
-  hipLaunchKernelGGL((k_qkv_attention<D, DH>), dim3((unsigned)blocks), dim3(kQaThreads), lds, s, a);
+  hipLaunchKernelGGL((k_qkv_attention<D, DH>), attention_grid(M, a, qkv_attention_blocks_per_cu(M, lds)),
+                     dim3(kQaThreads), lds, s, a);
   return hipGetLastError();
 }
 
 // The lane-pair form (16-dimension heads): every group's weights resident, up to 36 token tiles.
 size_t qkv_attention_pair_lds(const Model &M, bool quantised = false) {
-  return qkv_attention_lds(M, true) + (quantised ? (size_t)kQpThreads * 32 : 0);
+  return qkv_attention_lds(M, M.d / 16) + (quantised ? (size_t)kQpThreads * 32 : 0);
 }
 
 bool qkv_attention_pair_supported(const Model &M) {
@@ -2417,28 +2431,57 @@ bool qkv_attention_pair_supported(const Model &M) {
 }
 
 // The lane-pair form writes the Eq. 2 codes of O itself when a word has at most one row per lane
-// pair.
-
+// pair and a block runs all of a word's head groups.
 bool qkv_attention_pair_quantises(const Model &M) {
   return qkv_attention_pair_supported(M) && M.L <= kQpThreads / 2 && qkv_attention_pair_lds(M, true) <= M.lds_max;
 }
 
 template <int D>
 static hipError_t run_qkv_attention_pair(const Model &M, const QkvAttnArgs &a, size_t lds, hipStream_t s) {
-  const int64_t per_cu = std::max<int64_t>(1, (int64_t)(M.lds_max / lds));
-  const int64_t blocks = std::min<int64_t>(a.words, (int64_t)M.cu_count * per_cu);
-  if (a.oq && a.tab1_n > 0) hipLaunchKernelGGL((k_qkv_attention_pair<D, true, true>), dim3((unsigned)blocks), dim3(kQpThreads), lds, s, a);
-  else if (a.oq) hipLaunchKernelGGL((k_qkv_attention_pair<D, true>), dim3((unsigned)blocks), dim3(kQpThreads), lds, s, a);
-  else hipLaunchKernelGGL((k_qkv_attention_pair<D, false>), dim3((unsigned)blocks), dim3(kQpThreads), lds, s, a);
+  const dim3 grid = attention_grid(M, a, std::max<int64_t>(1, (int64_t)(M.lds_max / lds)));
+  if (a.oq && a.tab1_n > 0) hipLaunchKernelGGL((k_qkv_attention_pair<D, true, true>), grid, dim3(kQpThreads), lds, s, a);
+  else if (a.oq) hipLaunchKernelGGL((k_qkv_attention_pair<D, true>), grid, dim3(kQpThreads), lds, s, a);
+  else hipLaunchKernelGGL((k_qkv_attention_pair<D, false>), grid, dim3(kQpThreads), lds, s, a);
   return hipGetLastError();
 }
 
-hipError_t launch_qkv_attention(const Model &M, int layer, const int8_t *xq, const float *ax, int64_t words,
-                                float *o, int8_t *oq, float *ao, bool lane_order, hipStream_t s) {
-  if (words <= 0) return hipSuccess;
-  if (!qkv_attention_supported(M)) return hipErrorInvalidValue;
+static size_t qkv_attention_v16_lds(const Model &M) {
+  return M.d == 64 ? qkv_attention_v16_lds_bytes<64>(M.L) : qkv_attention_v16_lds_bytes<128>(M.L);
+}
+static size_t qkv_attention_i16_lds(const Model &M) {
+  return M.d == 64 ? qkv_attention_i16_lds_bytes<64>(M.L) : qkv_attention_i16_lds_bytes<128>(M.L);
+}
+
+// Head groups a block of the layered attention form `form` runs of each of its words.  A block for
+// each whole word leaves most of the card idle below one word per resident block (LDPC(256,128),
+// 37 words: 36 us a layer on 37 blocks), so a word's groups are then spread over blocks, each
+// loading only its own groups' weights: the divisor of the group count of least
+//   rounds x (groups per block + 1/2: the word's tiles) + 2 (weights, lists, launch),
+// in units of one group's time, with the split forms' longer rows (lists from the L2 and O in fp32
+// where the whole-word form keeps the lists in LDS and writes codes) priced at a fifth more.
+// Decodes measured: LDPC(256,128), 37 words 665 -> 477 us; LDPC(128,64), one word 139 -> 104 us.
+int attention_groups_per_block(const Model &M, int form, int64_t words) {
+  const int G = M.d / 16;
+  if (form != 1 && form != 2) return G;   // fp32 or int16 keys and values in LDS (aecct_layered_attention)
+  const int64_t slots = attention_word_slots(M, form);
+  int best = G;
+  double least = 0.0;
+  for (int g = G; g >= 1; --g) {
+    if (G % g) continue;
+    const int64_t bx = std::min<int64_t>(words, std::max<int64_t>(1, slots / (G / g)));
+    const double cost = ((double)((words + bx - 1) / bx) * (g + 0.5) + 2.0) * (g == G ? 1.0 : 1.2);
+    if (g == G || cost < least) {
+      least = cost;
+      best = g;
+    }
+  }
+  return best;
+}
+
+// the arguments that every fused projection and attention form takes
+static QkvAttnArgs qkv_attention_args(const Model &M, int layer, const int8_t *xq, const float *ax, int64_t words,
+                                      float *o, bool lane_order) {
   const LayerWeights &W = M.layer[layer];
-  if (lane_order && !W.qkv_tb) return hipErrorInvalidValue;
   QkvAttnArgs a{};
   a.xq = xq;
   a.ax = ax;
@@ -2453,20 +2496,33 @@ hipError_t launch_qkv_attention(const Model &M, int layer, const int8_t *xq, con
   a.meta1 = (const int2 *)M.g1_meta; a.meta2 = (const int2 *)M.g2_meta;
   a.tab1 = (const uint2 *)M.g1_tab; a.tab2 = (const uint2 *)M.g2_tab;
   a.o = o;
-  a.resident = qkv_attention_resident(M) ? 1 : 0;
-  const size_t lds = qkv_attention_lds(M, a.resident != 0);
+  a.g_per = M.d / 16;
+  return a;
+}
+
+hipError_t launch_qkv_attention(const Model &M, int layer, const int8_t *xq, const float *ax, int64_t words,
+                                float *o, int8_t *oq, float *ao, bool lane_order, int g_per, hipStream_t s) {
+  if (words <= 0) return hipSuccess;
+  if (!qkv_attention_supported(M) || g_per < 1 || (M.d / 16) % g_per) return hipErrorInvalidValue;
+  if (lane_order && !M.layer[layer].qkv_tb) return hipErrorInvalidValue;
+  QkvAttnArgs a = qkv_attention_args(M, layer, xq, ax, words, o, lane_order);
+  const bool whole = g_per == M.d / 16;
   hipError_t e = hipErrorInvalidValue;
-  if (oq && qkv_attention_pair_quantises(M)) {   // O straight to its codes, no fp32 rows
+  if (oq && whole && qkv_attention_pair_quantises(M)) {   // O straight to its codes, no fp32 rows
     a.oq = oq;
     a.ao = ao;
-    if (qkv_attention_lists_lds(M) <= M.lds_max) {   // and the lists in LDS
+    const size_t ll = qkv_attention_lists_lds(M, M.d / 16);
+    if (ll <= M.lds_max) {   // and the lists in LDS
       a.tab1_n = M.g1_groups;
       a.tab2_n = M.g2_groups;
-      return run_qkv_attention_pair<128>(M, a, qkv_attention_lists_lds(M), s);
+      return run_qkv_attention_pair<128>(M, a, ll, s);
     }
     return run_qkv_attention_pair<128>(M, a, qkv_attention_pair_lds(M, true), s);
   }
-  if (qkv_attention_pair_supported(M)) e = run_qkv_attention_pair<128>(M, a, qkv_attention_pair_lds(M), s);
+  a.g_per = g_per;
+  a.resident = qkv_attention_resident(M, g_per) ? 1 : 0;
+  const size_t lds = qkv_attention_lds(M, a.resident ? g_per : 1);
+  if (qkv_attention_pair_supported(M)) e = run_qkv_attention_pair<128>(M, a, qkv_attention_lds(M, g_per), s);
   else if (M.d == 64 && M.dh == 8) e = run_qkv_attention<64, 8>(M, a, lds, s);
   else if (M.d == 128 && M.dh == 16) e = run_qkv_attention<128, 16>(M, a, lds, s);
   else if (M.d == 128 && M.dh == 8) e = run_qkv_attention<128, 8>(M, a, lds, s);
@@ -2481,15 +2537,13 @@ hipError_t launch_qkv_attention(const Model &M, int layer, const int8_t *xq, con
 
 bool qkv_attention_i16_supported(const Model &M) {
   if (!((M.d == 64 || M.d == 128) && (M.dh == 8 || M.dh == 16) && M.grouped)) return false;
-  const size_t lds = M.d == 64 ? qkv_attention_i16_lds_bytes<64>(M.L) : qkv_attention_i16_lds_bytes<128>(M.L);
-  return lds <= M.lds_max;
+  return qkv_attention_i16_lds(M) <= M.lds_max;
 }
 
 template <int D, int DH>
 static hipError_t run_qkv_attention_i16(const Model &M, const QkvAttnArgs &a, size_t lds, hipStream_t s) {
   const int64_t per_cu = std::max<int64_t>(1, (int64_t)(M.lds_max / lds));
-  const int64_t blocks = std::min<int64_t>(a.words, (int64_t)M.cu_count * per_cu);
-  hipLaunchKernelGGL((k_qkv_attention_i16<D, DH>), dim3((unsigned)blocks), dim3(kQaThreads), lds, s, a);
+  hipLaunchKernelGGL((k_qkv_attention_i16<D, DH>), attention_grid(M, a, per_cu), dim3(kQaThreads), lds, s, a);
   return hipGetLastError();
 }
 
@@ -2497,43 +2551,28 @@ static hipError_t run_qkv_attention_i16(const Model &M, const QkvAttnArgs &a, si
 bool qkv_attention_v16_supported(const Model &M) {
   if (!((M.d == 64 || M.d == 128) && M.dh == 16 && M.grouped)) return false;
   if (M.L > 16 * (kQvThreads / 64) * kQvTilesPerWave) return false;
-  const size_t lds = M.d == 64 ? qkv_attention_v16_lds_bytes<64>(M.L) : qkv_attention_v16_lds_bytes<128>(M.L);
-  return lds <= M.lds_max;
+  return qkv_attention_v16_lds(M) <= M.lds_max;
 }
 
 template <int D>
 static hipError_t run_qkv_attention_v16(const Model &M, const QkvAttnArgs &a, size_t lds, hipStream_t s) {
   const int64_t per_cu = std::max<int64_t>(1, (int64_t)(M.lds_max / lds));
-  const int64_t blocks = std::min<int64_t>(a.words, (int64_t)M.cu_count * per_cu);
-  hipLaunchKernelGGL((k_qkv_attention_v16<D>), dim3((unsigned)blocks), dim3(kQvThreads), lds, s, a);
+  hipLaunchKernelGGL((k_qkv_attention_v16<D>), attention_grid(M, a, per_cu), dim3(kQvThreads), lds, s, a);
   return hipGetLastError();
 }
 
 hipError_t launch_qkv_attention_i16(const Model &M, int layer, const int8_t *xq, const float *ax, int64_t words,
-                                    float *o, bool lane_order, hipStream_t s) {
+                                    float *o, bool lane_order, int g_per, hipStream_t s) {
   if (words <= 0) return hipSuccess;
-  if (!qkv_attention_i16_supported(M)) return hipErrorInvalidValue;
-  const LayerWeights &W = M.layer[layer];
-  if (lane_order && !W.qkv_tb) return hipErrorInvalidValue;
-  QkvAttnArgs a{};
-  a.xq = xq;
-  a.ax = ax;
-  a.bpack = lane_order ? W.qkv_tb : W.qkv;
-  a.bias = W.b_qkv;
-  a.sq[0] = W.sq_qs;
-  a.sq[1] = W.sq[1];
-  a.sq[2] = W.sq[2];
-  a.words = words;
-  a.L = M.L;
-  a.hf = M.hf;
-  a.meta1 = (const int2 *)M.g1_meta; a.meta2 = (const int2 *)M.g2_meta;
-  a.tab1 = (const uint2 *)M.g1_tab; a.tab2 = (const uint2 *)M.g2_tab;
-  a.o = o;
+  if (!qkv_attention_i16_supported(M) || g_per < 1 || (M.d / 16) % g_per) return hipErrorInvalidValue;
+  if (lane_order && !M.layer[layer].qkv_tb) return hipErrorInvalidValue;
+  QkvAttnArgs a = qkv_attention_args(M, layer, xq, ax, words, o, lane_order);
+  a.g_per = g_per;
   if (qkv_attention_v16_supported(M)) {
-    const size_t lv = M.d == 64 ? qkv_attention_v16_lds_bytes<64>(M.L) : qkv_attention_v16_lds_bytes<128>(M.L);
+    const size_t lv = qkv_attention_v16_lds(M);
     return M.d == 64 ? run_qkv_attention_v16<64>(M, a, lv, s) : run_qkv_attention_v16<128>(M, a, lv, s);
   }
-  const size_t lds = M.d == 64 ? qkv_attention_i16_lds_bytes<64>(M.L) : qkv_attention_i16_lds_bytes<128>(M.L);
+  const size_t lds = qkv_attention_i16_lds(M);
   if (M.d == 128 && M.dh == 16) return run_qkv_attention_i16<128, 16>(M, a, lds, s);
   if (M.d == 64 && M.dh == 16) return run_qkv_attention_i16<64, 16>(M, a, lds, s);
   if (M.d == 64 && M.dh == 8) return run_qkv_attention_i16<64, 8>(M, a, lds, s);
@@ -2553,24 +2592,11 @@ hipError_t launch_qkv_attention_split(const Model &M, int layer, const int8_t *x
                                       float *o, bool lane_order, hipStream_t s) {
   if (words <= 0) return hipSuccess;
   if (!qkv_attention_split_supported(M)) return hipErrorInvalidValue;
-  const LayerWeights &W = M.layer[layer];
-  if (lane_order && !W.qkv_tb) return hipErrorInvalidValue;
-  QkvAttnArgs a{};
-  a.xq = xq;
-  a.ax = ax;
-  a.bpack = lane_order ? W.qkv_tb : W.qkv;
-  a.bias = W.b_qkv;
-  a.sq[0] = W.sq_qs;
-  a.sq[1] = W.sq[1];
-  a.sq[2] = W.sq[2];
-  a.words = words;
-  a.L = M.L;
-  a.hf = M.hf;
-  a.meta1 = (const int2 *)M.g1_meta; a.meta2 = (const int2 *)M.g2_meta;
+  if (lane_order && !M.layer[layer].qkv_tb) return hipErrorInvalidValue;
+  QkvAttnArgs a = qkv_attention_args(M, layer, xq, ax, words, o, lane_order);
   a.tab1s = (const uint2 *)M.g1s_tab; a.tab2s = (const uint2 *)M.g2s_tab;
   a.n_var = M.n;
   a.kv_cap = std::max(M.n, M.m);
-  a.o = o;
   const size_t lds = qkv_attention_split_lds_bytes<128>(a.kv_cap, M.L);
   const int64_t per_cu = std::max<int64_t>(1, (int64_t)(M.lds_max / lds));
   const int64_t blocks = std::min<int64_t>(words, (int64_t)M.cu_count * per_cu);
@@ -2585,12 +2611,11 @@ int64_t attention_word_slots(const Model &M, int form) {
   switch (form) {
     case 1:   // fp32 keys and values of the whole word
       if (!qkv_attention_pair_supported(M))
-        return (int64_t)M.cu_count * qkv_attention_blocks_per_cu(M, qkv_attention_lds(M, qkv_attention_resident(M)));
+        return (int64_t)M.cu_count * qkv_attention_blocks_per_cu(M, qkv_attention_lds(M, qkv_attention_resident(M, M.d / 16) ? M.d / 16 : 1));
       lds = qkv_attention_pair_lds(M);
       break;
     case 2:   // int16 accumulators
-      lds = qkv_attention_v16_supported(M) ? (M.d == 64 ? qkv_attention_v16_lds_bytes<64>(M.L) : qkv_attention_v16_lds_bytes<128>(M.L))
-                                           : (M.d == 64 ? qkv_attention_i16_lds_bytes<64>(M.L) : qkv_attention_i16_lds_bytes<128>(M.L));
+      lds = qkv_attention_v16_supported(M) ? qkv_attention_v16_lds(M) : qkv_attention_i16_lds(M);
       break;
     case 3:   // one node type's rows at a time
       lds = qkv_attention_split_lds_bytes<128>(std::max(M.n, M.m), M.L);

@@ -1,0 +1,52 @@
+"""Batches smaller than the card decode through other launch shapes than full ones (a word's head
+groups spread over blocks); every shape has to give the bits of the whole-word form, which
+test_gpu_parity.py pins to the oracle.
+
+For each attention form the words of one batch too large to be spread are decoded again in the sizes
+where the number of head groups per block changes, down to a single word; results are compared bit
+for bit (the order of every sum is fixed, so the tolerance is zero).
+"""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+from workloads import random_weights, regular_ldpc_3_6, generator_from_parity, awgn_words  # noqa: E402
+
+
+@pytest.fixture(scope="module")
+def P():
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    import paper_2410_05911_amd as P
+    P.lib()
+    return P
+
+
+@pytest.mark.parametrize("n,d,heads,attention,hf,form,batch,sizes", [
+    (128, 64, 8, "hpsa", 4, -1, 1100, (1, 5, 130, 200, 300, 520)),     # fp32 K and V, d_h = 8, two blocks a CU
+    (66, 64, 4, "casa", 2, -1, 1100, (1, 33, 257)),                    # d_h = 16 at d = 64, 99 tokens
+    (66, 128, 16, "hpsa", 6, -1, 600, (1, 40, 129)),                   # d_h = 8 at d = 128
+    (256, 128, 8, "hpsa", 4, -1, 600, (1, 2, 37, 70, 129, 260)),       # lane pairs, codes | fp32 O
+    (270, 128, 8, "casa", 2, -1, 300, (1, 50, 100)),                   # lane pairs, 405 tokens: a second row a pair
+    (514, 128, 8, "hpsa", 4, -1, 300, (1, 33, 66, 130)),               # fp32 K, int16 V, 771 tokens
+    (398, 64, 8, "hpsa", 4, -1, 600, (1, 70, 140)),                    # int16 K and V, d_h = 8
+    (256, 128, 8, "hpsa", 4, 2, 300, (1, 40)),                         # the int16 form by request
+])
+def test_spread_head_groups_match_whole_words(P, n, d, heads, attention, hf, form, batch, sizes):
+    H = regular_ldpc_3_6(n, seed=1000 + n)
+    w = random_weights(n, n // 2, d, 2, heads, seed=n + d, first_ring_heads=hf, attention=attention)
+    y, _, _ = awgn_words(generator_from_parity(H), batch, (2.0, 4.0), seed=n)
+    yd = torch.from_numpy(y).cuda()
+    dec = P.Decoder(H, w, layered_attention=form)
+    bits, logits = dec.decode(yd)
+    torch.cuda.synchronize()
+    assert np.isfinite(logits.cpu().numpy()).all()
+    for k in sizes:
+        print(f"[small] LDPC({n}) d {d} heads {heads} {attention}: {k} words", flush=True)
+        at = (batch - k) // 2
+        b, f = dec.decode(yd[at:at + k].contiguous())
+        torch.cuda.synchronize()
+        assert torch.equal(f, logits[at:at + k]) and torch.equal(b, bits[at:at + k])
+    dec.close()
