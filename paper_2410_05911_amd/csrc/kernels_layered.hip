@@ -2037,6 +2037,230 @@ __global__ __launch_bounds__(kTbWaves * 64) void k_token_block(TokenBlockArgs p)
 }
 
 // ------------------------------------------------------------------------------------------
+// The token block for few strips (batches smaller than the card): one block of d / 16 wavefronts
+// per 16-token strip.  k_token_block gives a strip to one wavefront after staging 9 d^2 bytes of
+// fragments per block; with a strip or less per resident wavefront its time is that staging and
+// the strip's serial chain on otherwise idle units (LDPC(256,128), one word: 28 us a layer with the attention, 23 as here).  Here
+// the strip's products are split over the wavefronts, and every fragment is used once, so it goes
+// from the L2 straight to registers: wavefront w forms output tile w of O and FF2 and the hidden
+// tiles 4 w .. 4 w + 3, which are exactly FF2's k-steps 2 w and 2 w + 1; FF2's int32 partial sums
+// are added over the wavefronts through LDS (exact in any order).  What needs a whole token, the
+// LayerNorms and the Eq. 2 maxima, is exchanged through LDS and formed by every wavefront from the
+// same values in k_token_block's order, so the results are its results bit for bit.
+// ------------------------------------------------------------------------------------------
+template <int D>
+constexpr size_t token_strip_lds() {   // FF2 partials, the strip's rows, vectors as in k_token_block, maxima
+  return (size_t)(D / 16) * (D / 16) * 1024 + (size_t)16 * (D + 4) * 4 + (size_t)11 * D * 4 + (size_t)(D / 16) * 64;
+}
+
+template <int D, bool OQ, bool Z, bool E>
+__global__ __launch_bounds__(D * 4, 4) void k_token_strip(TokenBlockArgs p) {
+  constexpr int V = D / 4, S = D / 32, TO = D / 16, NW = D / 16, SH = D / 8, NT = 64 * NW, XR = D + 4;
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  v4i *part = (v4i *)smem;                                   // [NW][TO][64] FF2 partial sums
+  float *xs = (float *)(smem + (size_t)NW * TO * 1024);      // [16][XR] a row's d values as [g][v]
+  float *lv = xs + 16 * XR;                                  // [6][4][V] vectors, [4 D] FF1 bias, [4][V] W_{d->1}
+  float *mx = lv + 11 * D;                                   // [NW][16] hidden maxima
+  const int tid = threadIdx.x, lane = tid & 63, c = lane & 15, g = lane >> 4;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int64_t row0 = (int64_t)blockIdx.x * 16, tok = row0 + c;
+  const bool ok = tok < p.rows;
+  const int64_t tl = ok ? tok : p.rows - 1;                  // padding columns: a copy, never stored
+  // the wavefront's fragments of O and FF1 (FF2's once FF1 is under way)
+  long fo[S], f1[4][S];
+#pragma unroll
+  for (int s = 0; s < S; ++s) fo[s] = (long)p.fo[(w * S + s) * 64 + lane];
+#pragma unroll
+  for (int o = 0; o < 4; ++o)
+#pragma unroll
+    for (int s = 0; s < S; ++s) f1[o][s] = (long)p.f1[((4 * w + o) * S + s) * 64 + lane];
+  for (int u = tid; u < 6 * D; u += NT) lv[u] = p.vec[u];
+  for (int u = tid; u < 4 * D; u += NT) lv[6 * D + u] = p.b1[u];
+  if constexpr (Z)
+    for (int u = tid; u < D; u += NT) lv[10 * D + u] = p.w1[u];
+  const float *vec = lv;
+  // the residual's four values of this lane's output tile: features v = 4 w .. 4 w + 3
+  const int xo = g * V + 4 * w;
+  float4 xr;
+  if constexpr (E) {
+    const uint32_t L = (uint32_t)p.L;
+    uint32_t ie = (uint32_t)row0 % L + (uint32_t)c;
+    while (ie >= L) ie -= L;
+    const float tt = p.t[tl];
+    const float4 e = *(const float4 *)(p.elo + ie * D + xo);
+    const float4 q = p.plo ? *(const float4 *)(p.plo + ie * D + xo) : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    xr = make_float4(__builtin_fmaf(tt, e.x, q.x), __builtin_fmaf(tt, e.y, q.y), __builtin_fmaf(tt, e.z, q.z),
+                     __builtin_fmaf(tt, e.w, q.w));
+  } else {
+    xr = *(const float4 *)(p.x + tl * D + xo);
+  }
+  // Eq. 2 of the token's attention output, in every wavefront (each needs all of its k-steps)
+  long bq[S];
+  float sc;
+  if constexpr (OQ) {
+#pragma unroll
+    for (int s = 0; s < S; ++s) bq[s] = *(const long *)(p.oq + tl * D + 32 * s + 8 * g);
+    sc = p.ao[tl] * p.sq_o;
+  } else {
+    float ov[S][8];
+    float om = 0.0f;
+#pragma unroll
+    for (int s = 0; s < S; ++s)
+#pragma unroll
+      for (int k = 0; k < 8; k += 4) {
+        const float4 f = *(const float4 *)(p.o + tl * D + 32 * s + 8 * g + k);
+        ov[s][k] = f.x; ov[s][k + 1] = f.y; ov[s][k + 2] = f.z; ov[s][k + 3] = f.w;
+      }
+#pragma unroll
+    for (int s = 0; s < S; ++s)
+#pragma unroll
+      for (int k = 0; k < 8; ++k) om = fmaxf(om, fabsf(ov[s][k]));
+    om = tb_token_max(om);
+    const float oinv = inv127(om);
+#pragma unroll
+    for (int s = 0; s < S; ++s) {
+      uint32_t b[8];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) b[k] = quant_bits(ov[s][k], oinv);
+      bq[s] = tb_pack8(b);
+    }
+    sc = om * p.sq_o;
+  }
+  __syncthreads();   // the vectors
+  float *const xrow = xs + c * XR + g * V;   // this lane's V values of its token
+  // residual sums of the wavefront's tile to LDS, then the whole row in every wavefront, normalised
+  auto layer_norm = [&](const v4i &acc, float scale, const float *bias, const float4 &res, const float *gain,
+                        const float *shift, float (&x)[V], float &amax) {
+    const float4 b = *(const float4 *)(bias + xo);
+    *(float4 *)(xrow + 4 * w) =
+        make_float4(res.x + __builtin_fmaf((float)acc[0], scale, b.x), res.y + __builtin_fmaf((float)acc[1], scale, b.y),
+                    res.z + __builtin_fmaf((float)acc[2], scale, b.z), res.w + __builtin_fmaf((float)acc[3], scale, b.w));
+    __syncthreads();
+#pragma unroll
+    for (int v = 0; v < V; v += 4) {
+      const float4 f = *(const float4 *)(xrow + v);
+      x[v] = f.x; x[v + 1] = f.y; x[v + 2] = f.z; x[v + 3] = f.w;
+    }
+    const float mean = tb_token_sum<V>(x) / (float)D;
+    float sq[V];
+#pragma unroll
+    for (int v = 0; v < V; ++v) {
+      x[v] = x[v] - mean;
+      sq[v] = x[v] * x[v];
+    }
+    const float var = tb_token_sum<V>(sq) / (float)D;
+    const float rho = ln_rsqrt(var + p.eps);
+    amax = 0.0f;
+#pragma unroll
+    for (int v = 0; v < V; ++v) {
+      x[v] = __builtin_fmaf(x[v] * rho, gain[g * V + v], shift[g * V + v]);
+      amax = fmaxf(amax, fabsf(x[v]));
+    }
+  };
+  // values 4 w .. 4 w + 3 of a row held whole (w is wave-uniform)
+  auto own = [&](const float (&x)[V]) {
+    float4 r = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+#pragma unroll
+    for (int o = 0; o < TO; ++o)
+      if (o == w) r = make_float4(x[4 * o], x[4 * o + 1], x[4 * o + 2], x[4 * o + 3]);
+    return r;
+  };
+  // ---- output projection, residual, LN1, Eq. 2 ----
+  long xb[S];
+  float4 x1o;
+  float sc1;
+  {
+    const v4i acc = mfma_i8_steps<S>([&](int s) { return fo[s]; }, [&](int s) { return bq[s]; }, v4i{0, 0, 0, 0});
+    float x1[V], amax;
+    layer_norm(acc, sc, vec, xr, vec + D, vec + 2 * D, x1, amax);
+    amax = tb_token_max(amax);
+    const float inv = inv127(amax);
+#pragma unroll
+    for (int s = 0; s < S; ++s) {
+      uint32_t b[8];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) b[k] = quant_bits(x1[8 * s + k], inv);
+      xb[s] = tb_pack8(b);
+    }
+    x1o = own(x1);
+    sc1 = amax * p.sq_1;
+  }
+  // ---- FFN1 with ReLU: four hidden tiles, the token's maximum over every wavefront's ----
+  long f2[TO][2];
+#pragma unroll
+  for (int o = 0; o < TO; ++o) {
+    f2[o][0] = (long)p.f2[(o * SH + 2 * w) * 64 + lane];
+    f2[o][1] = (long)p.f2[(o * SH + 2 * w + 1) * 64 + lane];
+  }
+  float hid[4][4], am = 0.0f;
+#pragma unroll
+  for (int o = 0; o < 4; ++o) {
+    const v4i acc = mfma_i8_steps<S>([&](int s) { return f1[o][s]; }, [&](int s) { return xb[s]; }, v4i{0, 0, 0, 0});
+    const float4 b = *(const float4 *)(lv + 6 * D + 16 * (4 * w + o) + 4 * g);
+    const float bb[4] = {b.x, b.y, b.z, b.w};
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      hid[o][i] = __builtin_fmaf((float)acc[i], sc1, bb[i]);
+      am = fmaxf(am, hid[o][i]);
+    }
+  }
+  am = tb_token_max(am + 0.0f);   // +0: a -0 maximum would not order like its bits
+  if (g == 0) mx[w * 16 + c] = am;
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < NW; ++k) am = fmaxf(am, mx[k * 16 + c]);
+  const float inv1 = inv127(am);
+  // ---- FFN2: this wavefront's two k-steps of every output tile ----
+  {
+    long gb[2];
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      uint32_t b[8];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        b[i] = quant_bits(hid[2 * j][i], inv1);
+        b[4 + i] = quant_bits(hid[2 * j + 1][i], inv1);
+      }
+      gb[j] = (long)(((uint64_t)pack4_relu(b[4], b[5], b[6], b[7]) << 32) | pack4_relu(b[0], b[1], b[2], b[3]));
+    }
+#pragma unroll
+    for (int o = 0; o < TO; ++o)
+      part[(w * TO + o) * 64 + lane] = mfma_i8_16x16x64(f2[o][0], f2[o][1], gb[0], gb[1], v4i{0, 0, 0, 0});
+  }
+  __syncthreads();
+  v4i acc2 = part[w * 64 + lane];
+#pragma unroll
+  for (int k = 1; k < NW; ++k) acc2 += part[(k * TO + w) * 64 + lane];
+  // ---- FFN2 epilogue: residual, LN2, Eq. 2 of the next layer's input ----
+  float v2[V], amax;
+  layer_norm(acc2, am * p.sq_2, vec + 3 * D, x1o, vec + 4 * D, vec + 5 * D, v2, amax);
+  if constexpr (Z) {
+    if (w != 0) return;
+    const float *w1l = vec + 10 * D + g * V;
+    float pr[V];
+#pragma unroll
+    for (int v = 0; v < V; ++v) pr[v] = v2[v] * w1l[v];
+    const float zt = tb_token_sum<V>(pr) + p.head_b1;
+    if (ok && g == 0) p.z[tok] = zt;
+  } else {
+    amax = tb_token_max(amax);
+    const float inv = inv127(amax);
+    if (ok) {
+      *(float4 *)(p.x + tok * D + xo) = own(v2);
+#pragma unroll
+      for (int s = 0; s < S; ++s)
+        if (s == w) {   // step s's eight codes of this lane
+          uint32_t b[8];
+#pragma unroll
+          for (int k = 0; k < 8; ++k) b[k] = quant_bits(v2[8 * s + k], inv);
+          *(long *)(p.xq + tok * D + 32 * s + 8 * g) = tb_pack8(b);
+        }
+      if (w == 0 && g == 0) p.ax[tok] = amax;
+    }
+  }
+}
+
+// ------------------------------------------------------------------------------------------
 // Output head and hard decision (Section 3): one block per word.  z_i = W_{d->1} x_i + b1
 // (16 lanes per token, pairwise over features), then f_o = sum_i z_i W_o[i][o] + b_o in
 // ascending token order, bit = [y < 0] xor [f < 0].
@@ -2653,10 +2877,21 @@ bool token_block_supported(const Model &M) {
   return (M.d == 64 || M.d == 128) && M.dff == 4 * M.d && M.layer[0].tb_o != nullptr;
 }
 
+// A block per strip (k_token_strip) up to three strips for two compute units: beyond that its fragment
+// reads (9 d^2 bytes a strip from the L2) cost more than the staging they save.  Decodes measured, a
+// wavefront against a block per strip: LDPC(256,128) 1 word 285 / 234 us, 10 words (240 strips) 297 /
+// 247, 20 words (480) 324 / 316, 30 words (720) 347 / 401; LDPC(128,64) 21 words (252) 107 / 98,
+// 43 words (516) 111 / 113; LDPC(1024,512) 4 words (384) 751 / 750, 8 words (768) 782 / 842.
+bool token_strip_faster(const Model &M, int64_t strips) { return 2 * strips <= 3 * (int64_t)M.cu_count; }
+
 template <int D, bool OQ, bool Z, bool E>
 static hipError_t run_token_block(const Model &M, const TokenBlockArgs &a, hipStream_t s) {
-  constexpr size_t lds = token_block_lds<D>();
   const int64_t strips = (a.rows + 15) / 16;
+  if (token_strip_faster(M, strips)) {
+    hipLaunchKernelGGL((k_token_strip<D, OQ, Z, E>), dim3((unsigned)strips), dim3(4 * D), token_strip_lds<D>(), s, a);
+    return hipGetLastError();
+  }
+  constexpr size_t lds = token_block_lds<D>();
   const int64_t per_cu = std::max<int64_t>(1, (int64_t)(M.lds_max / lds));
   const int64_t blocks = std::min<int64_t>((strips + kTbWaves - 1) / kTbWaves, (int64_t)M.cu_count * per_cu);
   hipLaunchKernelGGL((k_token_block<D, OQ, Z, E>), dim3((unsigned)std::max<int64_t>(blocks, 1)), dim3(kTbWaves * 64), lds, s, a);
@@ -2678,6 +2913,10 @@ static hipError_t run_token_block_oq(const Model &M, const TokenBlockArgs &a, hi
 template <int D, int K>
 static const void *token_block_kernel() {
   return (const void *)k_token_block<D, (K & 1) != 0, (K & 2) != 0, (K & 4) != 0>;
+}
+template <int D, int K>
+static const void *token_strip_kernel() {
+  return (const void *)k_token_strip<D, (K & 1) != 0, (K & 2) != 0, (K & 4) != 0>;
 }
 
 hipError_t launch_token_block(const Model &M, int layer, const float *o, const int8_t *oq, const float *ao,
@@ -2778,7 +3017,10 @@ hipError_t set_layered_kernel_attributes(const Model &M) {
       token_block_kernel<64, 6>(),  token_block_kernel<64, 7>(),  token_block_kernel<128, 0>(),
       token_block_kernel<128, 1>(), token_block_kernel<128, 2>(), token_block_kernel<128, 3>(),
       token_block_kernel<128, 4>(), token_block_kernel<128, 5>(), token_block_kernel<128, 6>(),
-      token_block_kernel<128, 7>(),                   (const void *)k_embed_words<64>,
+      token_block_kernel<128, 7>(), token_strip_kernel<128, 0>(), token_strip_kernel<128, 1>(),
+      token_strip_kernel<128, 2>(), token_strip_kernel<128, 3>(), token_strip_kernel<128, 4>(),
+      token_strip_kernel<128, 5>(), token_strip_kernel<128, 6>(), token_strip_kernel<128, 7>(),
+      (const void *)k_embed_words<64>,
       (const void *)k_embed_words<128>};
   for (const void *f : fns) {
     const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)M.lds_max);

@@ -1,9 +1,10 @@
 """Batches smaller than the card decode through other launch shapes than full ones (a word's head
-groups spread over blocks); every shape has to give the bits of the whole-word form, which
+groups spread over blocks, a 16-token strip split over a block's wavefronts); every shape has to give the bits of the whole-word form, which
 test_gpu_parity.py pins to the oracle.
 
 For each attention form the words of one batch too large to be spread are decoded again in the sizes
-where the number of head groups per block changes, down to a single word; results are compared bit
+where the number of head groups per block and the token block's form change (up to 384 strips of 16
+tokens on 256 compute units take a block per strip), down to a single word; results are compared bit
 for bit (the order of every sum is fixed, so the tolerance is zero).
 """
 import numpy as np
@@ -25,10 +26,10 @@ def P():
 
 
 @pytest.mark.parametrize("n,d,heads,attention,hf,form,batch,sizes", [
-    (128, 64, 8, "hpsa", 4, -1, 1100, (1, 5, 130, 200, 300, 520)),     # fp32 K and V, d_h = 8, two blocks a CU
+    (128, 64, 8, "hpsa", 4, -1, 1100, (1, 5, 32, 33, 130, 200, 300, 520)),     # fp32 K and V, d_h = 8, two blocks a CU
     (66, 64, 4, "casa", 2, -1, 1100, (1, 33, 257)),                    # d_h = 16 at d = 64, 99 tokens
     (66, 128, 16, "hpsa", 6, -1, 600, (1, 40, 129)),                   # d_h = 8 at d = 128
-    (256, 128, 8, "hpsa", 4, -1, 600, (1, 2, 37, 70, 129, 260)),       # lane pairs, codes | fp32 O
+    (256, 128, 8, "hpsa", 4, -1, 600, (1, 2, 16, 17, 37, 70, 129, 260)),       # lane pairs, codes | fp32 O
     (270, 128, 8, "casa", 2, -1, 300, (1, 50, 100)),                   # lane pairs, 405 tokens: a second row a pair
     (514, 128, 8, "hpsa", 4, -1, 300, (1, 33, 66, 130)),               # fp32 K, int16 V, 771 tokens
     (398, 64, 8, "hpsa", 4, -1, 600, (1, 70, 140)),                    # int16 K and V, d_h = 8
@@ -36,7 +37,7 @@ def P():
 ])
 def test_spread_head_groups_match_whole_words(P, n, d, heads, attention, hf, form, batch, sizes):
     H = regular_ldpc_3_6(n, seed=1000 + n)
-    w = random_weights(n, n // 2, d, 2, heads, seed=n + d, first_ring_heads=hf, attention=attention)
+    w = random_weights(n, n // 2, d, 3, heads, seed=n + d, first_ring_heads=hf, attention=attention, with_pos=hf == 2)
     y, _, _ = awgn_words(generator_from_parity(H), batch, (2.0, 4.0), seed=n)
     yd = torch.from_numpy(y).cuda()
     dec = P.Decoder(H, w, layered_attention=form)
