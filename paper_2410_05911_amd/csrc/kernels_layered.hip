@@ -113,10 +113,12 @@ __device__ __forceinline__ void embed_row_lo(const EmbedArgs &p, int64_t g, int 
 }
 
 // Lane order, one word per block (persistent over the words): the word's y in LDS, every
-// token's t_i from it (the checks' lists from the L2), then the rows, 16 lanes each.
+// token's t_i from it (the checks' lists from the L2), then the rows, 16 lanes each.  A word's rows
+// are split over gridDim.y blocks of `per` rows each where the batch has fewer words than the card has
+// room for blocks (one word of LDPC(1024,512) took 51 us on one block).
 constexpr int kEwThreads = 256;
 template <int D>
-__global__ __launch_bounds__(kEwThreads) void k_embed_words(EmbedArgs p, int64_t words) {
+__global__ __launch_bounds__(kEwThreads) void k_embed_words(EmbedArgs p, int64_t words, int per) {
   extern __shared__ float esm[];   // [n] the word's y, [L] its t
   float *ys = esm, *ts = esm + p.n;
   const int tid = threadIdx.x, c = tid & 15;
@@ -124,7 +126,8 @@ __global__ __launch_bounds__(kEwThreads) void k_embed_words(EmbedArgs p, int64_t
     const float *yw = p.y + w * p.n;
     for (int i = tid; i < p.n; i += kEwThreads) ys[i] = yw[i];
     __syncthreads();
-    for (int i = tid; i < p.L; i += kEwThreads) {
+    const int r0 = (int)blockIdx.y * per, r1 = min(p.L, r0 + per);
+    for (int i = r0 + tid; i < r1; i += kEwThreads) {
       float t;
       if (i < p.n) {
         t = fabsf(ys[i]);
@@ -136,7 +139,7 @@ __global__ __launch_bounds__(kEwThreads) void k_embed_words(EmbedArgs p, int64_t
       ts[i] = t;
     }
     __syncthreads();
-    for (int i = tid >> 4; i < p.L; i += kEwThreads / 16) embed_row_lo<D>(p, w * p.L + i, i, ts[i], c);
+    for (int i = r0 + (tid >> 4); i < r1; i += kEwThreads / 16) embed_row_lo<D>(p, w * p.L + i, i, ts[i], c);
     __syncthreads();   // the next word overwrites y and t
   }
 }
@@ -2317,46 +2320,74 @@ __global__ __launch_bounds__(256) void k_head_z(HeadArgs p, int64_t rows, float 
   }
 }
 
-constexpr int kHeadWords = 16, kHeadOuts = 64, kHeadK = 32;
+constexpr int kHeadOuts = 64;
 
-// Block (word tile, output tile): thread (w = tid / 16, j = tid % 16) owns word w and outputs
-// 4 j .. 4 j + 3 of the tile.  Per chunk of 32 tokens the tile's z values and W_o rows are
-// staged in LDS; the chunk length is the same for every thread (the order of the chains).
+// Block (word tile of WT words, output tile): thread (wl, j) owns word wl and outputs U j .. U j + U - 1
+// of the tile.  Chunks of KC tokens, the tile's z values and W_o rows, go through two LDS buffers: the
+// next chunk is read into registers while the current one is multiplied, so a chunk costs its chain of
+// KC multiply-adds or one L2 latency, not both.  Chunks of 32 tokens read, awaited and multiplied in turn
+// took 2.3 us each whatever the batch (LDPC(1024,512), one word: 113 of the decode's 623 us).  WT = 4 with
+// KC = 128 where WT = 16 leaves compute units without a block (one output per thread, four times the
+// blocks).
+template <int WT, int KC>
 __global__ __launch_bounds__(256) void k_head_gemm(HeadArgs p, int64_t words, const float *z) {
-  __shared__ float zs[kHeadK][kHeadWords];
-  __shared__ __attribute__((aligned(16))) float ws[kHeadK][kHeadOuts];
-  const int tid = threadIdx.x, wl = tid >> 4, j = tid & 15;
-  const int64_t w0 = (int64_t)blockIdx.x * kHeadWords;
+  constexpr int U = WT * kHeadOuts / 256, TPW = 256 / WT, NZ = (KC * WT + 255) / 256, NWO = KC * kHeadOuts / 256;
+  __shared__ float zs[2][KC][WT];
+  __shared__ __attribute__((aligned(16))) float ws[2][KC][kHeadOuts];
+  const int tid = threadIdx.x, wl = tid / TPW, j = tid % TPW;
+  const int64_t w0 = (int64_t)blockIdx.x * WT;
   const int o0 = blockIdx.y * kHeadOuts;
   const int n = p.n, L = p.L;
-  float acc[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-  for (int i0 = 0; i0 < L; i0 += kHeadK) {
-    const int kc = min(kHeadK, L - i0);
-    for (int u = tid; u < kHeadK * kHeadWords; u += 256) {      // z of the tile's words
-      const int k = u / kHeadWords, w = u % kHeadWords;
-      const int64_t wg = w0 + w;
-      zs[k][w] = (k < kc && wg < words) ? z[wg * L + i0 + k] : 0.0f;
+  float acc[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) acc[u] = 0.0f;
+  float rz[NZ], rw[NWO];
+  auto load = [&](int i0) {
+#pragma unroll
+    for (int u = 0; u < NZ; ++u) {                              // z of the tile's words, tokens on adjacent lanes
+      const int e = tid + 256 * u, k = e % KC, w = e / KC;
+      rz[u] = (w < WT && i0 + k < L && w0 + w < words) ? z[(w0 + w) * L + i0 + k] : 0.0f;
     }
-    for (int u = tid; u < kHeadK * kHeadOuts; u += 256) {       // rows i0 .. i0 + kc - 1 of W_o
-      const int k = u / kHeadOuts, o = u % kHeadOuts;
-      ws[k][o] = (k < kc && o0 + o < n) ? p.wo[(int64_t)(i0 + k) * n + o0 + o] : 0.0f;
+#pragma unroll
+    for (int u = 0; u < NWO; ++u) {                             // rows i0 .. of W_o
+      const int e = tid + 256 * u, k = e / kHeadOuts, o = e % kHeadOuts;
+      rw[u] = (i0 + k < L && o0 + o < n) ? p.wo[(int64_t)(i0 + k) * n + o0 + o] : 0.0f;
     }
-    __syncthreads();
+  };
+  load(0);
+  for (int i0 = 0, b = 0; i0 < L; i0 += KC, b ^= 1) {
+#pragma unroll
+    for (int u = 0; u < NZ; ++u) {
+      const int e = tid + 256 * u, k = e % KC, w = e / KC;
+      if (w < WT) zs[b][k][w] = rz[u];
+    }
+#pragma unroll
+    for (int u = 0; u < NWO; ++u) {
+      const int e = tid + 256 * u;
+      ws[b][e / kHeadOuts][e % kHeadOuts] = rw[u];
+    }
+    __syncthreads();   // the buffer written next was last read before this barrier
+    if (i0 + KC < L) load(i0 + KC);
+    const int kc = min(KC, L - i0);
+#pragma unroll 8
     for (int k = 0; k < kc; ++k) {
-      const float zv = zs[k][wl];
-      const float4 wv = *(const float4 *)&ws[k][4 * j];
-      acc[0] = __builtin_fmaf(zv, wv.x, acc[0]);
-      acc[1] = __builtin_fmaf(zv, wv.y, acc[1]);
-      acc[2] = __builtin_fmaf(zv, wv.z, acc[2]);
-      acc[3] = __builtin_fmaf(zv, wv.w, acc[3]);
+      const float zv = zs[b][k][wl];
+      if constexpr (U == 4) {
+        const float4 wv = *(const float4 *)&ws[b][k][4 * j];
+        acc[0] = __builtin_fmaf(zv, wv.x, acc[0]);
+        acc[1] = __builtin_fmaf(zv, wv.y, acc[1]);
+        acc[2] = __builtin_fmaf(zv, wv.z, acc[2]);
+        acc[3] = __builtin_fmaf(zv, wv.w, acc[3]);
+      } else {
+        acc[0] = __builtin_fmaf(zv, ws[b][k][j], acc[0]);
+      }
     }
-    __syncthreads();
   }
   const int64_t w = w0 + wl;
   if (w >= words) return;
 #pragma unroll
-  for (int u = 0; u < 4; ++u) {
-    const int o = o0 + 4 * j + u;
+  for (int u = 0; u < U; ++u) {
+    const int o = o0 + U * j + u;
     if (o >= n) break;
     const float f = acc[u] + p.bo[o];
     const float yv = p.y[w * n + o];
@@ -2462,9 +2493,12 @@ hipError_t launch_embed(const Model &M, const float *y, int64_t words, float *x,
   if (lane_order) {
     const size_t lds = embed_words_lds(M);
     if (lds <= M.lds_max) {
-      const unsigned wgrid = (unsigned)std::min<int64_t>(words, (int64_t)M.cu_count * 8);
-      if (M.d == 64) hipLaunchKernelGGL((k_embed_words<64>), dim3(wgrid), dim3(kEwThreads), lds, s, a, words);
-      else hipLaunchKernelGGL((k_embed_words<128>), dim3(wgrid), dim3(kEwThreads), lds, s, a, words);
+      // two blocks per compute unit in all, at least 16 rows (one pass of its 16 row lanes) each
+      const int64_t parts = std::max<int64_t>(1, std::min<int64_t>((M.L + 15) / 16, 2 * (int64_t)M.cu_count / words));
+      const int per = (int)((M.L + parts - 1) / parts + 15) / 16 * 16;
+      const dim3 wgrid((unsigned)std::min<int64_t>(words, (int64_t)M.cu_count * 8), (unsigned)((M.L + per - 1) / per));
+      if (M.d == 64) hipLaunchKernelGGL((k_embed_words<64>), wgrid, dim3(kEwThreads), lds, s, a, words, per);
+      else hipLaunchKernelGGL((k_embed_words<128>), wgrid, dim3(kEwThreads), lds, s, a, words, per);
     } else if (M.d == 64) {
       hipLaunchKernelGGL((k_embed<64, true>), grid, dim3(256), 0, s, a);
     } else {
@@ -2971,8 +3005,13 @@ hipError_t launch_head_tiled(const Model &M, const float *x, const float *y, int
       break;
     default: return hipErrorInvalidValue;
   }
-  const dim3 grid((unsigned)((words + kHeadWords - 1) / kHeadWords), (unsigned)((M.n + kHeadOuts - 1) / kHeadOuts));
-  hipLaunchKernelGGL(k_head_gemm, grid, dim3(256), 0, s, a, words, (const float *)zbuf);
+  const unsigned gy = (unsigned)((M.n + kHeadOuts - 1) / kHeadOuts);
+  const int64_t gx = (words + 15) / 16;
+  if (gx * gy >= M.cu_count)
+    hipLaunchKernelGGL((k_head_gemm<16, 64>), dim3((unsigned)gx, gy), dim3(256), 0, s, a, words, (const float *)zbuf);
+  else
+    hipLaunchKernelGGL((k_head_gemm<4, 128>), dim3((unsigned)((words + 3) / 4), gy), dim3(256), 0, s, a, words,
+                       (const float *)zbuf);
   return hipGetLastError();
 }
 
