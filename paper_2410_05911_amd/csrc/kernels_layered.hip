@@ -488,6 +488,8 @@ struct QkvAttnArgs {
   int resident;                // k_qkv_attention: the weight tiles of all the block's head groups stay in LDS
   int g_per;                   // head groups per block (blockIdx.y-th run of them): all of them, or, for a
                                // batch of fewer words than blocks that run at once, a part
+  int row_parts;               // k_qkv_attention_v16: blocks (blockIdx.z) that share a word's rows of a head
+                               // group, each projecting all of its keys and values
   // k_qkv_attention_split: the same lists with every entry counted from the first token of its
   // node type (variables from 0, checks from n), the variable count n, and the LDS capacity in
   // tokens of the larger node type
@@ -1445,6 +1447,7 @@ __global__ __launch_bounds__(kQvThreads) void k_qkv_attention_v16(QkvAttnArgs p)
       for (int j = 0; j < TW / 2; ++j) {
         const int ta = 2 * wg + 2 * NWV * j;   // the pair's first tile
         if (ta >= ntiles) break;
+        if (j % p.row_parts != (int)blockIdx.z) continue;
         // the pair's queries, transposed: lane (t, r) gets query dimensions 4 r + i of token t
         // of each tile, dequantised as the projection defines them
         v4i qa = v4i{0, 0, 0, 0}, qb = v4i{0, 0, 0, 0};
@@ -2838,7 +2841,15 @@ bool qkv_attention_v16_supported(const Model &M) {
 template <int D>
 static hipError_t run_qkv_attention_v16(const Model &M, const QkvAttnArgs &a, size_t lds, hipStream_t s) {
   const int64_t per_cu = std::max<int64_t>(1, (int64_t)(M.lds_max / lds));
-  hipLaunchKernelGGL((k_qkv_attention_v16<D>), attention_grid(M, a, per_cu), dim3(kQvThreads), lds, s, a);
+  QkvAttnArgs b = a;
+  dim3 grid = attention_grid(M, a, per_cu);
+  // with one head group a block and compute units to spare, a wavefront's tile pairs over 2 or 4 blocks:
+  // the rows of its pairs run one after the other (LDPC(1024,512), one word: 517 -> 381 us)
+  b.row_parts = 1;
+  while (a.g_per == 1 && b.row_parts < kQvTilesPerWave / 2 && 2 * b.row_parts * (int64_t)grid.x * grid.y <= M.cu_count)
+    b.row_parts *= 2;
+  grid.z = (unsigned)b.row_parts;
+  hipLaunchKernelGGL((k_qkv_attention_v16<D>), grid, dim3(kQvThreads), lds, s, b);
   return hipGetLastError();
 }
 
