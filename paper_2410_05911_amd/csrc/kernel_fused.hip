@@ -1,4 +1,5 @@
-// Fused path: one wavefront decodes one whole word, every layer, in one launch.
+// Fused path: one wavefront decodes one whole word, every layer, in one launch (for batches smaller
+// than the card, one wavefront per token tile of the word, the word's wavefronts in one block).
 //
 // Shapes: d = 32, 8 heads of 4, d_ff = 128, L = n + m <= 64 tokens, n <= 64.  A word's
 // tokens fill NT = ceil(L / 16) tiles of 16 token "slots"; the host orders tokens by
@@ -237,19 +238,34 @@ __device__ __forceinline__ void attend_tile(const float (&q)[4], const uint16_t 
 
 }  // namespace
 
-template <int NT, int WAVES>
+// SPLIT: a word's NT token tiles run on NT wavefronts of its block (a block decodes waves / NT words at a
+// time), which exchange keys, values and the head's z through LDS and the block's barrier.  A single
+// wavefront walks its tiles' neighbour loops one after the other: BCH(31,16), one word, 63 us.
+template <int NT, int WAVES, bool SPLIT>
 __global__ __launch_bounds__(WAVES * 64, 1) void k_fused_decode(FusedArgs p) {
+  constexpr int TW = SPLIT ? 1 : NT;   // tiles of a wavefront
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   const int tid = threadIdx.x, nthr = blockDim.x;
   // ---- one-time staging: packed ternary fragments -> int8, per-layer vectors, tables ----
   {
-    uint64_t *sf = (uint64_t *)smem;
-    const int nf = p.N * fz::FRAGS * 64;
-    for (int u = tid; u < nf; u += nthr) sf[u] = unpack_ternary8(p.frag[u]);
-    float *sv = (float *)(smem + p.off_vec);
-    for (int u = tid; u < p.N * fz::VEC; u += nthr) sv[u] = p.vec[u];
-    uint32_t *sn = (uint32_t *)(smem + p.off_nbr);
-    for (int u = tid; u < p.nbr_words; u += nthr) sn[u] = p.nbr[u];
+    // 16-byte loads (no measurable difference to 2-byte ones: BCH(31,16), one word, 62 us either way)
+    const uint4 *gf = (const uint4 *)p.frag;
+    ulonglong2 *sf = (ulonglong2 *)smem;
+    const int nf = p.N * fz::FRAGS * 8;
+#pragma unroll 2
+    for (int u = tid; u < nf; u += nthr) {
+      const uint4 q = gf[u];
+      const uint32_t w[4] = {q.x, q.y, q.z, q.w};
+#pragma unroll
+      for (int k = 0; k < 4; ++k) sf[4 * u + k] = make_ulonglong2(unpack_ternary8(w[k] & 0xffffu), unpack_ternary8(w[k] >> 16));
+    }
+    static_assert(fz::VEC % 4 == 0, "vectors in 16-byte groups");
+    float4 *sv = (float4 *)(smem + p.off_vec);
+#pragma unroll 2
+    for (int u = tid; u < p.N * fz::VEC / 4; u += nthr) sv[u] = ((const float4 *)p.vec)[u];
+    uint4 *sn = (uint4 *)(smem + p.off_nbr);
+#pragma unroll 2
+    for (int u = tid; u < p.nbr_words / 4; u += nthr) sn[u] = ((const uint4 *)p.nbr)[u];
     uint32_t *ss = (uint32_t *)(smem + p.off_slot);
     for (int u = tid; u < 32 * NT; u += nthr) ss[u] = p.slot_tab[u];
     uint64_t *sc = (uint64_t *)(smem + p.off_chk);
@@ -269,11 +285,15 @@ __global__ __launch_bounds__(WAVES * 64, 1) void k_fused_decode(FusedArgs p) {
   const int32_t *stok = (const int32_t *)(smem + p.off_tok);
   // Keys (then values) of the current head group, head-major: head h of slot s at
   // (h * 16 NT + s) * 16 bytes, so the 16 lanes of one head gather from all banks.
-  unsigned char *kv = smem + p.off_kv + wave * p.kv_bytes;
+  // SPLIT: one buffer per word, the wavefront's tile t0 of word slot ws of the block.
+  const int ws = SPLIT ? wave / NT : wave, t0 = SPLIT ? wave - ws * NT : 0, nslot = SPLIT ? nw / NT : nw;
+  unsigned char *kv = smem + p.off_kv + ws * p.kv_bytes;
+  const auto sync_word = [] { if constexpr (SPLIT) __syncthreads(); else wave_sync_lds(); };
+  const auto tile = [&](int t) { return SPLIT ? t0 : t; };
   constexpr int HS = (16 * NT + 1) * 16;   // one head: 16 NT slot rows and the pad row
   const int vofs = 4 * HS;                 // values follow the keys of all four heads
   unsigned char *kbase = kv + g * HS;
-  if (lane < 4) {                          // pad rows of the four heads: key NaN, value 0
+  if (lane < 4 && t0 == 0) {               // pad rows of the four heads: key NaN, value 0
     *(float4 *)(kv + lane * HS + 16 * NT * 16) = make_float4(__builtin_nanf(""), __builtin_nanf(""),
                                                              __builtin_nanf(""), __builtin_nanf(""));
     *(float4 *)(kv + vofs + lane * HS + 16 * NT * 16) = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
@@ -286,28 +306,33 @@ __global__ __launch_bounds__(WAVES * 64, 1) void k_fused_decode(FusedArgs p) {
   // blocks: no SIMD then runs more than one word above the others.  v runs over the rounds
   // wave-major, which selects exactly those waves for the last round; w is the word it stands for.
   // (32-bit indices: the launcher passes at most 2^31 - 1 words per launch.)
-  const uint32_t words = (uint32_t)p.words, wt = gridDim.x * (uint32_t)nw, full = words / wt;
+  // SPLIT: word slot ws of block b takes words ws gridDim.x + b, ...; a slot past the batch decodes the
+  // last word again and stores nothing, so that every wavefront of the block meets its barriers.
+  const uint32_t words = (uint32_t)p.words, wt = gridDim.x * (uint32_t)nslot, full = words / wt;
   const uint32_t rq = (words - full * wt) / gridDim.x, rr = words - full * wt - rq * gridDim.x;
   const uint32_t last_w = full * wt + blockIdx.x * rq + min(blockIdx.x, rr) + (uint32_t)wave;
   uint32_t base = blockIdx.x * (uint32_t)nw + (uint32_t)wave;
-  for (uint32_t v = (uint32_t)wave * gridDim.x + blockIdx.x; v < words; v += wt, base += wt) {
-    const int64_t w = base < full * wt ? base : last_w;
+  // SPLIT: uniform over the block (its first slot's word), the same number of rounds for every wavefront
+  for (uint32_t v = SPLIT ? blockIdx.x : (uint32_t)wave * gridDim.x + blockIdx.x; v < words; v += wt, base += wt) {
+    const uint32_t vs = v + (uint32_t)ws * gridDim.x;
+    const bool live = !SPLIT || vs < words;
+    const int64_t w = SPLIT ? (live ? vs : words - 1) : base < full * wt ? base : last_w;
     // Per-word copy of the lane index: the addresses of the embedding and head steps derive
     // from it, so they are recomputed per word rather than held through the layers.
     int lw = lane;
     asm volatile("" : "+v"(lw));
     const int cw = lw & 15, gw = lw >> 4;
-    int tok[NT];
+    int tok[TW];
 #pragma unroll
-    for (int t = 0; t < NT; ++t) tok[t] = stok[16 * t + cw];
+    for (int t = 0; t < TW; ++t) tok[t] = stok[16 * tile(t) + cw];
     // ---- pre-processing h(y) (Section 3) and embedding ----
     const float *yw = p.y + w * p.n;
     const float ylane = lw < p.n ? yw[lw] : 0.0f;
     const uint64_t neg = __ballot(ylane < 0.0f);
-    float X[NT][8], al[NT];
-    uint32_t xb[NT][2];
+    float X[TW][8], al[TW];
+    uint32_t xb[TW][2];
 #pragma unroll
-    for (int t = 0; t < NT; ++t) {
+    for (int t = 0; t < TW; ++t) {
       const int tk = tok[t];
       const float yv = __builtin_bit_cast(
           float, __builtin_amdgcn_ds_bpermute(((tk >= 0 && tk < p.n) ? tk : 0) << 2, __builtin_bit_cast(int, ylane)));
@@ -320,12 +345,12 @@ __global__ __launch_bounds__(WAVES * 64, 1) void k_fused_decode(FusedArgs p) {
           tv = s ? -1.0f : 1.0f;
         }
       }
-      const float4 *er = (const float4 *)(p.eperm + ((16 * t + cw) * 4 + gw) * 8);
+      const float4 *er = (const float4 *)(p.eperm + ((16 * tile(t) + cw) * 4 + gw) * 8);
       const float4 e0 = er[0], e1 = er[1];
       const float ev[8] = {e0.x, e0.y, e0.z, e0.w, e1.x, e1.y, e1.z, e1.w};
       float pv[8] = {0, 0, 0, 0, 0, 0, 0, 0};
       if (p.pperm) {
-        const float4 *pr = (const float4 *)(p.pperm + ((16 * t + cw) * 4 + gw) * 8);
+        const float4 *pr = (const float4 *)(p.pperm + ((16 * tile(t) + cw) * 4 + gw) * 8);
         const float4 p0 = pr[0], p1 = pr[1];
         pv[0] = p0.x; pv[1] = p0.y; pv[2] = p0.z; pv[3] = p0.w;
         pv[4] = p1.x; pv[5] = p1.y; pv[6] = p1.z; pv[7] = p1.w;
@@ -342,12 +367,12 @@ __global__ __launch_bounds__(WAVES * 64, 1) void k_fused_decode(FusedArgs p) {
       const float sq_o = V[fz::V_SQ + 3], sq_1 = V[fz::V_SQ + 4], sq_2 = V[fz::V_SQ + 5];
       // ---- per head group (heads g, then 4 + g): queries, keys, values (Eq. 3) of that
       // group, keys and values to LDS, then head-partitioned attention (Section 4.2) ----
-      float ob[NT][8];
+      float ob[TW][8];
 #pragma unroll
       for (int grp = 0; grp < 2; ++grp) {
         // keys and values of every tile to LDS; queries are made per tile just before use
 #pragma unroll
-        for (int t = 0; t < NT; ++t) {
+        for (int t = 0; t < TW; ++t) {
           const long bop = as_long(xb[t][0], xb[t][1]);
           const v4i ak = mfma_i8_16x16x32((long)F[(2 + grp) * 64], bop, v4i{0, 0, 0, 0});
           const v4i av = mfma_i8_16x16x32((long)F[(4 + grp) * 64], bop, v4i{0, 0, 0, 0});
@@ -359,13 +384,13 @@ __global__ __launch_bounds__(WAVES * 64, 1) void k_fused_decode(FusedArgs p) {
             kk[i] = __builtin_fmaf((float)ak[i], sck, bq[32 + i]);
             vv[i] = __builtin_fmaf((float)av[i], scv, bq[64 + i]);
           }
-          *(float4 *)(kbase + (16 * t + c) * 16) = make_float4(kk[0], kk[1], kk[2], kk[3]);
-          *(float4 *)(kbase + vofs + (16 * t + c) * 16) = make_float4(vv[0], vv[1], vv[2], vv[3]);
+          *(float4 *)(kbase + (16 * tile(t) + c) * 16) = make_float4(kk[0], kk[1], kk[2], kk[3]);
+          *(float4 *)(kbase + vofs + (16 * tile(t) + c) * 16) = make_float4(vv[0], vv[1], vv[2], vv[3]);
         }
-        wave_sync_lds();
+        sync_word();
         const int mask = grp == 0 ? mask1 : mask2;
 #pragma unroll
-        for (int t = 0; t < NT; ++t) {
+        for (int t = 0; t < TW; ++t) {
           const v4i aq =
               mfma_i8_16x16x32((long)F[(0 + grp) * 64], as_long(xb[t][0], xb[t][1]), v4i{0, 0, 0, 0});
           const float scq = al[t] * sq_q;
@@ -373,18 +398,18 @@ __global__ __launch_bounds__(WAVES * 64, 1) void k_fused_decode(FusedArgs p) {
           float q[4];
 #pragma unroll
           for (int i = 0; i < 4; ++i) q[i] = __builtin_fmaf((float)aq[i], scq, bq[i]);
-          const uint32_t st = sslot[(16 * t + c) * 2 + mask];
-          const int T = (int)__builtin_amdgcn_readfirstlane(p.tile_tab[2 * t + grp]);
+          const uint32_t st = sslot[(16 * tile(t) + c) * 2 + mask];
+          const int T = (int)__builtin_amdgcn_readfirstlane(p.tile_tab[2 * tile(t) + grp]);
           float o[4];
           attend_tile(q, snbr + (st & 0xffff), (int)(st >> 16), T, kbase, vofs, o);
 #pragma unroll
           for (int i = 0; i < 4; ++i) ob[t][4 * grp + i] = o[i];
         }
-        wave_sync_lds();
+        sync_word();
       }
       // ---- output projection, residual, LN1 (Section 6), Eq. 2 ----
 #pragma unroll
-      for (int t = 0; t < NT; ++t) {
+      for (int t = 0; t < TW; ++t) {
         uint32_t lo, hi;
         const float ao = quant8(ob[t], lo, hi);
         const long bop = as_long(lo, hi);
@@ -402,7 +427,7 @@ __global__ __launch_bounds__(WAVES * 64, 1) void k_fused_decode(FusedArgs p) {
       }
       // ---- feed-forward block with ReLU, residual, LN2, Eq. 2 ----
 #pragma unroll
-      for (int t = 0; t < NT; ++t) {
+      for (int t = 0; t < TW; ++t) {
         const long bop = as_long(xb[t][0], xb[t][1]);
         v4i acc[8];
 #pragma unroll
@@ -449,24 +474,24 @@ __global__ __launch_bounds__(WAVES * 64, 1) void k_fused_decode(FusedArgs p) {
       const float4 w0 = wr[0], w1 = wr[1];
       const float wv[8] = {w0.x, w0.y, w0.z, w0.w, w1.x, w1.y, w1.z, w1.w};
 #pragma unroll
-      for (int t = 0; t < NT; ++t) {
+      for (int t = 0; t < TW; ++t) {
         float pr[8];
 #pragma unroll
         for (int v = 0; v < 8; ++v) pr[v] = X[t][v] * wv[v];
         const float z = token_sum(pr) + p.b1;
-        const int tk = stok[16 * t + (lh & 15)];
+        const int tk = stok[16 * tile(t) + (lh & 15)];
         if (lh < 16 && tk >= 0) zbuf[tk] = z;
       }
     }
-    wave_sync_lds();
-    if (lh < p.n) {
+    sync_word();
+    if (lh < p.n && live && t0 == 0) {
       float acc = 0.0f;
       for (int i = 0; i < p.L; ++i) acc = __builtin_fmaf(zbuf[i], p.wo[(int64_t)i * p.n + lh], acc);
       const float f = acc + p.bo[lh];
       p.bits[w * p.n + lh] = (uint8_t)((ylane < 0.0f) != (f < 0.0f));
       if (p.logits) p.logits[w * p.n + lh] = f;
     }
-    wave_sync_lds();
+    sync_word();
   }
 }
 
@@ -525,8 +550,10 @@ bool fused_fits(const Model &M, int nbr_words) { return fused_waves(M, nbr_words
 // The largest dynamic LDS the fused kernel may use on the model's device, set once per model at
 // create time (the launches only choose a size within it).
 hipError_t set_fused_kernel_attributes(const Model &M) {
-  const void *fns[] = {(const void *)k_fused_decode<1, fz::kWaves>, (const void *)k_fused_decode<2, fz::kWaves>,
-                       (const void *)k_fused_decode<3, fz::kWaves>, (const void *)k_fused_decode<4, fz::kWaves>};
+  const void *fns[] = {(const void *)k_fused_decode<1, fz::kWaves, false>, (const void *)k_fused_decode<2, fz::kWaves, false>,
+                       (const void *)k_fused_decode<3, fz::kWaves, false>, (const void *)k_fused_decode<4, fz::kWaves, false>,
+                       (const void *)k_fused_decode<2, fz::kWaves, true>, (const void *)k_fused_decode<3, fz::kWaves, true>,
+                       (const void *)k_fused_decode<4, fz::kWaves, true>};
   const int lds = (int)std::min<size_t>(M.lds_max, fz::kLdsMax);
   for (const void *f : fns) {
     const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
@@ -535,9 +562,9 @@ hipError_t set_fused_kernel_attributes(const Model &M) {
   return hipSuccess;
 }
 
-template <int NT, int WAVES>
+template <int NT, int WAVES, bool SPLIT>
 static hipError_t launch_nt(const FusedArgs &a, size_t lds, int grid, int waves, hipStream_t s) {
-  hipLaunchKernelGGL((k_fused_decode<NT, WAVES>), dim3(grid), dim3(waves * 64), lds, s, a);
+  hipLaunchKernelGGL((k_fused_decode<NT, WAVES, SPLIT>), dim3(grid), dim3(waves * 64), lds, s, a);
   return hipGetLastError();
 }
 
@@ -594,15 +621,29 @@ hipError_t launch_fused(const Model &M, const float *y, int64_t words, uint8_t *
   if (waves < 1 || waves > fz::kWaves || off + (size_t)waves * a.kv_bytes > lds_max)
     return hipErrorInvalidConfiguration;
   const size_t lds = off + (size_t)waves * a.kv_bytes;
-  int64_t blocks = (words + waves - 1) / waves;
   const int64_t per_cu = (int64_t)(lds_max / lds) > 0 ? (int64_t)(lds_max / lds) : 1;
   const int64_t cap = (int64_t)M.cu_count * per_cu;
-  const int grid = (int)(blocks < cap ? blocks : cap);
+  // a block for every `waves` words, but a small batch spreads over the compute units (BCH(31,16), 256
+  // words: 101 us on 22 full blocks, 63 on 256 of one word)
+  const int grid = (int)std::min<int64_t>(std::max<int64_t>((words + waves - 1) / waves, std::min<int64_t>(words, M.cu_count)), cap);
+  // a word's tiles over wavefronts while one round of blocks holds the batch that way: BCH(31,16) 1-256
+  // words 63 -> 35 us, 512 words 67 -> 37, 1024 words 72 -> 52 (a wavefront alone keeps three quarters of
+  // its SIMD's issue slots busy, so beyond that round the split has nothing left to fill)
+  const int slots = waves / NT;
+  if (NT > 1 && words <= M.cu_count * (int64_t)slots) {
+    const int sw = (int)std::min<int64_t>(slots, (words + M.cu_count - 1) / M.cu_count) * NT;
+    const int sgrid = (int)std::min<int64_t>(words, M.cu_count);
+    switch (NT) {
+      case 2: return launch_nt<2, fz::kWaves, true>(a, lds, sgrid, sw, s);
+      case 3: return launch_nt<3, fz::kWaves, true>(a, lds, sgrid, sw, s);
+      case 4: return launch_nt<4, fz::kWaves, true>(a, lds, sgrid, sw, s);
+    }
+  }
   switch (NT) {
-    case 1: return launch_nt<1, fz::kWaves>(a, lds, grid, waves, s);
-    case 2: return launch_nt<2, fz::kWaves>(a, lds, grid, waves, s);
-    case 3: return launch_nt<3, fz::kWaves>(a, lds, grid, waves, s);
-    case 4: return launch_nt<4, fz::kWaves>(a, lds, grid, waves, s);
+    case 1: return launch_nt<1, fz::kWaves, false>(a, lds, grid, waves, s);
+    case 2: return launch_nt<2, fz::kWaves, false>(a, lds, grid, waves, s);
+    case 3: return launch_nt<3, fz::kWaves, false>(a, lds, grid, waves, s);
+    case 4: return launch_nt<4, fz::kWaves, false>(a, lds, grid, waves, s);
   }
   return hipErrorInvalidValue;
 }

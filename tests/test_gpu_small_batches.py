@@ -1,6 +1,6 @@
 """Batches smaller than the card decode through other launch shapes than full ones (a word's head
-groups spread over blocks, a 16-token strip split over a block's wavefronts); every shape has to give the bits of the whole-word form, which
-test_gpu_parity.py pins to the oracle.
+groups spread over blocks, a 16-token strip or a short word's tiles over wavefronts); every shape has
+to give the bits of the whole-word form, which test_gpu_parity.py pins to the oracle.
 
 For each attention form the words of one batch too large to be spread are decoded again in the sizes
 where the number of head groups per block and the token block's form change (up to 384 strips of 16
@@ -50,4 +50,29 @@ def test_spread_head_groups_match_whole_words(P, n, d, heads, attention, hf, for
         b, f = dec.decode(yd[at:at + k].contiguous())
         torch.cuda.synchronize()
         assert torch.equal(f, logits[at:at + k]) and torch.equal(b, bits[at:at + k])
+    dec.close()
+
+
+@pytest.mark.parametrize("n,m,attention,sizes", [
+    (7, 3, "hpsa", (1, 64, 300)),                       # one token tile: never split
+    (20, 10, "hpsa", (1, 5, 257, 1537, 1536)),          # two tiles, up to six words a block
+    (31, 15, "casa", (1, 255, 256, 257, 513, 1024, 1025)),   # three tiles, up to four words a block
+    (40, 20, "hpsa", (1, 256, 700, 768, 769)),          # four tiles, up to three words a block
+])
+def test_fused_word_over_wavefronts_matches_one_wavefront(P, n, m, attention, sizes):
+    rng = np.random.default_rng(n)
+    H = (rng.random((m, n)) < 0.3).astype(np.uint8)
+    H[np.arange(n) % m, np.arange(n)] = 1               # no empty row or column
+    w = random_weights(n, m, 32, 3, seed=n, attention=attention, with_pos=m == 20)
+    batch = 3500
+    yd = torch.from_numpy((1.0 + 0.6 * rng.standard_normal((batch, n))).astype(np.float32)).cuda()
+    dec = P.Decoder(H, w, path=P.PATH_FUSED)
+    bits, logits = dec.decode(yd)
+    torch.cuda.synchronize()
+    assert np.isfinite(logits.cpu().numpy()).all()
+    for k in sizes:
+        print(f"[small] fused n {n} m {m} {attention}: {k} words", flush=True)
+        b, f = dec.decode(yd[batch - k:].contiguous())
+        torch.cuda.synchronize()
+        assert torch.equal(f, logits[batch - k:]) and torch.equal(b, bits[batch - k:])
     dec.close()
