@@ -195,46 +195,85 @@ struct TrainDeltaJobs { TrainDeltaJob j[kTrainJobsPerLaunch]; int n; };
 hipError_t train_aap(const TrainAapJobs &jobs, float eps, hipStream_t s);
 hipError_t train_delta_grad(const TrainDeltaJobs &jobs, float eps, hipStream_t s);
 hipError_t train_embed(const float *y, int64_t rows, int n, int L, int d, const int32_t *chk_ptr,
-                       const int32_t *chk_idx, const float *E, const float *P, float *x, float *t, hipStream_t s);
-hipError_t train_quant(const float *x, int64_t rows, int K, bool relu, float *xh, hipStream_t s);
-// C[M][N] = (accumulate ? C : 0) + scale (op(A) op(B)) + bias; ta: A stored [K][M]; tb: B stored [N][K].
-// part: scratch of part_floats floats for split reductions over K.
-// Products with a ternary right operand on the bf16 matrix cores (fp32 A split exactly into three
-// bf16 parts): train_pack_tern lays each job's T [R][C] (or its transpose) out as B fragments in
-// out (2 R C bytes), train_gemm_tern forms C = beta C + scale (A B) + bias; N a multiple of 64, K
-// of 32, A, C and the bias 16-byte aligned with lda and ldc multiples of 4 (train_tern_operands_ok).
-bool train_tern_shape_ok(int64_t N, int64_t K);
-bool train_tern_operands_ok(const float *A, int64_t lda, const float *C, int64_t ldc, const float *bias, int64_t N,
-                            int64_t K);
+                       const int32_t *chk_idx, const float *E, const float *P, float *x, float *t, int8_t *xq, float *tx,
+                       hipStream_t s);
+// A ternary matrix T [R][C] (fp32) laid out for the products that read it: int8 fragments for the forward
+// (R C bytes), bf16 fragments of T^T for the input gradients (2 R C bytes); R and C multiples of 32.
+enum TernPackMode { kTernI8 = 0, kTernI8Hidden = 1, kTernBf16T = 2 };
 struct TernPackJob {
   const float *T;
-  int R, C, trans;
+  int R, C, mode;
   void *out;
 };
 struct TernPackJobs { TernPackJob j[kTrainJobsPerLaunch]; int n; };
 hipError_t train_pack_tern(const TernPackJobs &jobs, hipStream_t s);
-hipError_t train_gemm_tern(const float *A, int64_t lda, const void *frag, float *C, int64_t ldc, int64_t M, int64_t N,
-                           int64_t K, const float *scale, const float *bias, bool accumulate, hipStream_t s);
-// nseg (<= 3) ternary matrices side by side: C[:, k seg_n .. (k + 1) seg_n) = beta C + scale[k] (A T_k) +
-// bias[k] for each k, over one read of A
-hipError_t train_gemm_tern_seg(const float *A, int64_t lda, const void *const *frag, float *C, int64_t ldc, int64_t M,
-                               int64_t seg_n, int nseg, int64_t K, const float *const *scale, const float *const *bias,
-                               bool accumulate, hipStream_t s);
-// C = D + sum_k scale[k] (A[:, k kseg .. (k + 1) kseg) T_k) over nseg (<= 3) ternary matrices along A's
-// row, D (optional, laid out like C, may be C) an addend: the input gradient summed over the query,
-// key and value maps from their packed gradient
-hipError_t train_gemm_tern_ksum(const float *A, int64_t lda, const void *const *frag, int nseg, int64_t kseg,
-                                const float *const *scale, const float *D, float *C, int64_t ldc, int64_t M, int64_t N,
-                                hipStream_t s);
+// Input gradients on the bf16 matrix cores (fp32 A split exactly into three bf16 parts): C = D + sum_k
+// scale[k] (A[:, k kseg .. (k + 1) kseg) T_k^T) over nseg (<= 3) ternary matrices along A's row, D an
+// optional addend laid out like C; with mask (N a multiple of 128) the elements whose bit is 0 become 0.
+// N and kseg multiples of 32, A, C and D 16-byte aligned with lda and ldc multiples of 4.
+hipError_t train_gemm_tern(const float *A, int64_t lda, const void *const *frag, int nseg, int64_t kseg,
+                           const float *const *scale, const float *D, const uint32_t *mask, float *C, int64_t ldc,
+                           int64_t M, int64_t N, hipStream_t s);
+// The query, key and value maps (Eq. 3) of codes xq with row scales tx (alpha / 127): qkv [rows][3 d].
+struct TrainQkv {
+  const int8_t *xq;
+  const float *tx;
+  const uint64_t *f[3];       // int8 fragments (kTernI8)
+  const float *s[3], *b[3];   // Eq. 1 scales (device scalars), biases [d]
+  float *qkv;
+  int64_t rows;
+};
+hipError_t train_qkv(int d, const TrainQkv &a, int cu_count, size_t lds_max, hipStream_t s);
+// The token-local half of a layer's forward: Eq. 2 of O, output map, residual, LN1, Eq. 2, first
+// feed-forward map, ReLU, Eq. 2, second map, residual, LN2 and Eq. 2 of the next layer's input, leaving
+// what the backward reads: the codes and scales (alpha / 127) of every map's input, both normalised
+// rows and their 1 / sigma, and the ReLU mask (layout: GemmTern::mask).
+struct TrainBlock {
+  const float *o;                         // [rows][d]
+  const float *res, *res_g, *res_b;       // X [rows][d], or (res_g not null) xn with X = xn res_g + res_b
+  const uint64_t *fo, *f1, *f2;           // int8 fragments: kTernI8, kTernI8Hidden, kTernI8Hidden
+  const float *so, *s1, *s2;              // Eq. 1 scales (device scalars)
+  const float *bo, *g1, *be1, *b1, *b2, *g2, *be2;
+  float eps;
+  int64_t rows;
+  int8_t *oq, *x1q, *gq;
+  float *to, *t1, *tg;
+  float *xn1, *rho1, *xn2, *rho2;
+  uint32_t *mask;
+  int8_t *xq;                             // the next layer's codes and scales, or null (the last layer)
+  float *tx;
+  float *x;                               // the output X (the last layer), or null
+};
+hipError_t train_block(int d, const TrainBlock &a, int cu_count, size_t lds_max, hipStream_t s);
+hipError_t train_set_attributes(size_t lds_max);   // the current device's dynamic LDS for the two
+// Weight and bias gradients of a layer's maps in one launch and one reduction: dw = Xh^T dY with Xh = codes
+// q [rows][K] x scales t [rows], and the column sums of dY [rows][N] (rows ldy apart); column c goes
+// to gw[c / seg][K][seg] and gb[c / seg].  K, N and seg multiples of d.
+constexpr int kTrainDwJobs = 4;
+struct TrainDwJob {
+  const int8_t *q;
+  const float *t, *dy;
+  int64_t ldy;
+  int K, N, seg;
+  float *gw[3], *gb[3];
+};
+struct TrainDwJobs {
+  TrainDwJob j[kTrainDwJobs];
+  int n;
+  int tile0[kTrainDwJobs + 1];   // filled by the launcher from here on
+  int64_t rows, chunk;
+  int splits;
+  float *part, *cpart;
+};
+int train_dw_splits(int64_t rows, int tiles, int cu_count);   // at most; scratch: splits x tiles x d (d + 1) floats
+hipError_t train_weight_grads(int d, TrainDwJobs &jobs, int cu_count, float *part, int64_t part_floats, hipStream_t s);
+// C[M][N] = (accumulate ? C : 0) + scale (op(A) op(B)) + bias; ta: A stored [K][M]; tb: B stored [N][K].
+// part: scratch of part_floats floats for split reductions over K.
 hipError_t train_gemm(bool ta, bool tb, const float *A, int64_t lda, const float *B, int64_t ldb, float *C, int64_t ldc,
                       int64_t M, int64_t N, int64_t K, const float *scale, const float *bias, bool accumulate,
                       float *part, int64_t part_floats, int cu_count, hipStream_t s);
 // which: 0 forward (o, lse), 1 query gradients (dqkv's Q third, Dv), 2 key and value gradients
 hipError_t train_attention(int which, int dh, const TrainAttn &a, hipStream_t s);
-// out = LN(a + b), xn the normalised row, rho its 1 / sigma; xh (if given) the Eq. 2 codes of out and
-// their values, as train_quant forms them
-hipError_t train_ln_fwd(const float *a, const float *b, int64_t rows, int d, const float *g, const float *beta, float eps,
-                        float *out, float *xn, float *rho, float *xh, hipStream_t s);
 hipError_t train_ln_bwd(const float *dy, const float *g, const float *xn, const float *rho, int64_t rows, int d,
                         float *dR, hipStream_t s);
 // out[c] (+)= sum_r A[r][c] (B[r][c] if B) (w[r] if w), rows of A lda apart, B dense [rows][C]
@@ -244,11 +283,6 @@ hipError_t train_colsum(const float *A, int64_t lda, const float *Bm, const floa
 // shift gradients)
 hipError_t train_colsum_dual(const float *A, int64_t lda, const float *Bm, int64_t rows, int C, float *out_ab,
                              float *out_a, float *part, int64_t part_floats, hipStream_t s);
-// the column sums of A's nseg * seg columns, segment k to outs[k] (nseg <= 3: the query, key and value
-// bias gradients from one pass over the packed [rows][3 d] gradient)
-hipError_t train_colsum_split(const float *A, int64_t lda, int64_t rows, int seg, int nseg, float *const *outs,
-                              float *part, int64_t part_floats, hipStream_t s);
-hipError_t train_relu_bwd(float *dg, const float *f, int64_t count, hipStream_t s);
 hipError_t train_rowdot(const float *x, int64_t rows, int d, const float *w1, const float *b1, float *z, hipStream_t s);
 hipError_t train_outer(const float *dz, int64_t rows, const float *w1, int d, float *dx, hipStream_t s);
 hipError_t train_loss(const float *f, const float *y, const float *xs, int64_t count, float *df, float *part,

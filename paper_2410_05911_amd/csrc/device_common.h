@@ -197,4 +197,54 @@ __device__ __forceinline__ uint64_t unpack_ternary8(uint32_t pk) {
   return out;
 }
 
+// The two values of lanes l and l ^ M (M = 16 or 32) with the gfx950 lane swaps: a swap of v
+// with itself returns, in some order, the lane's own v and its partner's, so their sum or
+// maximum is a butterfly step's (both operations commute).  The swap's two results are taken
+// out of its vector as integers: __builtin_bit_cast applied directly to an element of a vector
+// reads element 0 with this compiler.
+template <int M>
+__device__ __forceinline__ void lane_swap_pair(uint32_t v, uint32_t &a, uint32_t &b) {
+  if constexpr (M == 32) {
+    const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+    a = r[0];
+    b = r[1];
+  } else {
+    const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+    a = r[0];
+    b = r[1];
+  }
+}
+// v of this lane plus v of lane l ^ M (the same bits in both lanes)
+template <int M>
+__device__ __forceinline__ float lane_xor_add(float t) {
+  uint32_t a, b;
+  lane_swap_pair<M>(__builtin_bit_cast(uint32_t, t), a, b);
+  return __builtin_bit_cast(float, a) + __builtin_bit_cast(float, b);
+}
+
+// Byte 0 of eight Eq. 2 code patterns into one 64-bit B operand (byte e from b[e]).
+__device__ __forceinline__ long tb_pack8(const uint32_t (&b)[8]) {
+  const uint32_t lo = __builtin_amdgcn_perm(__builtin_amdgcn_perm(b[3], b[2], 0x0c0c0400u),
+                                            __builtin_amdgcn_perm(b[1], b[0], 0x0c0c0400u), 0x05040100u);
+  const uint32_t hi = __builtin_amdgcn_perm(__builtin_amdgcn_perm(b[7], b[6], 0x0c0c0400u),
+                                            __builtin_amdgcn_perm(b[5], b[4], 0x0c0c0400u), 0x05040100u);
+  return (long)(((uint64_t)hi << 32) | lo);
+}
+
+// Pairwise sum of a token's d features, V of them in each of the four lanes l, l ^ 16, l ^ 32, l ^ 48.
+template <int V>
+__device__ __forceinline__ float tb_token_sum(const float (&x)[V]) {
+  float u[V];
+#pragma unroll
+  for (int v = 0; v < V; ++v) u[v] = x[v];
+  return lane_xor_add<16>(lane_xor_add<32>(lane_tree<V>(u)));
+}
+// Maximum over the four lanes of a token (non-negative floats order like their bit patterns).
+__device__ __forceinline__ float tb_token_max(float a) {
+  uint32_t u = __builtin_bit_cast(uint32_t, a), p, q;
+  lane_swap_pair<32>(u, p, q);
+  lane_swap_pair<16>(max(p, q), p, q);
+  return __builtin_bit_cast(float, max(p, q));
+}
+
 }  // namespace aecct

@@ -19,40 +19,6 @@ template <int D>
 __device__ __forceinline__ int lane_order_x(int f) { return (f & 3) * (D / 4) + (f >> 2); }
 __device__ __forceinline__ int lane_order_q(int f) { return (f & ~31) + 8 * (f & 3) + ((f >> 2) & 7); }
 
-// The two values of lanes l and l ^ M (M = 16 or 32) with the gfx950 lane swaps: a swap of v
-// with itself returns, in some order, the lane's own v and its partner's, so their sum or
-// maximum is a butterfly step's (both operations commute).  The swap's two results are taken
-// out of its vector as integers: __builtin_bit_cast applied directly to an element of a vector
-// reads element 0 with this compiler.
-template <int M>
-__device__ __forceinline__ void lane_swap_pair(uint32_t v, uint32_t &a, uint32_t &b) {
-  if constexpr (M == 32) {
-    const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
-    a = r[0];
-    b = r[1];
-  } else {
-    const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
-    a = r[0];
-    b = r[1];
-  }
-}
-// v of this lane plus v of lane l ^ M (the same bits in both lanes)
-template <int M>
-__device__ __forceinline__ float lane_xor_add(float t) {
-  uint32_t a, b;
-  lane_swap_pair<M>(__builtin_bit_cast(uint32_t, t), a, b);
-  return __builtin_bit_cast(float, a) + __builtin_bit_cast(float, b);
-}
-
-// Byte 0 of eight Eq. 2 code patterns into one 64-bit B operand (byte e from b[e]).
-__device__ __forceinline__ long tb_pack8(const uint32_t (&b)[8]) {
-  const uint32_t lo = __builtin_amdgcn_perm(__builtin_amdgcn_perm(b[3], b[2], 0x0c0c0400u),
-                                            __builtin_amdgcn_perm(b[1], b[0], 0x0c0c0400u), 0x05040100u);
-  const uint32_t hi = __builtin_amdgcn_perm(__builtin_amdgcn_perm(b[7], b[6], 0x0c0c0400u),
-                                            __builtin_amdgcn_perm(b[5], b[4], 0x0c0c0400u), 0x05040100u);
-  return (long)(((uint64_t)hi << 32) | lo);
-}
-
 // ------------------------------------------------------------------------------------------
 // Embedding: pre-processing h(y) (Section 3), X = t * E (+ P), and the Eq. 2 code of X.
 // 16 lanes per row.  Natural layout: lane c holds features c + 16 t, t < D / 16.  LO: X and Xq in
@@ -1731,22 +1697,6 @@ struct TbIn {
 template <int D>
 constexpr size_t token_block_lds() {
   return (size_t)9 * D * D + (size_t)11 * D * 4;
-}
-
-// Pairwise sum of a token's d features held as x[v] = feature 4 v + g.
-template <int V>
-__device__ __forceinline__ float tb_token_sum(const float (&x)[V]) {
-  float u[V];
-#pragma unroll
-  for (int v = 0; v < V; ++v) u[v] = x[v];
-  return lane_xor_add<16>(lane_xor_add<32>(lane_tree<V>(u)));
-}
-// Maximum over the four lanes of a token (non-negative floats order like their bit patterns).
-__device__ __forceinline__ float tb_token_max(float a) {
-  uint32_t u = __builtin_bit_cast(uint32_t, a), p, q;
-  lane_swap_pair<32>(u, p, q);
-  lane_swap_pair<16>(max(p, q), p, q);
-  return __builtin_bit_cast(float, max(p, q));
 }
 
 // Z: the last layer, which leaves the head's z per token (TokenBlockArgs::z) instead of x, xq, ax.

@@ -151,12 +151,16 @@ __global__ __launch_bounds__(kAapThreads) void k_aap(TrainAapJobs jobs, float ep
 }
 
 // ------------------------------------------------------------------------------------------
-// Pre-processing and embedding (Section 3): t = [|y|, 1 - 2 s(y)], X = t E (+ P); one wavefront
-// per token row.
+// Pre-processing and embedding (Section 3): t = [|y|, 1 - 2 s(y)], X = t E (+ P), and the Eq. 2 codes
+// of X with their scale alpha / 127; one wavefront per token row.
+//
+// Every map's input is kept as Eq. 2 codes (int8, natural layout) and t = alpha / 127 per row; the value
+// they stand for is code x t.  The forward maps then are exact integer products scaled once in the
+// epilogue, fma(acc, t s, bias), and the weight gradients take the codes as exact bf16 operands.
 // ------------------------------------------------------------------------------------------
 __global__ __launch_bounds__(kThreads) void k_embed(const float *y, int64_t rows, int n, int L, int d,
                                                     const int32_t *chk_ptr, const int32_t *chk_idx, const float *E,
-                                                    const float *P, float *x, float *tv) {
+                                                    const float *P, float *x, float *tv, int8_t *xq, float *tx) {
   const int64_t r = (int64_t)blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
   if (r >= rows) return;
@@ -171,47 +175,22 @@ __global__ __launch_bounds__(kThreads) void k_embed(const float *y, int64_t rows
     for (int e = chk_ptr[i - n]; e < chk_ptr[i - n + 1]; ++e) s ^= yw[chk_idx[e]] < 0.0f ? 1 : 0;
     t = s ? -1.0f : 1.0f;
   }
-  for (int c = lane; c < d; c += 64) x[r * d + c] = fmaf(t, E[(int64_t)i * d + c], P ? P[(int64_t)i * d + c] : 0.0f);
-  if (lane == 0) tv[r] = t;
-}
-
-// Eq. 2 per token row and the value the codes stand for, q alpha / 127 (0 when alpha = 0); of
-// max(x, 0) when RELU.  One wavefront per row.
-template <bool RELU>
-__global__ __launch_bounds__(kThreads) void k_quant_dequant(const float *x, int64_t rows, int K, float *xh) {
-  const int64_t r = (int64_t)blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6);
-  const int lane = threadIdx.x & 63;
-  if (r >= rows) return;
-  const float *xr = x + r * K;
-  float a = 0.0f;
-  constexpr int kHeld = 8;   // rows up to 512 wide are read whole before their maximum is formed
-  if (K <= 64 * kHeld) {
-    float v[kHeld];
+  float v[2], a = 0.0f;   // d <= 128
 #pragma unroll
-    for (int u = 0; u < kHeld; ++u) v[u] = lane + 64 * u < K ? xr[lane + 64 * u] : 0.0f;
-#pragma unroll
-    for (int u = 0; u < kHeld; ++u) {
-      if (RELU) v[u] = fmaxf(v[u], 0.0f);
-      a = fmaxf(a, fabsf(v[u]));
-    }
-    a = wave_max(a);
-    const float inv = inv127(a);
-#pragma unroll
-    for (int u = 0; u < kHeld; ++u) {
-      const int c = lane + 64 * u;
-      if (c < K) xh[r * K + c] = a == 0.0f ? 0.0f : (float)quant_code(v[u], inv) * a / 127.0f;
-    }
-    return;
-  }
-  for (int c = lane; c < K; c += 64) {
-    const float v = RELU ? fmaxf(xr[c], 0.0f) : xr[c];
-    a = fmaxf(a, fabsf(v));
+  for (int u = 0; u < 2; ++u) {
+    const int c = lane + 64 * u;
+    v[u] = c < d ? fmaf(t, E[(int64_t)i * d + c], P ? P[(int64_t)i * d + c] : 0.0f) : 0.0f;
+    if (c < d) x[r * d + c] = v[u];
+    a = fmaxf(a, fabsf(v[u]));
   }
   a = wave_max(a);
   const float inv = inv127(a);
-  for (int c = lane; c < K; c += 64) {
-    const float v = RELU ? fmaxf(xr[c], 0.0f) : xr[c];
-    xh[r * K + c] = a == 0.0f ? 0.0f : (float)quant_code(v, inv) * a / 127.0f;
+#pragma unroll
+  for (int u = 0; u < 2; ++u)
+    if (lane + 64 * u < d) xq[r * d + lane + 64 * u] = quant_code(v[u], inv);
+  if (lane == 0) {
+    tv[r] = t;
+    tx[r] = a / 127.0f;
   }
 }
 
@@ -447,23 +426,20 @@ __global__ __launch_bounds__(kThreads) void k_gemm_mfma(GemmF32 g) {
 }
 
 // ------------------------------------------------------------------------------------------
-// Products with a ternary operand: C[M][N] = beta C + scale (A B) + bias[N] where B holds only
-// -1, 0, +1 (Eq. 1's T, or its transpose) and A is fp32.  Each fp32 a splits exactly into three
-// bf16 parts, a = hi + mid + lo (hi the leading 8 significant bits by truncation, mid the next 8,
-// lo the remaining at most 8), each part times a ternary entry is exact, and the three
-// v_mfma_f32_16x16x32_bf16 products accumulate in fp32: the result is an fp32-accumulated sum of
-// exact products, as in the fp32 kernels, at the bf16 matrix rate.  B comes pre-packed as bf16 MFMA
-// B fragments (k_pack_tern).  A wave computes 16 rows x 16 NJ columns, a block four waves.
+// Input gradients, products with a ternary operand: C[M][N] = D + sum_s scale_s (A_s T_s^T) where T holds
+// only -1, 0, +1 (Eq. 1) and A is fp32.  Each fp32 a splits exactly into three bf16 parts, a = hi + mid +
+// lo (hi the leading 8 significant bits by truncation, mid the next 8, lo the remaining at most 8), each
+// part times a ternary entry is exact, and the three v_mfma_f32_16x16x32_bf16 products accumulate in
+// fp32: the result is an fp32-accumulated sum of exact products, as in the fp32 kernels, at the bf16
+// matrix rate.  T^T comes pre-packed as bf16 MFMA B fragments (k_pack_tern).  A wave computes 16 rows x
+// 16 NJ columns, a block four waves.
 // ------------------------------------------------------------------------------------------
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-// Up to three ternary matrices in one product, either side by side in C's columns (segments of
-// seg_n columns: the query, key and value maps over one read of their shared input) or one after
-// another along k (segments of kseg k-steps of A's row: the input gradient summed over the three
-// maps from the packed [rows][3 d] gradient).  Segment s has its own fragments and scale, a column
-// segment its own bias; C = D + sum_s scale_s (A_s T_s) + bias, D an optional addend laid out like C
-// (C itself to accumulate).
+// Up to three ternary matrices in one product, one after another along k (segments of kseg k-steps of
+// A's row: the input gradient summed over the query, key and value maps from the packed [rows][3 d]
+// gradient).  Segment s has its own fragments and scale; D is an optional addend laid out like C.
 struct GemmTern {
   const float *A;
   const uint4 *B[3];       // fragment (nt, kt) at (nt * kt_s + kt) * 64, kt_s the segment's k-steps:
@@ -472,8 +448,9 @@ struct GemmTern {
   const float *D;
   int64_t M, N, K, lda, ldc;
   const float *scale[3];   // device scalar or null (1)
-  const float *bias[3];    // [seg_n] or null
-  int64_t seg_n;           // a multiple of the block's 16 NJ columns
+  const uint32_t *mask;    // null, or which elements of C stay (the rest are 0): one bit each, word
+                           // (row * 4 + g) * N / 128 + n / 128, bit 4 ((n / 16) mod 8) + i of column
+                           // n = 16 (n / 16) + 4 g + i (N a multiple of 128, blocks of 128 columns)
   int kseg;                // k-steps per k segment (K / 32 when there is one)
 };
 
@@ -482,25 +459,39 @@ __device__ __forceinline__ T pick3(const T (&v)[3], int i) {   // a selected ker
   return i == 0 ? v[0] : (i == 1 ? v[1] : v[2]);
 }
 
-// Ternary matrix T [R][C] (fp32 -1 / 0 / +1, row-major) as bf16 B fragments of B = T (k = row,
-// n = column) or, with trans, B = T^T (k = column, n = row); one job per blockIdx.y.
+// Ternary matrix T [R][C] (fp32 -1 / 0 / +1, row-major), one job per blockIdx.y, as
+//   kTernBf16T: bf16 B fragments of T^T (k = column, n = row) for the input gradients;
+//   kTernI8, kTernI8Hidden: int8 A fragments of the transposed forward products (output rows = columns
+//   of T, k = rows of T): fragment (t, s), lane l: output 16 t + (l & 15), k-slots 8 (l >> 4) + e in
+//   byte e.  Slot k of step s reads input 32 s + k, or (Hidden) input 32 s + 16 (e >> 2) + 4 (l >> 4) +
+//   (e & 3): the eight codes that the product before leaves in a lane group.
 __global__ __launch_bounds__(kThreads) void k_pack_tern(TernPackJobs jobs) {
   const TernPackJob &J = jobs.j[blockIdx.y];
   const float *T = J.T;
-  const int R = J.R, Cc = J.C, trans = J.trans;
-  uint4 *out = (uint4 *)J.out;
-  const int K = trans ? Cc : R, N = trans ? R : Cc, KT = K / 32;
+  const int R = J.R, Cc = J.C;
   const int64_t u = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-  if (u >= (int64_t)(N / 16) * KT * 64) return;
-  const int l = (int)(u & 63), f = (int)(u >> 6), nt = f / KT, kt = f - nt * KT;
-  const int n = 16 * nt + (l & 15), k0 = 32 * kt + 8 * (l >> 4);
-  uint32_t h[8];
+  if (u >= (int64_t)R * Cc / 8) return;
+  const int l = (int)(u & 63), f = (int)(u >> 6), g = l >> 4;
+  if (J.mode == kTernBf16T) {
+    const int KT = Cc / 32, nt = f / KT, kt = f - nt * KT;
+    const int n = 16 * nt + (l & 15), k0 = 32 * kt + 8 * g;
+    uint32_t h[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const float t = T[(int64_t)n * Cc + k0 + e];
+      h[e] = t > 0.0f ? 0x3F80u : (t < 0.0f ? 0xBF80u : 0u);   // bf16 of +1, -1, 0
+    }
+    ((uint4 *)J.out)[u] = make_uint4(h[0] | h[1] << 16, h[2] | h[3] << 16, h[4] | h[5] << 16, h[6] | h[7] << 16);
+    return;
+  }
+  const int S = R / 32, t = f / S, s = f - t * S, c = 16 * t + (l & 15);
+  uint64_t w = 0;
 #pragma unroll
   for (int e = 0; e < 8; ++e) {
-    const float t = trans ? T[(int64_t)n * Cc + k0 + e] : T[(int64_t)(k0 + e) * Cc + n];
-    h[e] = t > 0.0f ? 0x3F80u : (t < 0.0f ? 0xBF80u : 0u);   // bf16 of +1, -1, 0
+    const int k = 32 * s + (J.mode == kTernI8Hidden ? 16 * (e >> 2) + 4 * g + (e & 3) : 8 * g + e);
+    w |= (uint64_t)(uint8_t)(int8_t)T[(int64_t)k * Cc + c] << (8 * e);
   }
-  out[u] = make_uint4(h[0] | h[1] << 16, h[2] | h[3] << 16, h[4] | h[5] << 16, h[6] | h[7] << 16);
+  ((uint64_t *)J.out)[u] = w;
 }
 
 // the bf16 bit patterns of eight fp32 values that are exact in bf16 (low 16 bits zero)
@@ -540,8 +531,6 @@ template <int NJ, int S>
 __global__ __launch_bounds__(kThreads) void k_gemm_tern(GemmTern g) {
   const int wave = threadIdx.x >> 6, l = threadIdx.x & 63, col = l & 15, grp = l >> 4;
   const int64_t m0 = (int64_t)blockIdx.y * 64 + 16 * wave, n0 = (int64_t)blockIdx.x * (16 * NJ);
-  const int sg = (int)(n0 / g.seg_n);
-  const int64_t ns = n0 - sg * g.seg_n;   // the block's first column inside its segment
   const int KT = (int)(g.K / 32), ks = g.kseg;
   const int64_t r = m0 + col;
   const float *arow = g.A + (r < g.M ? r : g.M - 1) * g.lda + 8 * grp;   // rows past M: a copy, never stored
@@ -556,7 +545,7 @@ __global__ __launch_bounds__(kThreads) void k_gemm_tern(GemmTern g) {
   uint4 b[S][NJ];
   auto issue = [&](int kt, float4 (&as)[2], uint4 (&bs)[NJ]) {
     const int s = kt / ks;   // the k segment (0 with one)
-    const uint4 *bcol = pick3(g.B, sg + s) + (ns / 16) * ks * 64 + l;
+    const uint4 *bcol = pick3(g.B, s) + (n0 / 16) * ks * 64 + l;
 #pragma unroll
     for (int j = 0; j < NJ; ++j) bs[j] = bcol[(j * ks + kt - s * ks) * 64];
     as[0] = *(const float4 *)(arow + 32 * kt);
@@ -582,7 +571,7 @@ __global__ __launch_bounds__(kThreads) void k_gemm_tern(GemmTern g) {
         acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bb, ph, acc[j], 0, 0, 0);
       }
       if (kt + 1 == kend) {   // a k segment's products, scaled, into o
-        const float *sp = pick3(g.scale, sg + kt / ks);
+        const float *sp = pick3(g.scale, kt / ks);
         const float sc = sp ? *sp : 1.0f;
 #pragma unroll
         for (int j = 0; j < NJ; ++j) {
@@ -597,15 +586,16 @@ __global__ __launch_bounds__(kThreads) void k_gemm_tern(GemmTern g) {
     }
   }
   if (r >= g.M) return;
-  const float *bias = pick3(g.bias, sg);
-  if (bias) {
+  if constexpr (NJ == 8) {
+    if (g.mask) {
+      const uint32_t keep = g.mask[(r * 4 + grp) * (g.N / 128) + blockIdx.x];
 #pragma unroll
-    for (int j = 0; j < NJ; ++j) {
-      const float4 bj = *(const float4 *)(bias + ns + 16 * j + 4 * grp);
-      o[j].x += bj.x;
-      o[j].y += bj.y;
-      o[j].z += bj.z;
-      o[j].w += bj.w;
+      for (int j = 0; j < NJ; ++j) {
+        o[j].x = (keep >> (4 * j)) & 1u ? o[j].x : 0.0f;
+        o[j].y = (keep >> (4 * j + 1)) & 1u ? o[j].y : 0.0f;
+        o[j].z = (keep >> (4 * j + 2)) & 1u ? o[j].z : 0.0f;
+        o[j].w = (keep >> (4 * j + 3)) & 1u ? o[j].w : 0.0f;
+      }
     }
   }
   float *crow = g.C + r * g.ldc + n0 + 4 * grp;
@@ -647,6 +637,407 @@ __global__ __launch_bounds__(kThreads) void k_gemm_reduce(GemmF32 g, int splits)
   float v = (g.scale ? *g.scale : 1.0f) * s + (g.bias ? g.bias[c] : 0.0f);
   if (g.beta) v += g.C[r * g.ldc + c];
   g.C[r * g.ldc + c] = v;
+}
+
+// ------------------------------------------------------------------------------------------
+// Forward maps on Eq. 2 codes.  One wavefront per 16-token strip, products transposed on int8 MFMA
+// (weights the A operand, from LDS; the strip's tokens the columns), so lane (c, g) = (lane & 15,
+// lane >> 4) ends with outputs 16 t + 4 g .. + 3 of token c for every output tile t: one 16-byte
+// access per tile in the natural row layout.  int32 sums are exact; the only rounding of a map is
+// fma(acc, t s, bias).
+//
+// k_train_block is the inference path's token block with the backward's inputs written on the way.  The
+// separate kernels it stands for (quantise O, output map, LayerNorm, first map, ReLU and quantise,
+// second map, LayerNorm) passed every activation through memory in fp32 and wrote the dequantised
+// codes as fp32: LDPC(256,128), 256 words, 440 us a layer; this one moves 3 KB a token.
+// ------------------------------------------------------------------------------------------
+constexpr int kTbWaves = 8;
+
+template <int D>
+constexpr size_t qkv_lds() { return (size_t)3 * D * D + (size_t)3 * D * 4; }
+template <int D>
+constexpr size_t block_lds() { return (size_t)9 * D * D + (size_t)12 * D * 4; }
+
+// `words` 16-byte words to LDS, four loads of a thread in flight at a time
+__device__ __forceinline__ void stage16(const void *src, void *dst, int words, int tid) {
+  constexpr int NT = kTbWaves * 64;
+  for (int u = tid; u < words; u += 4 * NT) {
+    uint4 r[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) r[k] = ((const uint4 *)src)[std::min(u + k * NT, words - 1)];
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+      if (u + k * NT < words) ((uint4 *)dst)[u + k * NT] = r[k];
+  }
+}
+__device__ __forceinline__ void stage_vec(const float *src, float *dst, int n, int tid) {
+  for (int u = tid; u < n; u += kTbWaves * 64) dst[u] = src[u];
+}
+
+template <int D>
+__global__ __launch_bounds__(kTbWaves * 64) void k_train_qkv(TrainQkv p) {
+  constexpr int S = D / 32, TO = D / 16;
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, c = lane & 15, g = lane >> 4;
+  uint64_t *fr = (uint64_t *)smem;               // [3][TO][S][64]
+  float *bl = (float *)(smem + (size_t)3 * D * D);
+#pragma unroll
+  for (int m = 0; m < 3; ++m) {
+    stage16(p.f[m], fr + (size_t)m * TO * S * 64, D * D / 16, tid);
+    stage_vec(p.b[m], bl + m * D, D, tid);
+  }
+  __syncthreads();
+  const float sq[3] = {*p.s[0], *p.s[1], *p.s[2]};
+  const int64_t nstrips = (p.rows + 15) / 16, stride = (int64_t)gridDim.x * kTbWaves;
+  for (int64_t strip = (int64_t)blockIdx.x * kTbWaves + wave; strip < nstrips; strip += stride) {
+    const int64_t tok = strip * 16 + c, tl = tok < p.rows ? tok : p.rows - 1;
+    long x[S];
+#pragma unroll
+    for (int s = 0; s < S; ++s) x[s] = *(const long *)(p.xq + tl * D + 32 * s + 8 * g);
+    const float t = p.tx[tl];
+    float *out = p.qkv + tok * 3 * D + 4 * g;
+#pragma unroll
+    for (int m = 0; m < 3; ++m) {
+      const float sc = t * sq[m];
+#pragma unroll
+      for (int o = 0; o < TO; ++o) {
+        const v4i acc = mfma_i8_steps<S>([&](int s) { return (long)fr[((m * TO + o) * S + s) * 64 + lane]; },
+                                         [&](int s) { return x[s]; }, v4i{0, 0, 0, 0});
+        const float4 b = *(const float4 *)(bl + m * D + 16 * o + 4 * g);
+        if (tok < p.rows)
+          *(float4 *)(out + m * D + 16 * o) =
+              make_float4(fmaf((float)acc[0], sc, b.x), fmaf((float)acc[1], sc, b.y), fmaf((float)acc[2], sc, b.z),
+                          fmaf((float)acc[3], sc, b.w));
+      }
+    }
+  }
+}
+
+// Eq. 2 codes of a token's row held as x[v] = feature 16 (v >> 2) + 4 g + (v & 3): step s's eight codes
+// of this lane (the next product's B operand) to xb, and to the natural row q of int8 codes.
+template <int S>
+__device__ __forceinline__ void store_codes(const float (&x)[8 * S], float inv, int g, bool ok, int8_t *q, long (&xb)[S]) {
+#pragma unroll
+  for (int s = 0; s < S; ++s) {
+    uint32_t b[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) b[k] = quant_bits(x[8 * s + k], inv);
+    xb[s] = tb_pack8(b);
+    if (ok) {
+      *(uint32_t *)(q + 32 * s + 4 * g) = (uint32_t)xb[s];
+      *(uint32_t *)(q + 32 * s + 16 + 4 * g) = (uint32_t)((uint64_t)xb[s] >> 32);
+    }
+  }
+}
+
+template <int D>
+__global__ __launch_bounds__(kTbWaves * 64) void k_train_block(TrainBlock p) {
+  constexpr int V = D / 4, S = D / 32, TO = D / 16, TH = D / 4, SH = D / 8, MW = D / 32;
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, c = lane & 15, g = lane >> 4;
+  uint64_t *f1 = (uint64_t *)smem, *f2 = f1 + (size_t)TH * S * 64, *fo = f2 + (size_t)TO * SH * 64;
+  float *lv = (float *)(smem + (size_t)9 * D * D);   // bo, g1, be1, b2, g2, be2, res_g, res_b, b1 [4 D]
+  stage16(p.f1, f1, D * D / 4, tid);
+  stage16(p.f2, f2, D * D / 4, tid);
+  stage16(p.fo, fo, D * D / 16, tid);
+  {
+    const float *src[8] = {p.bo, p.g1, p.be1, p.b2, p.g2, p.be2, p.res_g, p.res_b};
+#pragma unroll
+    for (int k = 0; k < 8; ++k)
+      if (src[k]) stage_vec(src[k], lv + k * D, D, tid);
+    stage_vec(p.b1, lv + 8 * D, 4 * D, tid);
+  }
+  __syncthreads();
+  const float so = *p.so, s1 = *p.s1, s2 = *p.s2;
+  // the lane's fragments and vectors from opaque byte offsets, so that the unrolled reads share one
+  // running address each
+  uint32_t of1 = (uint32_t)lane * 8u, of2 = (uint32_t)(TH * S * 64 + lane) * 8u, ov = (uint32_t)(9 * D * D) + 16u * (uint32_t)g;
+  asm volatile("" : "+v"(of1), "+v"(of2), "+v"(ov));
+  const uint64_t *f1l = (const uint64_t *)(smem + of1), *f2l = (const uint64_t *)(smem + of2);
+  const float *vl = (const float *)(smem + ov);       // vl[k D + 16 t + i]: vector k, feature 16 t + 4 g + i
+  const int64_t nstrips = (p.rows + 15) / 16, stride = (int64_t)gridDim.x * kTbWaves;
+  for (int64_t strip = (int64_t)blockIdx.x * kTbWaves + wave; strip < nstrips; strip += stride) {
+    const int64_t tok = strip * 16 + c;
+    const bool ok = tok < p.rows;
+    const int64_t tl = ok ? tok : p.rows - 1;          // padding columns: a copy, never stored
+    float x[V];                                        // the residual, then each LayerNorm's output
+    long bq[S];
+    float sc;
+    {
+      float ov8[8 * S], om = 0.0f;                     // the output map reads O's features 32 s + 8 g + e
+#pragma unroll
+      for (int s = 0; s < S; ++s)
+#pragma unroll
+        for (int k = 0; k < 8; k += 4) {
+          const float4 f = *(const float4 *)(p.o + tl * D + 32 * s + 8 * g + k);
+          ov8[8 * s + k] = f.x; ov8[8 * s + k + 1] = f.y; ov8[8 * s + k + 2] = f.z; ov8[8 * s + k + 3] = f.w;
+        }
+#pragma unroll
+      for (int t = 0; t < TO; ++t) {
+        const float4 f = *(const float4 *)(p.res + tl * D + 16 * t + 4 * g);
+        x[4 * t] = f.x; x[4 * t + 1] = f.y; x[4 * t + 2] = f.z; x[4 * t + 3] = f.w;
+      }
+#pragma unroll
+      for (int k = 0; k < 8 * S; ++k) om = fmaxf(om, fabsf(ov8[k]));
+      om = tb_token_max(om);
+      const float inv = inv127(om);
+#pragma unroll
+      for (int s = 0; s < S; ++s) {
+        uint32_t b[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) b[k] = quant_bits(ov8[8 * s + k], inv);
+        bq[s] = tb_pack8(b);
+        if (ok) *(long *)(p.oq + tok * D + 32 * s + 8 * g) = bq[s];
+      }
+      const float t = om / 127.0f;
+      if (ok && g == 0) p.to[tok] = t;
+      sc = t * so;
+    }
+    if (p.res_g) {
+#pragma unroll
+      for (int v = 0; v < V; ++v) x[v] = fmaf(x[v], vl[6 * D + 16 * (v >> 2) + (v & 3)], vl[7 * D + 16 * (v >> 2) + (v & 3)]);
+    }
+    // x := LN(x), its normalised row and 1 / sigma to xn, rho; returns max |x| over the token
+    auto norm = [&](int kg, int kb, float *xn, float *rho) {
+      const float mean = tb_token_sum<V>(x) / (float)D;
+      float q[V];
+#pragma unroll
+      for (int v = 0; v < V; ++v) {
+        x[v] = x[v] - mean;
+        q[v] = x[v] * x[v];
+      }
+      const float rh = 1.0f / sqrtf(tb_token_sum<V>(q) / (float)D + p.eps);
+      float am = 0.0f;
+#pragma unroll
+      for (int t = 0; t < TO; ++t) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) x[4 * t + i] *= rh;
+        if (ok) *(float4 *)(xn + tok * D + 16 * t + 4 * g) = make_float4(x[4 * t], x[4 * t + 1], x[4 * t + 2], x[4 * t + 3]);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          x[4 * t + i] = fmaf(x[4 * t + i], vl[kg * D + 16 * t + i], vl[kb * D + 16 * t + i]);
+          am = fmaxf(am, fabsf(x[4 * t + i]));
+        }
+      }
+      if (ok && g == 0) rho[tok] = rh;
+      return tb_token_max(am);
+    };
+    // ---- output map, residual, LN1, Eq. 2 ----
+#pragma unroll
+    for (int o = 0; o < TO; ++o) {
+      const v4i acc = mfma_i8_steps<S>([&](int s) { return (long)fo[(o * S + s) * 64 + lane]; }, [&](int s) { return bq[s]; },
+                                       v4i{0, 0, 0, 0});
+#pragma unroll
+      for (int i = 0; i < 4; ++i) x[4 * o + i] += fmaf((float)acc[i], sc, vl[16 * o + i]);
+    }
+    const float a1 = norm(1, 2, p.xn1, p.rho1);
+    long xb[S];
+    store_codes<S>(x, inv127(a1), g, ok, p.x1q + tok * D, xb);
+    const float t1 = a1 / 127.0f, sc1 = t1 * s1;
+    if (ok && g == 0) p.t1[tok] = t1;
+    // ---- first feed-forward map: the hidden row in registers, its ReLU mask and maximum ----
+    float hid[TH][4], am = 0.0f;
+#pragma unroll
+    for (int w = 0; w < MW; ++w) {
+      uint32_t keep = 0;
+#pragma unroll
+      for (int o8 = 0; o8 < 8; ++o8) {
+        const int o = 8 * w + o8;
+        const v4i acc = mfma_i8_steps<S>([&](int s) { return (long)f1l[(o * S + s) * 64]; }, [&](int s) { return xb[s]; },
+                                         v4i{0, 0, 0, 0});
+        const float4 b = *(const float4 *)(vl + 8 * D + 16 * o);
+        const float bb[4] = {b.x, b.y, b.z, b.w};
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          hid[o][i] = fmaf((float)acc[i], sc1, bb[i]);
+          keep |= hid[o][i] > 0.0f ? 1u << (4 * o8 + i) : 0u;
+          am = fmaxf(am, hid[o][i]);
+        }
+      }
+      if (ok) p.mask[(tok * 4 + g) * MW + w] = keep;
+    }
+    am = tb_token_max(am + 0.0f);   // +0: a -0 maximum would not order like its bits
+    const float invh = inv127(am), tg = am / 127.0f;
+    if (ok && g == 0) p.tg[tok] = tg;
+    // ---- ReLU and Eq. 2 on the codes, second map ----
+    v4i acc2[TO];
+#pragma unroll
+    for (int o = 0; o < TO; ++o) acc2[o] = v4i{0, 0, 0, 0};
+    static_assert(SH % 2 == 0, "k-steps taken in pairs");
+#pragma unroll
+    for (int st = 0; st < SH; st += 2) {
+      long gb[2];
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        uint32_t w[2];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const int o = 2 * (st + j) + h;
+          w[h] = pack4_relu(quant_bits(hid[o][0], invh), quant_bits(hid[o][1], invh), quant_bits(hid[o][2], invh),
+                            quant_bits(hid[o][3], invh));
+          if (ok) *(uint32_t *)(p.gq + tok * 4 * D + 16 * o + 4 * g) = w[h];
+        }
+        gb[j] = (long)(((uint64_t)w[1] << 32) | w[0]);
+      }
+#pragma unroll
+      for (int o = 0; o < TO; ++o)
+        acc2[o] = mfma_i8_16x16x64((long)f2l[(o * SH + st) * 64], (long)f2l[(o * SH + st + 1) * 64], gb[0], gb[1], acc2[o]);
+    }
+    // ---- residual, LN2, Eq. 2 of the next layer's input ----
+    const float sc2 = tg * s2;
+#pragma unroll
+    for (int o = 0; o < TO; ++o)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) x[4 * o + i] += fmaf((float)acc2[o][i], sc2, vl[3 * D + 16 * o + i]);
+    const float ax = norm(4, 5, p.xn2, p.rho2);
+    if (p.x) {
+      if (ok)
+#pragma unroll
+        for (int t = 0; t < TO; ++t)
+          *(float4 *)(p.x + tok * D + 16 * t + 4 * g) = make_float4(x[4 * t], x[4 * t + 1], x[4 * t + 2], x[4 * t + 3]);
+    } else {
+      long nb[S];
+      store_codes<S>(x, inv127(ax), g, ok, p.xq + tok * D, nb);
+      if (ok && g == 0) p.tx[tok] = ax / 127.0f;
+    }
+    __builtin_amdgcn_sched_barrier(0);   // strips do not overlap (their registers would not fit)
+  }
+}
+
+// ------------------------------------------------------------------------------------------
+// Weight gradients G = Xh^T dY of every map of a layer, Xh = q t per row (codes and scales): the codes
+// are exact in bf16 and fp32(t dY) splits exactly into three bf16 parts, so three bf16 MFMAs form fp32
+// sums of exact products (as k_gemm_tern), at 16 times the fp32 matrix rate each.  A block takes a
+// D x D tile of one map's gradient over a range of rows: per step of 4096 / D rows a thread reads two
+// columns of eight rows of either operand and writes them to LDS as MFMA fragments (the contraction
+// runs over rows, so a lane needs eight rows of one column), the next step's reads in flight while the
+// current one is multiplied.  The bias gradients are the column sums of the dY that pass by.  All four
+// products of a layer go out as one launch, their partial sums reduced by one more in a fixed order
+// (fp32 MFMAs on fp32 Xh, with a launch, a reduction and a column-sum pass per map: LDPC(256,128),
+// 256 words, 480 us a layer; BCH(31,16), 128 words, 160 us).
+// ------------------------------------------------------------------------------------------
+template <int D>
+__global__ __launch_bounds__(kThreads, 2) void k_train_dw(TrainDwJobs J) {
+  constexpr int CP = D / 2, RG = kThreads / CP, RS = 8 * RG, TM = D / 32;
+  __shared__ uint4 As[RG][D], Bs[3][RG][D];   // eight rows of a column as bf16
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, fr = lane >> 4, fc = lane & 15;
+  const int cp = tid % CP, rg = tid / CP;
+  int ji = 0;
+  while (ji + 1 < J.n && (int)blockIdx.x >= J.tile0[ji + 1]) ++ji;
+  const TrainDwJob &j = J.j[ji];
+  const int tile = (int)blockIdx.x - J.tile0[ji], kts = j.K / D, nt = tile / kts, kt = tile - nt * kts;
+  const int64_t r0 = (int64_t)blockIdx.y * J.chunk, r1 = std::min<int64_t>(J.rows, r0 + J.chunk);
+  const int8_t *qp = j.q + kt * D + 2 * cp;
+  const float *yp = j.dy + nt * D + 2 * cp;
+  const float *tp = j.t;
+  const int64_t K = j.K, ldy = j.ldy;
+  uint32_t q[8];
+  float2 y[8];
+  float t[8];
+  auto load = [&](int64_t r) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const int64_t row = r + 8 * rg + e;
+      const bool ok = row < r1;
+      q[e] = ok ? *(const uint16_t *)(qp + row * K) : 0u;
+      y[e] = ok ? *(const float2 *)(yp + row * ldy) : make_float2(0.0f, 0.0f);
+      t[e] = ok ? tp[row] : 0.0f;
+    }
+  };
+  f32x4 acc[TM][TM];
+#pragma unroll
+  for (int a = 0; a < TM; ++a)
+#pragma unroll
+    for (int b = 0; b < TM; ++b) acc[a][b] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+  const int wm = (wave >> 1) * (D / 2), wn = (wave & 1) * (D / 2);
+  float cs[2] = {0.0f, 0.0f};
+  load(r0);
+  for (int64_t r = r0; r < r1; r += RS) {
+#pragma unroll
+    for (int f = 0; f < 2; ++f) {
+      float a[8], v[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        a[e] = (float)(int8_t)(q[e] >> (8 * f));
+        const float yv = f ? y[e].y : y[e].x;
+        cs[f] += yv;
+        v[e] = yv * t[e];
+      }
+      As[rg][2 * cp + f] = __builtin_bit_cast(uint4, bf16_hi8(a));
+      bf16x8 ph, pm, pl;
+      split_bf16x3(make_float4(v[0], v[1], v[2], v[3]), make_float4(v[4], v[5], v[6], v[7]), ph, pm, pl);
+      Bs[0][rg][2 * cp + f] = __builtin_bit_cast(uint4, ph);
+      Bs[1][rg][2 * cp + f] = __builtin_bit_cast(uint4, pm);
+      Bs[2][rg][2 * cp + f] = __builtin_bit_cast(uint4, pl);
+    }
+    __syncthreads();
+    if (r + RS < r1) load(r + RS);
+#pragma unroll
+    for (int ks = 0; ks < RS / 32; ++ks) {
+      bf16x8 af[TM];
+#pragma unroll
+      for (int a = 0; a < TM; ++a) af[a] = __builtin_bit_cast(bf16x8, As[4 * ks + fr][wm + 16 * a + fc]);
+#pragma unroll
+      for (int b = 0; b < TM; ++b) {
+#pragma unroll
+        for (int pt = 2; pt >= 0; --pt) {   // smallest part first
+          const bf16x8 bf = __builtin_bit_cast(bf16x8, Bs[pt][4 * ks + fr][wn + 16 * b + fc]);
+#pragma unroll
+          for (int a = 0; a < TM; ++a) acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[a], bf, acc[a][b], 0, 0, 0);
+        }
+      }
+    }
+    __syncthreads();
+  }
+  const int64_t slot = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
+  float *out = J.part + slot * D * D;
+#pragma unroll
+  for (int a = 0; a < TM; ++a)
+#pragma unroll
+    for (int b = 0; b < TM; ++b)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) out[(wm + 16 * a + 4 * fr + v) * D + wn + 16 * b + fc] = acc[a][b][v];
+  if (kt == 0) {
+    float (*red)[D] = (float (*)[D])As;
+    red[rg][2 * cp] = cs[0];
+    red[rg][2 * cp + 1] = cs[1];
+    __syncthreads();
+    if (tid < D) {
+      float s = 0.0f;
+#pragma unroll
+      for (int k = 0; k < RG; ++k) s += red[k][tid];
+      J.cpart[slot * D + tid] = s;
+    }
+  }
+}
+
+// The partial sums of k_train_dw added over the row ranges in order: per tile D D / 256 blocks of its
+// elements, then one of its column sums.
+template <int D>
+__global__ __launch_bounds__(kThreads) void k_train_dw_reduce(TrainDwJobs J) {
+  constexpr int EB = D * D / kThreads;
+  const int tile = (int)blockIdx.x / (EB + 1), eb = (int)blockIdx.x - tile * (EB + 1), tid = threadIdx.x;
+  int ji = 0;
+  while (ji + 1 < J.n && tile >= J.tile0[ji + 1]) ++ji;
+  const TrainDwJob &j = J.j[ji];
+  const int ti = tile - J.tile0[ji], kts = j.K / D, nt = ti / kts, kt = ti - nt * kts, tiles = J.tile0[J.n];
+  const bool col = eb == EB;
+  if (col && (kt != 0 || tid >= D)) return;
+  const int e = col ? tid : eb * kThreads + tid;
+  const float *src = col ? J.cpart + (int64_t)tile * D + e : J.part + (int64_t)tile * D * D + e;
+  const int64_t step = (int64_t)tiles * D * (col ? 1 : D);
+  float s[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+  int z = 0;
+  for (; z + 3 < J.splits; z += 4)
+#pragma unroll
+    for (int u = 0; u < 4; ++u) s[u] += src[(z + u) * step];
+  for (; z < J.splits; ++z) s[0] += src[z * step];
+  const float v = (s[0] + s[1]) + (s[2] + s[3]);
+  const int n = nt * D + (col ? e : e % D), sg = n / j.seg, nc = n - sg * j.seg;
+  float *const gw = sg == 0 ? j.gw[0] : (sg == 1 ? j.gw[1] : j.gw[2]);
+  float *const gb = sg == 0 ? j.gb[0] : (sg == 1 ? j.gb[1] : j.gb[2]);
+  if (col) gb[nc] = v;
+  else gw[(int64_t)(kt * D + e / D) * j.seg + nc] = v;
 }
 
 // ------------------------------------------------------------------------------------------
@@ -795,56 +1186,9 @@ __global__ __launch_bounds__(kThreads) void k_attn_bwd_kv(AttnT p) {
 }
 
 // ------------------------------------------------------------------------------------------
-// LayerNorm of the Post-LN block (Section 6), one wavefront per row: forward of R = a + b, keeping
-// the normalised row xn and 1 / sqrt(var + eps); backward dR = rho (dxn - mean dxn - xn mean(dxn
-// xn)) with dxn = dy g.
+// LayerNorm backward (Post-LN block, Section 6), one wavefront per row: dR = rho (dxn - mean dxn - xn
+// mean(dxn xn)) with dxn = dy g, xn the normalised row and rho its 1 / sqrt(var + eps).
 // ------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(kThreads) void k_ln_fwd(const float *a, const float *b, int64_t rows, int d,
-                                                     const float *g, const float *beta, float eps, float *out,
-                                                     float *xn, float *rho, float *xh) {
-  const int64_t r = (int64_t)blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6);
-  const int lane = threadIdx.x & 63;
-  if (r >= rows) return;
-  float v[2], s = 0.0f;
-#pragma unroll
-  for (int u = 0; u < 2; ++u) {
-    const int c = lane + 64 * u;
-    v[u] = c < d ? a[r * d + c] + b[r * d + c] : 0.0f;
-    s += v[u];
-  }
-  const float mean = wave_sum(s) / (float)d;
-  float q = 0.0f;
-#pragma unroll
-  for (int u = 0; u < 2; ++u) {
-    const int c = lane + 64 * u;
-    if (c < d) q = fmaf(v[u] - mean, v[u] - mean, q);
-  }
-  const float rh = 1.0f / sqrtf(wave_sum(q) / (float)d + eps);
-#pragma unroll
-  for (int u = 0; u < 2; ++u) {
-    const int c = lane + 64 * u;
-    if (c >= d) continue;
-    const float x = (v[u] - mean) * rh;
-    xn[r * d + c] = x;
-    v[u] = fmaf(x, g[c], beta[c]);
-    out[r * d + c] = v[u];
-  }
-  if (lane == 0) rho[r] = rh;
-  if (!xh) return;
-  // the output row's Eq. 2 codes and their values, as k_quant_dequant forms them from out
-  float am = 0.0f;
-#pragma unroll
-  for (int u = 0; u < 2; ++u)
-    if (lane + 64 * u < d) am = fmaxf(am, fabsf(v[u]));
-  am = wave_max(am);
-  const float inv = inv127(am);
-#pragma unroll
-  for (int u = 0; u < 2; ++u) {
-    const int c = lane + 64 * u;
-    if (c < d) xh[r * d + c] = am == 0.0f ? 0.0f : (float)quant_code(v[u], inv) * am / 127.0f;
-  }
-}
-
 __global__ __launch_bounds__(kThreads) void k_ln_bwd(const float *dy, const float *g, const float *xn,
                                                      const float *rho, int64_t rows, int d, float *dR) {
   const int64_t r = (int64_t)blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6);
@@ -935,25 +1279,6 @@ __global__ __launch_bounds__(kThreads) void k_colsum(const float *A, int64_t lda
 // ------------------------------------------------------------------------------------------
 // Small elementwise steps.
 // ------------------------------------------------------------------------------------------
-// ReLU backward (the Eq. 2 code of the hidden row passes the gradient straight through)
-__global__ __launch_bounds__(kThreads) void k_relu_bwd(float *dg, const float *f, int64_t count) {
-  const int64_t e = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-  if (e < count && !(f[e] > 0.0f)) dg[e] = 0.0f;
-}
-// the same over 16-byte groups, every group written whole (zeroing only the dropped elements left
-// partly written lines behind)
-__global__ __launch_bounds__(kThreads) void k_relu_bwd4(float4 *dg, const float4 *f, int64_t count4) {
-  const int64_t e = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-  if (e >= count4) return;
-  const float4 fv = f[e];
-  float4 g = dg[e];
-  g.x = fv.x > 0.0f ? g.x : 0.0f;
-  g.y = fv.y > 0.0f ? g.y : 0.0f;
-  g.z = fv.z > 0.0f ? g.z : 0.0f;
-  g.w = fv.w > 0.0f ? g.w : 0.0f;
-  dg[e] = g;
-}
-
 // z = X w1 + b1 per row (Section 3 head, W_{d->1}); one wavefront per row
 __global__ __launch_bounds__(kThreads) void k_rowdot(const float *x, int64_t rows, int d, const float *w1,
                                                      const float *b1, float *z) {
@@ -1084,17 +1409,12 @@ hipError_t train_delta_grad(const TrainDeltaJobs &jobs, float eps, hipStream_t s
 }
 
 hipError_t train_embed(const float *y, int64_t rows, int n, int L, int d, const int32_t *chk_ptr,
-                       const int32_t *chk_idx, const float *E, const float *P, float *x, float *t, hipStream_t s) {
+                       const int32_t *chk_idx, const float *E, const float *P, float *x, float *t, int8_t *xq, float *tx,
+                       hipStream_t s) {
   if (rows <= 0) return hipSuccess;
+  if (d > 128) return hipErrorInvalidValue;
   hipLaunchKernelGGL(train::k_embed, dim3(blocks_for(rows, 4)), dim3(train::kThreads), 0, s, y, rows, n, L, d, chk_ptr,
-                     chk_idx, E, P, x, t);
-  return hipGetLastError();
-}
-
-hipError_t train_quant(const float *x, int64_t rows, int K, bool relu, float *xh, hipStream_t s) {
-  if (rows <= 0) return hipSuccess;
-  if (relu) hipLaunchKernelGGL(train::k_quant_dequant<true>, dim3(blocks_for(rows, 4)), dim3(train::kThreads), 0, s, x, rows, K, xh);
-  else hipLaunchKernelGGL(train::k_quant_dequant<false>, dim3(blocks_for(rows, 4)), dim3(train::kThreads), 0, s, x, rows, K, xh);
+                     chk_idx, E, P, x, t, xq, tx);
   return hipGetLastError();
 }
 
@@ -1148,76 +1468,135 @@ hipError_t train_gemm(bool ta, bool tb, const float *A, int64_t lda, const float
   return hipGetLastError();
 }
 
-bool train_tern_shape_ok(int64_t N, int64_t K) { return K % 32 == 0 && N % 64 == 0; }
-
-bool train_tern_operands_ok(const float *A, int64_t lda, const float *C, int64_t ldc, const float *bias, int64_t N,
-                            int64_t K) {
-  // 16-byte rows of A and C, 16-byte groups of the bias
-  const auto al16 = [](const float *q) { return ((uintptr_t)q & 15u) == 0; };
-  return train_tern_shape_ok(N, K) && lda % 4 == 0 && ldc % 4 == 0 && al16(A) && al16(C) && (!bias || al16(bias));
-}
-
 hipError_t train_pack_tern(const TernPackJobs &jobs, hipStream_t s) {
   if (jobs.n <= 0) return hipSuccess;
   int64_t lanes = 0;
   for (int i = 0; i < jobs.n; ++i) {
-    const TernPackJob &J = jobs.j[i];
-    if (!train_tern_shape_ok(J.trans ? J.R : J.C, J.trans ? J.C : J.R)) return hipErrorInvalidValue;
-    lanes = std::max<int64_t>(lanes, (int64_t)J.R * J.C / 8);   // one lane per 8 entries
+    if (jobs.j[i].R % 32 || jobs.j[i].C % 32) return hipErrorInvalidValue;
+    lanes = std::max<int64_t>(lanes, (int64_t)jobs.j[i].R * jobs.j[i].C / 8);   // one lane per 8 entries
   }
   hipLaunchKernelGGL(train::k_pack_tern, dim3(blocks_for(lanes, train::kThreads), (unsigned)jobs.n), dim3(train::kThreads), 0,
                      s, jobs);
   return hipGetLastError();
 }
 
-namespace {
-hipError_t gemm_tern_go(const train::GemmTern &g, hipStream_t s) {
+hipError_t train_gemm_tern(const float *A, int64_t lda, const void *const *frag, int nseg, int64_t kseg,
+                           const float *const *scale, const float *D, const uint32_t *mask, float *C, int64_t ldc,
+                           int64_t M, int64_t N, hipStream_t s) {
+  if (M <= 0 || N <= 0) return hipSuccess;
+  const auto al16 = [](const void *q) { return ((uintptr_t)q & 15u) == 0; };   // 16-byte rows of A, C, D
+  if (nseg < 1 || nseg > 3 || kseg <= 0 || kseg % 32 || N % 32 || lda % 4 || ldc % 4 || !al16(A) || !al16(C) || !al16(D) ||
+      (mask && N % 128))
+    return hipErrorInvalidValue;
+  train::GemmTern g{A, {}, C, D, M, N, kseg * nseg, lda, ldc, {}, mask, (int)(kseg / 32)};
+  for (int k = 0; k < nseg; ++k) {
+    g.B[k] = (const uint4 *)frag[k];
+    g.scale[k] = scale[k];
+  }
   constexpr int S = 3;   // operands two k-steps ahead
   const unsigned gy = (unsigned)((g.M + 63) / 64);
-  // a block's 16 NJ columns never straddle two column segments: seg_n is a multiple of 64 (and of
-  // 128 for NJ = 8)
-  if (g.seg_n % 128 == 0)
-    hipLaunchKernelGGL((train::k_gemm_tern<8, S>), dim3((unsigned)(g.N / 128), gy), dim3(train::kThreads), 0, s, g);
+  if (N % 128 == 0)
+    hipLaunchKernelGGL((train::k_gemm_tern<8, S>), dim3((unsigned)(N / 128), gy), dim3(train::kThreads), 0, s, g);
+  else if (N % 64 == 0)
+    hipLaunchKernelGGL((train::k_gemm_tern<4, S>), dim3((unsigned)(N / 64), gy), dim3(train::kThreads), 0, s, g);
   else
-    hipLaunchKernelGGL((train::k_gemm_tern<4, S>), dim3((unsigned)(g.N / 64), gy), dim3(train::kThreads), 0, s, g);
+    hipLaunchKernelGGL((train::k_gemm_tern<2, S>), dim3((unsigned)(N / 32), gy), dim3(train::kThreads), 0, s, g);
+  return hipGetLastError();
+}
+
+namespace {
+template <int D>
+hipError_t qkv_go(const TrainQkv &a, int cu_count, size_t lds_max, hipStream_t s) {
+  constexpr size_t lds = train::qkv_lds<D>();
+  const int64_t groups = ((a.rows + 15) / 16 + train::kTbWaves - 1) / train::kTbWaves;
+  const int64_t per_cu = std::max<int64_t>(1, std::min<int64_t>(2, (int64_t)(lds_max / lds)));
+  hipLaunchKernelGGL(train::k_train_qkv<D>, dim3((unsigned)std::min<int64_t>(groups, cu_count * per_cu)),
+                     dim3(train::kTbWaves * 64), lds, s, a);
+  return hipGetLastError();
+}
+template <int D>
+hipError_t block_go(const TrainBlock &a, int cu_count, size_t lds_max, hipStream_t s) {
+  constexpr size_t lds = train::block_lds<D>();
+  const int64_t groups = ((a.rows + 15) / 16 + train::kTbWaves - 1) / train::kTbWaves;
+  const int64_t per_cu = std::max<int64_t>(1, std::min<int64_t>(2, (int64_t)(lds_max / lds)));
+  hipLaunchKernelGGL(train::k_train_block<D>, dim3((unsigned)std::min<int64_t>(groups, cu_count * per_cu)),
+                     dim3(train::kTbWaves * 64), lds, s, a);
   return hipGetLastError();
 }
 }  // namespace
 
-hipError_t train_gemm_tern_seg(const float *A, int64_t lda, const void *const *frag, float *C, int64_t ldc, int64_t M,
-                               int64_t seg_n, int nseg, int64_t K, const float *const *scale, const float *const *bias,
-                               bool accumulate, hipStream_t s) {
-  if (M <= 0 || seg_n <= 0) return hipSuccess;
-  if (nseg < 1 || nseg > 3) return hipErrorInvalidValue;
-  for (int k = 0; k < nseg; ++k)
-    if (!train_tern_operands_ok(A, lda, C + k * seg_n, ldc, bias[k], seg_n, K)) return hipErrorInvalidValue;
-  train::GemmTern g{A, {}, C, accumulate ? C : nullptr, M, seg_n * nseg, K, lda, ldc, {}, {}, seg_n, (int)(K / 32)};
-  for (int k = 0; k < nseg; ++k) {
-    g.B[k] = (const uint4 *)frag[k];
-    g.scale[k] = scale[k];
-    g.bias[k] = bias[k];
+hipError_t train_set_attributes(size_t lds_max) {
+  const void *fns[] = {(const void *)train::k_train_qkv<32>,   (const void *)train::k_train_qkv<64>,
+                       (const void *)train::k_train_qkv<128>,  (const void *)train::k_train_block<32>,
+                       (const void *)train::k_train_block<64>, (const void *)train::k_train_block<128>};
+  if (lds_max < train::block_lds<128>()) return hipErrorInvalidValue;
+  for (const void *f : fns) {
+    const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_max);
+    if (e != hipSuccess) return e;
   }
-  return gemm_tern_go(g, s);
+  return hipSuccess;
 }
 
-hipError_t train_gemm_tern_ksum(const float *A, int64_t lda, const void *const *frag, int nseg, int64_t kseg,
-                                const float *const *scale, const float *D, float *C, int64_t ldc, int64_t M, int64_t N,
-                                hipStream_t s) {
-  if (M <= 0 || N <= 0) return hipSuccess;
-  if (nseg < 1 || nseg > 3 || kseg <= 0 || kseg % 32 != 0) return hipErrorInvalidValue;
-  if (!train_tern_operands_ok(A, lda, C, ldc, nullptr, N, kseg * nseg) || (D && ((uintptr_t)D & 15u) != 0))
-    return hipErrorInvalidValue;
-  train::GemmTern g{A, {}, C, D, M, N, kseg * nseg, lda, ldc, {}, {}, N, (int)(kseg / 32)};
-  for (int k = 0; k < nseg; ++k) {
-    g.B[k] = (const uint4 *)frag[k];
-    g.scale[k] = scale[k];
+hipError_t train_qkv(int d, const TrainQkv &a, int cu_count, size_t lds_max, hipStream_t s) {
+  if (a.rows <= 0) return hipSuccess;
+  switch (d) {
+    case 32: return qkv_go<32>(a, cu_count, lds_max, s);
+    case 64: return qkv_go<64>(a, cu_count, lds_max, s);
+    case 128: return qkv_go<128>(a, cu_count, lds_max, s);
   }
-  return gemm_tern_go(g, s);
+  return hipErrorInvalidValue;
 }
 
-hipError_t train_gemm_tern(const float *A, int64_t lda, const void *frag, float *C, int64_t ldc, int64_t M, int64_t N,
-                           int64_t K, const float *scale, const float *bias, bool accumulate, hipStream_t s) {
-  return train_gemm_tern_seg(A, lda, &frag, C, ldc, M, N, 1, K, &scale, &bias, accumulate, s);
+hipError_t train_block(int d, const TrainBlock &a, int cu_count, size_t lds_max, hipStream_t s) {
+  if (a.rows <= 0) return hipSuccess;
+  switch (d) {
+    case 32: return block_go<32>(a, cu_count, lds_max, s);
+    case 64: return block_go<64>(a, cu_count, lds_max, s);
+    case 128: return block_go<128>(a, cu_count, lds_max, s);
+  }
+  return hipErrorInvalidValue;
+}
+
+int train_dw_splits(int64_t rows, int tiles, int cu_count) {
+  // about two blocks per compute unit over all tiles, at least 128 rows each
+  const int64_t want = (2 * (int64_t)cu_count + tiles - 1) / tiles;
+  return (int)std::max<int64_t>(1, std::min<int64_t>(want, (rows + 127) / 128));
+}
+
+hipError_t train_weight_grads(int d, TrainDwJobs &J, int cu_count, float *part, int64_t part_floats, hipStream_t s) {
+  if (J.rows <= 0 || J.n < 1 || J.n > kTrainDwJobs) return hipErrorInvalidValue;
+  J.tile0[0] = 0;
+  for (int k = 0; k < J.n; ++k) {
+    const TrainDwJob &j = J.j[k];
+    if (j.K % d || j.N % d || j.seg % d || j.ldy % 2 || ((uintptr_t)j.dy & 7u) || ((uintptr_t)j.q & 1u)) return hipErrorInvalidValue;
+    J.tile0[k + 1] = J.tile0[k] + (j.K / d) * (j.N / d);
+  }
+  const int tiles = J.tile0[J.n];
+  const int rs = 4096 / d;   // rows of one step of the kernel
+  int64_t splits = train_dw_splits(J.rows, tiles, cu_count);
+  J.chunk = ((J.rows + splits - 1) / splits + rs - 1) / rs * rs;
+  splits = (J.rows + J.chunk - 1) / J.chunk;
+  J.splits = (int)splits;
+  J.part = part;
+  J.cpart = part + splits * tiles * d * d;
+  if (splits * tiles * (int64_t)d * (d + 1) > part_floats) return hipErrorInvalidValue;
+  const dim3 grid((unsigned)tiles, (unsigned)splits), rgrid((unsigned)(tiles * (d * d / train::kThreads + 1)));
+  switch (d) {
+    case 32:
+      hipLaunchKernelGGL(train::k_train_dw<32>, grid, dim3(train::kThreads), 0, s, J);
+      hipLaunchKernelGGL(train::k_train_dw_reduce<32>, rgrid, dim3(train::kThreads), 0, s, J);
+      break;
+    case 64:
+      hipLaunchKernelGGL(train::k_train_dw<64>, grid, dim3(train::kThreads), 0, s, J);
+      hipLaunchKernelGGL(train::k_train_dw_reduce<64>, rgrid, dim3(train::kThreads), 0, s, J);
+      break;
+    case 128:
+      hipLaunchKernelGGL(train::k_train_dw<128>, grid, dim3(train::kThreads), 0, s, J);
+      hipLaunchKernelGGL(train::k_train_dw_reduce<128>, rgrid, dim3(train::kThreads), 0, s, J);
+      break;
+    default: return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
 }
 
 hipError_t train_attention(int which, int dh, const TrainAttn &a, hipStream_t s) {
@@ -1235,15 +1614,6 @@ hipError_t train_attention(int which, int dh, const TrainAttn &a, hipStream_t s)
     default: return hipErrorInvalidValue;
   }
 #undef AECCT_TRAIN_ATTN
-  return hipGetLastError();
-}
-
-hipError_t train_ln_fwd(const float *a, const float *b, int64_t rows, int d, const float *g, const float *beta, float eps,
-                        float *out, float *xn, float *rho, float *xh, hipStream_t s) {
-  if (rows <= 0) return hipSuccess;
-  if (d > 128) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(train::k_ln_fwd, dim3(blocks_for(rows, 4)), dim3(train::kThreads), 0, s, a, b, rows, d, g, beta, eps,
-                     out, xn, rho, xh);
   return hipGetLastError();
 }
 
@@ -1302,24 +1672,6 @@ hipError_t train_colsum_dual(const float *A, int64_t lda, const float *Bm, int64
   if (!Bm) return hipErrorInvalidValue;
   return colsum_run(A, lda, Bm, nullptr, rows, C, true, train::ColOut{{out_ab, out_a, nullptr}, std::max(C, 1), 0},
                     false, part, part_floats, s);
-}
-
-hipError_t train_colsum_split(const float *A, int64_t lda, int64_t rows, int seg, int nseg, float *const *outs,
-                              float *part, int64_t part_floats, hipStream_t s) {
-  if (nseg < 1 || nseg > 3 || seg <= 0) return hipErrorInvalidValue;
-  train::ColOut fin{{outs[0], nseg > 1 ? outs[1] : nullptr, nseg > 2 ? outs[2] : nullptr}, seg, 0};
-  return colsum_run(A, lda, nullptr, nullptr, rows, seg * nseg, false, fin, false, part, part_floats, s);
-}
-
-hipError_t train_relu_bwd(float *dg, const float *f, int64_t count, hipStream_t s) {
-  if (count <= 0) return hipSuccess;
-  if (count % 4 == 0 && ((uintptr_t)dg & 15u) == 0 && ((uintptr_t)f & 15u) == 0)
-    hipLaunchKernelGGL(train::k_relu_bwd4, dim3(blocks_for(count / 4, train::kThreads)), dim3(train::kThreads), 0, s,
-                       (float4 *)dg, (const float4 *)f, count / 4);
-  else
-    hipLaunchKernelGGL(train::k_relu_bwd, dim3(blocks_for(count, train::kThreads)), dim3(train::kThreads), 0, s, dg, f,
-                       count);
-  return hipGetLastError();
 }
 
 hipError_t train_rowdot(const float *x, int64_t rows, int d, const float *w1, const float *b1, float *z, hipStream_t s) {

@@ -16,6 +16,7 @@ struct aecct_trainer {
   int n, m, L, d, N, heads, hf, dff, dh;
   float ln_eps, aap_eps;
   int device, cu_count;
+  size_t lds_max;
   void *blk;
   const int32_t *chk_ptr, *chk_idx, *m1_ptr, *m1_idx, *m2_ptr, *m2_idx;
 };
@@ -27,9 +28,11 @@ size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
 // Workspace regions (float offsets) for `batch` words.
 struct TrainWs {
-  struct Layer { size_t xh, qkv, lse, o, oh, xn1, rho1, x1h, f, gh, xn2, rho2; };
+  // per layer, for the backward: codes (int8) and scales alpha / 127 of every map's input, Q | K | V, the
+  // attention's output and log-sum-exp, both normalised rows with their 1 / sigma, the ReLU mask
+  struct Layer { size_t xq, tx, qkv, lse, o, oq, to, xn1, rho1, x1q, t1, mask, gq, tg, xn2, rho2; };
   std::vector<Layer> layer;
-  size_t t, x, x1, y, z, fo, df, dz, tw, tb16, gam, sc, lpart, dx, dr, dx1, dg, dO, dqkv, dv, part;
+  size_t t, x, z, fo, df, dz, tw, tpk, gam, sc, lpart, dx, dr2, dr1, dx1, dg, dO, dqkv, dv, part;
   size_t part_floats, total_bytes;
 };
 
@@ -37,47 +40,56 @@ size_t weight_floats(const aecct_trainer &T) {
   return (size_t)T.N * (4 * (size_t)T.d * T.d + 2 * (size_t)T.d * T.dff);
 }
 
+// d x d tiles of a layer's weight gradients: d_ff / d = 4 of each feed-forward map, the output map, three of Q | K | V
+constexpr int kDwTiles = 12;
+
 TrainWs train_ws(const aecct_trainer &T, int64_t batch) {
   const size_t R = (size_t)batch * T.L, d = T.d, dff = T.dff, h = T.heads;
   TrainWs w{};
   size_t off = 0;   // bytes
   auto take = [&](size_t floats) { size_t o = off; off = align_up(off + 4 * floats); return o / 4; };
+  auto bytes = [&](size_t n) { return take((n + 3) / 4); };
   w.layer.resize(T.N);
   for (auto &q : w.layer) {
-    q.xh = take(R * d);
+    q.xq = bytes(R * d);
+    q.tx = take(R);
     q.qkv = take(R * 3 * d);
     q.lse = take(R * h);
     q.o = take(R * d);
-    q.oh = take(R * d);
+    q.oq = bytes(R * d);
+    q.to = take(R);
     q.xn1 = take(R * d);
     q.rho1 = take(R);
-    q.x1h = take(R * d);
-    q.f = take(R * dff);
-    q.gh = take(R * dff);
+    q.x1q = bytes(R * d);
+    q.t1 = take(R);
+    q.mask = bytes(R * dff / 8);
+    q.gq = bytes(R * dff);
+    q.tg = take(R);
     q.xn2 = take(R * d);
     q.rho2 = take(R);
   }
   w.t = take(R);
   w.x = take(R * d);
-  w.x1 = take(R * d);
-  w.y = take(R * d);
   w.z = take(R);
   w.fo = take((size_t)batch * T.n);
   w.df = take((size_t)batch * T.n);
   w.dz = take(R);
   w.tw = take(weight_floats(T));
-  w.tb16 = take(weight_floats(T));   // every ternary matrix as bf16 B fragments, T and T^T
+  w.tpk = take(weight_floats(T));   // every ternary matrix as int8 fragments, then as bf16 ones of T^T
   w.gam = take((size_t)T.N * 6);
   w.sc = take((size_t)T.N * 6);
   w.lpart = take(((size_t)batch * T.n + 255) / 256 + 1);
   w.dx = take(R * d);
-  w.dr = take(R * d);
+  w.dr2 = take(R * d);
+  w.dr1 = take(R * d);
   w.dx1 = take(R * d);
   w.dg = take(R * dff);
   w.dO = take(R * d);
   w.dqkv = take(R * 3 * d);
   w.dv = take(R * h);
   w.part_floats = std::max<size_t>(size_t(1) << 22, 4 * std::max<size_t>((size_t)T.L * T.n, d * dff));
+  w.part_floats = std::max<size_t>(
+      w.part_floats, (size_t)aecct::train_dw_splits((int64_t)R, kDwTiles, T.cu_count) * kDwTiles * d * (d + 1));
   w.part = take(w.part_floats);
   w.total_bytes = off;
   return w;
@@ -136,9 +148,11 @@ aecct_status aecct_train_create(const uint8_t *H, int32_t m, int32_t n, int32_t 
   for (int k = 0; k < 6; ++k)
     if (!parts[k]->empty()) std::memcpy(img.data() + offs[k], parts[k]->data(), 4 * parts[k]->size());
 
-  int dev = 0, cus = 0;
+  int dev = 0, cus = 0, lds = 0;
   if (hipGetDevice(&dev) != hipSuccess ||
-      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
+      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+      hipDeviceGetAttribute(&lds, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess || cus <= 0 ||
+      lds <= 0 || aecct::train_set_attributes((size_t)lds) != hipSuccess)
     return AECCT_ERR_DEVICE;
   void *blk = nullptr;
   hipError_t e = hipMalloc(&blk, total);
@@ -153,7 +167,7 @@ aecct_status aecct_train_create(const uint8_t *H, int32_t m, int32_t n, int32_t 
     return AECCT_ERR_OUT_OF_MEMORY;
   }
   unsigned char *b = (unsigned char *)blk;
-  *tr = aecct_trainer{n, m, L, d, n_layers, heads, hf_eff, dff, dh, eps, aap_eps, dev, cus, blk,
+  *tr = aecct_trainer{n, m, L, d, n_layers, heads, hf_eff, dff, dh, eps, aap_eps, dev, cus, (size_t)lds, blk,
                       (const int32_t *)(b + offs[0]), (const int32_t *)(b + offs[1]), (const int32_t *)(b + offs[2]),
                       (const int32_t *)(b + offs[3]), (const int32_t *)(b + offs[4]), (const int32_t *)(b + offs[5])};
   *out = tr;
@@ -214,17 +228,15 @@ aecct_status aecct_train_grad(const aecct_trainer *tr, const aecct_train_params 
     return ws + o;
   };
   float *gam = ws + W.gam, *sc = ws + W.sc;
-  // the ternary matrices as bf16 fragments of B = T (the forward products) and B = T^T (the input
-  // gradients): at d, d_ff multiples of 64 every product with a ternary operand runs on
-  // train_gemm_tern, else on the fp32 kernels
-  const bool tern = d % 64 == 0 && dff % 64 == 0;
-  auto tfrag = [&](int l, int k, bool trans) {
-    size_t o = 0;   // in uint16 units
+  // a ternary matrix's packed forms: int8 fragments (the forward maps), bf16 fragments of T^T (the input
+  // gradients)
+  auto tpk = [&](int l, int k, bool trans) {
+    size_t o = 0;   // in bytes
     for (int ll = 0; ll < l; ++ll)
-      for (int kk = 0; kk < 6; ++kk) o += 2 * (size_t)K_in[kk] * K_out[kk];
-    for (int kk = 0; kk < k; ++kk) o += 2 * (size_t)K_in[kk] * K_out[kk];
+      for (int kk = 0; kk < 6; ++kk) o += 4 * (size_t)K_in[kk] * K_out[kk];
+    for (int kk = 0; kk < k; ++kk) o += 4 * (size_t)K_in[kk] * K_out[kk];
     if (trans) o += (size_t)K_in[k] * K_out[k];
-    return (void *)((uint16_t *)(ws + W.tb16) + o);
+    return (void *)((unsigned char *)(ws + W.tpk) + o);
   };
   hipError_t e = hipSuccess;
 #define AECCT_TRY(call)              \
@@ -244,57 +256,75 @@ aecct_status aecct_train_grad(const aecct_trainer *tr, const aecct_train_params 
                                        gam + 6 * l + k, sc + 6 * l + k};
     AECCT_TRY(train_aap(jobs, T.aap_eps, s));
   }
-  if (tern)   // both layouts of every matrix, a launch per four layers
-    for (int l0 = 0; l0 < N; l0 += kTrainJobsPerLaunch / 12) {
-      TernPackJobs pj{};
-      for (int l = l0; l < std::min(N, l0 + kTrainJobsPerLaunch / 12); ++l)
-        for (int k = 0; k < 6; ++k)
-          for (int tr = 0; tr < 2; ++tr)
-            pj.j[pj.n++] = TernPackJob{tmat(l, k), (int)K_in[k], (int)K_out[k], tr, tfrag(l, k, tr != 0)};
-      AECCT_TRY(train_pack_tern(pj, s));
-    }
-  float *X = ws + W.x, *X1 = ws + W.x1, *Y = ws + W.y, *tv = ws + W.t;
-  AECCT_TRY(train_embed(y, R, T.n, T.L, d, T.chk_ptr, T.chk_idx, p->embed, p->pos, X, tv, s));
+  for (int l0 = 0; l0 < N; l0 += kTrainJobsPerLaunch / 12) {   // both layouts of every matrix, a launch per four layers
+    TernPackJobs pj{};
+    for (int l = l0; l < std::min(N, l0 + kTrainJobsPerLaunch / 12); ++l)
+      for (int k = 0; k < 6; ++k) {
+        pj.j[pj.n++] = TernPackJob{tmat(l, k), (int)K_in[k], (int)K_out[k], k < 4 ? kTernI8 : kTernI8Hidden, tpk(l, k, false)};
+        pj.j[pj.n++] = TernPackJob{tmat(l, k), (int)K_in[k], (int)K_out[k], kTernBf16T, tpk(l, k, true)};
+      }
+    AECCT_TRY(train_pack_tern(pj, s));
+  }
+  auto i8 = [&](size_t o) { return (int8_t *)(ws + o); };
+  float *X = ws + W.x, *tv = ws + W.t;
+  AECCT_TRY(train_embed(y, R, T.n, T.L, d, T.chk_ptr, T.chk_idx, p->embed, p->pos, X, tv, i8(W.layer[0].xq),
+                        ws + W.layer[0].tx, s));
   auto gemm = [&](bool ta, bool tb, const float *A, int64_t lda, const float *Bm, int64_t ldb, float *C, int64_t ldc,
                   int64_t M, int64_t Nn, int64_t K, const float *scale, const float *bias, bool acc) {
     return train_gemm(ta, tb, A, lda, Bm, ldb, C, ldc, M, Nn, K, scale, bias, acc, part, (int64_t)PF, T.cu_count, s);
   };
-  // C = scale (A op(T)) + bias (+ C) for ternary matrix k of layer l, op(T) = T or (trans) T^T
-  auto tgemm = [&](bool trans, int l, int k, const float *A, int64_t lda, float *C, int64_t ldc, int64_t M, int64_t Nn,
-                   int64_t K, const float *scale, const float *bias, bool acc) {
-    if (tern && train_tern_operands_ok(A, lda, C, ldc, bias, Nn, K))
-      return train_gemm_tern(A, lda, tfrag(l, k, trans), C, ldc, M, Nn, K, scale, bias, acc, s);
-    return gemm(false, trans, A, lda, tmat(l, k), trans ? K : Nn, C, ldc, M, Nn, K, scale, bias, acc);
-  };
   for (int l = 0; l < N; ++l) {
     const TrainWs::Layer &q = W.layer[l];
-    float *Xh = ws + q.xh, *QKV = ws + q.qkv;
-    if (l == 0) AECCT_TRY(train_quant(X, R, d, false, Xh, s));   // later layers: from the previous LN2
-    {
-      // the query, key and value maps as one product over one read of Xh where the ternary path applies
-      const float *bq[3] = {pb[0] + (size_t)l * d, pb[1] + (size_t)l * d, pb[2] + (size_t)l * d};
-      const float *sq[3] = {sc + 6 * l, sc + 6 * l + 1, sc + 6 * l + 2};
-      bool fused = tern;
-      for (int k = 0; k < 3; ++k) fused = fused && train_tern_operands_ok(Xh, d, QKV + k * d, 3 * d, bq[k], d, d);
-      if (fused) {
-        const void *fq[3] = {tfrag(l, 0, false), tfrag(l, 1, false), tfrag(l, 2, false)};
-        AECCT_TRY(train_gemm_tern_seg(Xh, d, fq, QKV, 3 * d, R, d, 3, d, sq, bq, false, s));
-      } else {
-        for (int k = 0; k < 3; ++k) AECCT_TRY(tgemm(false, l, k, Xh, d, QKV + k * d, 3 * d, R, d, d, sq[k], bq[k], false));
-      }
+    TrainQkv qa{i8(q.xq), ws + q.tx, {}, {}, {}, ws + q.qkv, R};
+    for (int k = 0; k < 3; ++k) {
+      qa.f[k] = (const uint64_t *)tpk(l, k, false);
+      qa.s[k] = sc + 6 * l + k;
+      qa.b[k] = pb[k] + (size_t)l * d;
     }
-    TrainAttn at{QKV, R, T.L, d, T.heads, T.hf, T.m1_ptr, T.m1_idx, T.m2_ptr, T.m2_idx, ws + q.o, ws + q.lse,
+    AECCT_TRY(train_qkv(d, qa, T.cu_count, T.lds_max, s));
+    TrainAttn at{ws + q.qkv, R, T.L, d, T.heads, T.hf, T.m1_ptr, T.m1_idx, T.m2_ptr, T.m2_idx, ws + q.o, ws + q.lse,
                  nullptr, nullptr, nullptr};
     AECCT_TRY(train_attention(0, T.dh, at, s));
-    AECCT_TRY(train_quant(ws + q.o, R, d, false, ws + q.oh, s));
-    AECCT_TRY(tgemm(false, l, 3, ws + q.oh, d, Y, d, R, d, d, sc + 6 * l + 3, pb[3] + (size_t)l * d, false));
-    AECCT_TRY(train_ln_fwd(X, Y, R, d, p->ln1_g + (size_t)l * d, p->ln1_b + (size_t)l * d, T.ln_eps, X1, ws + q.xn1,
-                           ws + q.rho1, ws + q.x1h, s));
-    AECCT_TRY(tgemm(false, l, 4, ws + q.x1h, d, ws + q.f, dff, R, dff, d, sc + 6 * l + 4, pb[4] + (size_t)l * dff, false));
-    AECCT_TRY(train_quant(ws + q.f, R, dff, true, ws + q.gh, s));
-    AECCT_TRY(tgemm(false, l, 5, ws + q.gh, dff, Y, d, R, d, dff, sc + 6 * l + 5, pb[5] + (size_t)l * d, false));
-    AECCT_TRY(train_ln_fwd(X1, Y, R, d, p->ln2_g + (size_t)l * d, p->ln2_b + (size_t)l * d, T.ln_eps, X, ws + q.xn2,
-                           ws + q.rho2, l + 1 < N ? ws + W.layer[l + 1].xh : nullptr, s));
+    TrainBlock tb{};
+    tb.o = ws + q.o;
+    tb.res = l ? ws + W.layer[l - 1].xn2 : X;
+    if (l) {
+      tb.res_g = p->ln2_g + (size_t)(l - 1) * d;
+      tb.res_b = p->ln2_b + (size_t)(l - 1) * d;
+    }
+    tb.fo = (const uint64_t *)tpk(l, 3, false);
+    tb.f1 = (const uint64_t *)tpk(l, 4, false);
+    tb.f2 = (const uint64_t *)tpk(l, 5, false);
+    tb.so = sc + 6 * l + 3;
+    tb.s1 = sc + 6 * l + 4;
+    tb.s2 = sc + 6 * l + 5;
+    tb.bo = pb[3] + (size_t)l * d;
+    tb.b1 = pb[4] + (size_t)l * dff;
+    tb.b2 = pb[5] + (size_t)l * d;
+    tb.g1 = p->ln1_g + (size_t)l * d;
+    tb.be1 = p->ln1_b + (size_t)l * d;
+    tb.g2 = p->ln2_g + (size_t)l * d;
+    tb.be2 = p->ln2_b + (size_t)l * d;
+    tb.eps = T.ln_eps;
+    tb.rows = R;
+    tb.oq = i8(q.oq);
+    tb.to = ws + q.to;
+    tb.xn1 = ws + q.xn1;
+    tb.rho1 = ws + q.rho1;
+    tb.x1q = i8(q.x1q);
+    tb.t1 = ws + q.t1;
+    tb.mask = (uint32_t *)(ws + q.mask);
+    tb.gq = i8(q.gq);
+    tb.tg = ws + q.tg;
+    tb.xn2 = ws + q.xn2;
+    tb.rho2 = ws + q.rho2;
+    if (l + 1 < N) {
+      tb.xq = i8(W.layer[l + 1].xq);
+      tb.tx = ws + W.layer[l + 1].tx;
+    } else {
+      tb.x = X;
+    }
+    AECCT_TRY(train_block(d, tb, T.cu_count, T.lds_max, s));
   }
   // head and loss (Section 3, Section 6)
   float *z = ws + W.z, *fo = ws + W.fo, *df = ws + W.df, *dz = ws + W.dz;
@@ -311,58 +341,45 @@ aecct_status aecct_train_grad(const aecct_trainer *tr, const aecct_train_params 
   AECCT_TRY(gemm(false, true, df, T.n, p->head_wo, T.n, dz, T.L, B, T.L, T.n, nullptr, nullptr, false));
   AECCT_TRY(colsum(dz, 1, nullptr, nullptr, R, 1, g->head_b1));
   AECCT_TRY(colsum(X, d, nullptr, dz, R, d, g->head_w1));
-  float *dX = ws + W.dx, *dR = ws + W.dr, *dX1 = ws + W.dx1, *dG = ws + W.dg, *dO = ws + W.dO, *dQKV = ws + W.dqkv;
+  float *dX = ws + W.dx, *dR2 = ws + W.dr2, *dR1 = ws + W.dr1, *dX1 = ws + W.dx1, *dG = ws + W.dg, *dO = ws + W.dO,
+        *dQKV = ws + W.dqkv;
   AECCT_TRY(train_outer(dz, R, p->head_w1, d, dX, s));
+  // C = D + scale (A T^T) (masked) for ternary matrix k of layer l
+  auto tgrad = [&](int l, int k, const float *A, const float *D, const uint32_t *mask, float *C) {
+    const void *f = tpk(l, k, true);
+    const float *sk = sc + 6 * l + k;
+    return train_gemm_tern(A, K_out[k], &f, 1, K_out[k], &sk, D, mask, C, K_in[k], R, K_in[k], s);
+  };
   for (int l = N - 1; l >= 0; --l) {
     const TrainWs::Layer &q = W.layer[l];
     const size_t ld_ = (size_t)l * d;
-    // LN2, second feed-forward map, ReLU, first map
-    AECCT_TRY(train_ln_bwd(dX, p->ln2_g + ld_, ws + q.xn2, ws + q.rho2, R, d, dR, s));
+    // LN2, second feed-forward map, ReLU (the Eq. 2 code of the hidden row passes straight through), first map
+    AECCT_TRY(train_ln_bwd(dX, p->ln2_g + ld_, ws + q.xn2, ws + q.rho2, R, d, dR2, s));
     AECCT_TRY(train_colsum_dual(dX, d, ws + q.xn2, R, d, g->ln2_g + ld_, g->ln2_b + ld_, part, (int64_t)PF, s));
-    AECCT_TRY(gemm(true, false, ws + q.gh, dff, dR, d, gw[5] + wofs(l, 5), d, dff, d, R, nullptr, nullptr, false));
-    AECCT_TRY(colsum(dR, d, nullptr, nullptr, R, d, gb[5] + ld_));
-    AECCT_TRY(tgemm(true, l, 5, dR, d, dG, dff, R, dff, d, sc + 6 * l + 5, nullptr, false));
-    AECCT_TRY(train_relu_bwd(dG, ws + q.f, R * dff, s));
-    AECCT_TRY(gemm(true, false, ws + q.x1h, d, dG, dff, gw[4] + wofs(l, 4), dff, d, dff, R, nullptr, nullptr, false));
-    AECCT_TRY(colsum(dG, dff, nullptr, nullptr, R, dff, gb[4] + (size_t)l * dff));
-    // dX1 = dR + dG T4^T: on the ternary path with dR as the product's addend, else a copy and an
-    // accumulating product
-    if (tern && train_tern_operands_ok(dG, dff, dX1, d, nullptr, d, dff) && ((uintptr_t)dR & 15u) == 0) {
-      const void *f4 = tfrag(l, 4, true);
-      const float *s4 = sc + 6 * l + 4;
-      AECCT_TRY(train_gemm_tern_ksum(dG, dff, &f4, 1, dff, &s4, dR, dX1, d, R, d, s));
-    } else {
-      AECCT_TRY(hipMemcpyAsync(dX1, dR, sizeof(float) * R * d, hipMemcpyDeviceToDevice, s));
-      AECCT_TRY(tgemm(true, l, 4, dG, dff, dX1, d, R, d, dff, sc + 6 * l + 4, nullptr, true));
-    }
+    AECCT_TRY(tgrad(l, 5, dR2, nullptr, (const uint32_t *)(ws + q.mask), dG));
+    AECCT_TRY(tgrad(l, 4, dG, dR2, nullptr, dX1));
     // LN1, output map
-    AECCT_TRY(train_ln_bwd(dX1, p->ln1_g + ld_, ws + q.xn1, ws + q.rho1, R, d, dR, s));
+    AECCT_TRY(train_ln_bwd(dX1, p->ln1_g + ld_, ws + q.xn1, ws + q.rho1, R, d, dR1, s));
     AECCT_TRY(train_colsum_dual(dX1, d, ws + q.xn1, R, d, g->ln1_g + ld_, g->ln1_b + ld_, part, (int64_t)PF, s));
-    // dX = dR + sum_k dQKV_k T_k^T below: one product over the packed gradient with dR as its addend
-    // on the ternary path, else a copy now and three accumulating products
-    const bool qkv_sum = tern && train_tern_operands_ok(dQKV, 3 * d, dX, d, nullptr, d, 3 * d) &&
-                         ((uintptr_t)dR & 15u) == 0;
-    if (!qkv_sum) AECCT_TRY(hipMemcpyAsync(dX, dR, sizeof(float) * R * d, hipMemcpyDeviceToDevice, s));
-    AECCT_TRY(gemm(true, false, ws + q.oh, d, dR, d, gw[3] + wofs(l, 3), d, d, d, R, nullptr, nullptr, false));
-    AECCT_TRY(colsum(dR, d, nullptr, nullptr, R, d, gb[3] + ld_));
-    AECCT_TRY(tgemm(true, l, 3, dR, d, dO, d, R, d, d, sc + 6 * l + 3, nullptr, false));
-    // attention, then the query, key and value maps
+    AECCT_TRY(tgrad(l, 3, dR1, nullptr, nullptr, dO));
+    // attention, then the query, key and value maps: one product over their packed gradient
     TrainAttn at{ws + q.qkv, R, T.L, d, T.heads, T.hf, T.m1_ptr, T.m1_idx, T.m2_ptr, T.m2_idx, ws + q.o, ws + q.lse,
                  dO, dQKV, ws + W.dv};
     AECCT_TRY(train_attention(1, T.dh, at, s));
     AECCT_TRY(train_attention(2, T.dh, at, s));
-    float *const gbq[3] = {gb[0] + ld_, gb[1] + ld_, gb[2] + ld_};
-    AECCT_TRY(train_colsum_split(dQKV, 3 * d, R, d, 3, gbq, part, (int64_t)PF, s));
-    for (int k = 0; k < 3; ++k) {
-      AECCT_TRY(gemm(true, false, ws + q.xh, d, dQKV + k * d, 3 * d, gw[k] + wofs(l, k), d, d, d, R, nullptr, nullptr,
-                     false));
-      if (!qkv_sum) AECCT_TRY(tgemm(true, l, k, dQKV + k * d, 3 * d, dX, d, R, d, d, sc + 6 * l + k, nullptr, true));
-    }
-    if (qkv_sum) {
-      const void *fq[3] = {tfrag(l, 0, true), tfrag(l, 1, true), tfrag(l, 2, true)};
-      const float *sq[3] = {sc + 6 * l, sc + 6 * l + 1, sc + 6 * l + 2};
-      AECCT_TRY(train_gemm_tern_ksum(dQKV, 3 * d, fq, 3, d, sq, dR, dX, d, R, d, s));
-    }
+    const void *fq[3] = {tpk(l, 0, true), tpk(l, 1, true), tpk(l, 2, true)};
+    const float *sq[3] = {sc + 6 * l, sc + 6 * l + 1, sc + 6 * l + 2};
+    AECCT_TRY(train_gemm_tern(dQKV, 3 * d, fq, 3, d, sq, dR1, nullptr, dX, d, R, d, s));
+    // every weight and bias gradient of the layer
+    TrainDwJobs dw{};
+    dw.rows = R;
+    dw.n = kTrainDwJobs;
+    dw.j[0] = TrainDwJob{i8(q.gq), ws + q.tg, dR2, d, dff, d, d, {gw[5] + wofs(l, 5)}, {gb[5] + ld_}};
+    dw.j[1] = TrainDwJob{i8(q.x1q), ws + q.t1, dG, dff, d, dff, dff, {gw[4] + wofs(l, 4)}, {gb[4] + (size_t)l * dff}};
+    dw.j[2] = TrainDwJob{i8(q.oq), ws + q.to, dR1, d, d, d, d, {gw[3] + wofs(l, 3)}, {gb[3] + ld_}};
+    dw.j[3] = TrainDwJob{i8(q.xq), ws + q.tx, dQKV, 3 * d, d, 3 * d, d,
+                         {gw[0] + wofs(l, 0), gw[1] + wofs(l, 1), gw[2] + wofs(l, 2)}, {gb[0] + ld_, gb[1] + ld_, gb[2] + ld_}};
+    AECCT_TRY(train_weight_grads(d, dw, T.cu_count, part, (int64_t)PF, s));
   }
   // the straight-through Eq. 1 gradients of every matrix from its G = Xh^T dY (nothing in the
   // backward reads G once it is formed), a launch per eight layers

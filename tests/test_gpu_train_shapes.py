@@ -1,0 +1,56 @@
+"""The training step's row strips, tiles and row ranges at the sizes where they can go wrong: fewer rows
+than a 16-token strip or a wavefront's eight, a last strip that is partly filled, one layer (the
+first is the last), more layers than a packing or Eq. 1 launch takes, a positional table, odd lengths.
+
+Against the float64 oracle, normwise.  fp32 rounding alone gives a few 1e-7 (test_gpu_train.py, TIGHT);
+an int8 or ternary rounding decision that falls the other way in fp32 shifts the rest of its word by
+a code step, up to 1e-2 on batches of tens of words (FLIP there), and a wrong or missing row or tile
+moves a gradient by its whole share, above 1 / rows of it (at most 154 rows here, so above 6e-3, and
+in most of the twenty gradients far above): the median gradient error has to stay below 1e-3.
+"""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+from workloads import random_qat_params, regular_ldpc_3_6  # noqa: E402
+from workloads.codes import hamming_7_4  # noqa: E402
+from tests.test_gpu_train import _dev, _to_dev, _rel  # noqa: E402
+
+KINDS = ("q", "k", "v", "o", "ff1", "ff2")
+
+
+@pytest.mark.parametrize("n,d,layers,batch,attention,pos", [
+    (7, 32, 1, 1, "hpsa", False),      # 10 rows
+    (7, 64, 1, 2, "casa", True),       # 20 rows: a strip and a quarter
+    (7, 128, 9, 1, "hpsa", True),      # more layers than one launch of Eq. 1 (8) or of the packing (4)
+    (7, 128, 2, 13, "hpsa", False),    # 130 rows: two row ranges of the weight gradients
+    (66, 32, 2, 1, "hpsa", False),     # 99 rows
+    (66, 64, 2, 1, "casa", True),
+    (102, 128, 1, 1, "hpsa", True),    # 153 rows
+])
+def test_train_step_at_awkward_sizes(n, d, layers, batch, attention, pos):
+    import oracle.qat as Q
+    import paper_2410_05911_amd as P
+    H = hamming_7_4() if n == 7 else regular_ldpc_3_6(n, seed=1000 + n)
+    m = H.shape[0]
+    print(f"[train] n {n} d {d} layers {layers} batch {batch} {attention}", flush=True)
+    p = random_qat_params(n, m, d, layers, seed=n + d + layers)
+    rng = np.random.default_rng(n + batch)
+    if pos:
+        p["pos"] = (0.5 * rng.standard_normal((n + m, d))).astype(np.float32)
+    y = (1.0 + 0.7 * rng.standard_normal((batch, n))).astype(np.float32)
+    loss64, _, g64 = Q.forward_backward(H, p, y, None, heads=8, attention=attention)
+    tr = P.Trainer(H, d, layers, heads=8, attention=attention)
+    loss, g = tr.grad(_to_dev(p), _dev(y))
+    torch.cuda.synchronize()
+    errs = {"w_" + k: _rel(g["w"][k].cpu().numpy(), g64["w"][k]) for k in KINDS}
+    errs.update({"b_" + k: _rel(g["b"][k].cpu().numpy(), g64["b"][k]) for k in KINDS if k != "k"})
+    for k in ("embed", "delta", "ln1_g", "ln1_b", "ln2_g", "ln2_b", "head_w1", "head_wo", "head_bo"):
+        errs[k] = _rel(g[k].cpu().numpy(), g64[k])
+    print(" ".join(f"{k}={v:.1e}" for k, v in sorted(errs.items())), flush=True)
+    assert abs(loss.item() - loss64) <= 1e-3 * abs(loss64)
+    assert np.median(list(errs.values())) <= 1e-3 and max(errs.values()) <= 5e-2, errs
+    tr.close()
