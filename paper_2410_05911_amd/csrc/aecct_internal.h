@@ -272,8 +272,8 @@ hipError_t train_weight_grads(int d, TrainDwJobs &jobs, int cu_count, float *par
 hipError_t train_gemm(bool ta, bool tb, const float *A, int64_t lda, const float *B, int64_t ldb, float *C, int64_t ldc,
                       int64_t M, int64_t N, int64_t K, const float *scale, const float *bias, bool accumulate,
                       float *part, int64_t part_floats, int cu_count, hipStream_t s);
-// which: 0 forward (o, lse), 1 query gradients (dqkv's Q third, Dv), 2 key and value gradients
-hipError_t train_attention(int which, int dh, const TrainAttn &a, hipStream_t s);
+// forward (o, lse) or backward (dqkv from dout, o and lse; Dv scratch)
+hipError_t train_attention(bool backward, int dh, const TrainAttn &a, size_t lds_max, hipStream_t s);
 hipError_t train_ln_bwd(const float *dy, const float *g, const float *xn, const float *rho, int64_t rows, int d,
                         float *dR, hipStream_t s);
 // out[c] (+)= sum_r A[r][c] (B[r][c] if B) (w[r] if w), rows of A lda apart, B dense [rows][C]
