@@ -137,9 +137,11 @@ typedef struct aecct_options {
   int32_t layered_attention;  /* aecct_layered_attention (the layered path's form); a form the
                                  shape does not allow gives AECCT_ERR_UNSUPPORTED.  AUTO takes the
                                  first that fits of LDS_F32, LDS_I16, LDS_SPLIT, UNFUSED */
-  int32_t act_scale_mode;     /* aecct_act_scale.  WORD runs on the layered path in its unfused
-                                 form with natural activation layouts (path AUTO resolves to it;
-                                 FUSED or a fused layered form gives AECCT_ERR_UNSUPPORTED) */
+  int32_t act_scale_mode;     /* aecct_act_scale.  WORD runs on the layered path (path AUTO resolves to
+                                 it; FUSED or a fused layered form gives AECCT_ERR_UNSUPPORTED):
+                                 layered_attention UNFUSED with natural activation layouts, AUTO
+                                 with the fused attention kernels where the shape allows them (the
+                                 resolved form is reported as UNFUSED either way) */
 } aecct_options;
 
 typedef struct aecct_model aecct_model;   /* opaque */

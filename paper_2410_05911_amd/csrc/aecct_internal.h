@@ -43,6 +43,8 @@ struct Model {
   int path;              // resolved aecct_path
   int attention;         // aecct_attention; under CASA the second-ring lists hold the union, hf = 0
   int lattn;             // resolved aecct_layered_attention: the layered decode's Q/K/V + attention form
+  int word_form;         // with act_word: the fused attention form its decode runs (1 fp32, 2 int16 keys and
+                         // values in LDS) with the maps in stages (launch_word_stages); 0: the separate kernels
   int act_word;          // 1: Eq. 2 takes one alpha per word (aecct_act_scale WORD), else per token
   int device;            // HIP device the model's memory lives on
   int cu_count;          // compute units of that device (persistent grids)
@@ -149,6 +151,14 @@ hipError_t launch_ternary_gemm(const Model &M, int layer, int kind, const int8_t
 // layout: codes q [words][L][K], a[row] = the word's alpha for each of its L rows.
 hipError_t launch_word_quant(const Model &M, const float *x, int64_t words, int K, bool relu, int8_t *q, float *a,
                              hipStream_t s);
+// One alpha per word, d = 64, 128: m (maxima as float bits, one per word) cleared; raised to max |x| of
+// each word; codes xq and per-row alphas ax of X with those maxima; a layer after its attention (X and x1
+// in lane order, O natural; m1, mh, mx raised on the way; with z the last layer).
+hipError_t launch_word_clear(uint32_t *m, int64_t n, hipStream_t s);
+hipError_t launch_word_absmax(const Model &M, const float *x, int64_t words, uint32_t *m, hipStream_t s);
+hipError_t launch_word_codes(const Model &M, const float *x, int64_t words, const uint32_t *m, int8_t *xq, float *ax, hipStream_t s);
+hipError_t launch_word_stages(const Model &M, int layer, const float *o, float *x, float *x1, int64_t words, uint32_t *omax,
+                              uint32_t *m1, uint32_t *mh, uint32_t *mx, float *z, hipStream_t s);
 // First feed-forward map (Eq. 3) to fp32, before the ReLU: h [rows][d_ff].
 hipError_t launch_ffn1_f32(const Model &M, int layer, const int8_t *x1q, const float *a1, int64_t rows, float *h,
                            hipStream_t s);

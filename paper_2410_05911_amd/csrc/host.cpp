@@ -153,7 +153,8 @@ Plan make_plan(int n, int m, int d, int N, int dff, size_t E, size_t nnz1, size_
 // Layered-path workspace for `words` words: region offsets.
 struct WsPlan {
   size_t x, xq, ax, qkv, oq, ao, x1, x1q, a1, gq, ag;
-  size_t o32, h32;   // fp32 attention output and hidden row (one alpha per word only), or 0
+  size_t o32, h32;   // fp32 attention output and hidden row (one alpha per word, separate kernels), or 0
+  size_t wmax;       // the words' maxima, four per layer and one more (one alpha per word in stages), or 0
   size_t total;
 };
 
@@ -164,13 +165,21 @@ WsPlan ws_plan(const Model &M, int64_t words) {
   // codes in oq otherwise) and per-token scalars (the head's z in a1, the embedding's t in ag);
   // X1, its codes and the hidden codes stay in the token block's registers.
   const bool tb = !M.act_word && aecct::token_block_supported(M);
-  const bool unf = M.lattn == AECCT_LAYERED_ATTN_UNFUSED;
+  const bool unf = M.lattn == AECCT_LAYERED_ATTN_UNFUSED && !M.word_form;
   WsPlan w{};
   size_t off = 0;
   auto take = [&](size_t bytes) { size_t o = off; off = align_up(off + bytes); return o; };
   w.x = take(4 * R * d);
   w.xq = take(R * d);
   w.ax = take(4 * R);
+  if (M.word_form) {   // O in the qkv region, LN1's rows in x1, the head's z in a1
+    w.qkv = take(4 * R * d);
+    w.x1 = take(4 * R * d);
+    w.a1 = take(4 * R);
+    w.wmax = take(4 * (size_t)words * (4 * M.n_layers + 1));
+    w.total = off;
+    return w;
+  }
   w.qkv = take(4 * R * (tb && !unf ? 1 : 3) * d);
   w.oq = take(R * d);
   w.ao = take(4 * R);
@@ -196,7 +205,7 @@ int64_t chunk_words_within(const Model &M, int64_t batch, size_t cap_bytes) {
   if (cap < 1) cap = 1;
   while (cap > 1 && ws_plan(M, cap).total > cap_bytes) --cap;
   if (batch <= cap) return batch;
-  const int64_t slots = aecct::attention_word_slots(M, M.lattn);
+  const int64_t slots = aecct::attention_word_slots(M, M.word_form ? M.word_form : M.lattn);
   const int64_t nchunks = (batch + cap - 1) / cap;
   int64_t cw = (batch + nchunks - 1) / nchunks;
   if (slots > 1 && cw >= slots) {
@@ -687,6 +696,10 @@ aecct_status aecct_create(const uint8_t *H, int32_t m, int32_t n, const aecct_we
     return AECCT_ERR_UNSUPPORTED;
   }
   M.lattn = lattn;
+  // one alpha per word, no form asked for: the fused attention kernels on the word's alpha where a
+  // word fits them, the maps in stages between the word maxima
+  if (M.act_word && lattn_req == AECCT_LAYERED_ATTN_AUTO && aecct::token_block_supported(M))
+    M.word_form = aecct::qkv_attention_supported(M) ? 1 : aecct::qkv_attention_i16_supported(M) ? 2 : 0;
   am->M = M;
   *out = am;
   return AECCT_OK;
@@ -756,6 +769,33 @@ static aecct_status decode_chunks(const Model &M, const float *y, int64_t batch,
   // qa_codes: the lane-pair form that writes O as Eq. 2 codes, which the token block then takes as
   // they are (whole words per block; a word's head groups spread over blocks leave O in fp32)
   const int groups = M.d / 16;
+  if (M.word_form) {
+    uint32_t *wm = (uint32_t *)(ws + W.wmax);
+    for (int64_t w0 = 0; w0 < batch; w0 += cw) {
+      const int64_t nw = batch - w0 < cw ? batch - w0 : cw;
+      const int g_per = aecct::attention_groups_per_block(M, M.word_form, nw);
+      // per layer the maxima of its input, O, LN1's output and the hidden row
+      auto mx = [&](int l, int k) { return wm + (4 * l + k) * nw; };
+      hipError_t e = aecct::launch_word_clear(wm, nw * (4 * M.n_layers + 1), s);
+      if (e == hipSuccess) e = aecct::launch_embed(M, y + w0 * M.n, nw, x, xq, ax, true, s, nullptr);
+      if (e == hipSuccess) e = aecct::launch_word_absmax(M, x, nw, mx(0, 0), s);
+      for (int l = 0; l < M.n_layers && e == hipSuccess; ++l) {
+        e = aecct::launch_word_codes(M, x, nw, mx(l, 0), xq, ax, s);
+        if (e == hipSuccess)
+          e = M.word_form == 1 ? aecct::launch_qkv_attention(M, l, xq, ax, nw, qkv, nullptr, nullptr, true, g_per, s)
+                               : aecct::launch_qkv_attention_i16(M, l, xq, ax, nw, qkv, true, g_per, s);
+        if (e == hipSuccess) e = aecct::launch_word_absmax(M, qkv, nw, mx(l, 1), s);
+        if (e == hipSuccess)
+          e = aecct::launch_word_stages(M, l, qkv, x, x1, nw, mx(l, 1), mx(l, 2), mx(l, 3), mx(l + 1, 0),
+                                        l == M.n_layers - 1 ? a1 : nullptr, s);
+      }
+      if (e == hipSuccess)
+        e = aecct::launch_head_tiled(M, x, y + w0 * M.n, nw, bits + w0 * M.n, logits ? logits + w0 * M.n : nullptr, true, a1,
+                                     s, true);
+      if (e != hipSuccess) return AECCT_ERR_DEVICE;
+    }
+    return AECCT_OK;
+  }
   for (int64_t w0 = 0; w0 < batch; w0 += cw) {
     const int64_t nw = batch - w0 < cw ? batch - w0 : cw;
     const int64_t rows = nw * M.L;

@@ -2217,6 +2217,239 @@ __global__ __launch_bounds__(D * 4, 4) void k_token_strip(TokenBlockArgs p) {
 }
 
 // ------------------------------------------------------------------------------------------
+// The token-local half of a layer with one alpha per word (d = 64, 128).  Each of its four
+// quantisation points needs the word's maximum before its first code, so the token block is cut there
+// into three kernels over 16-token strips, with the maxima gathered by atomics on the bit patterns of
+// non-negative floats (an order-independent maximum; omax, m1, mh, mx: one word each, cleared before the
+// decode):
+//   1: Eq. 2 of O (omax), output map, residual, LN1 -> x1, m1;
+//   2: Eq. 2 of x1 (m1), first feed-forward map and ReLU -> mh only;
+//   3: the same again, Eq. 2 of the hidden row (mh), second map, residual, LN2 -> X, mx (or z).
+// The first map runs twice rather than pass its 4 d values through memory.  The separate kernels wrote
+// every map's result in fp32, read it twice for the maximum and the codes and gathered keys from device
+// memory: a decode of LDPC(128,64), 1024 words, took 2.54 ms, this way 0.82 ms.  Fragments, lane layout
+// and evaluation order as in k_token_block.
+// ------------------------------------------------------------------------------------------
+struct WordStageArgs {
+  const float *o;               // [rows][d] attention output, natural layout (stage 1)
+  float *x, *x1;                // [rows][d] in lane order
+  const uint64_t *fo, *f1, *f2;
+  const float *vec, *b1;
+  float sq_o, sq_1, sq_2, eps;
+  int64_t rows;
+  int L;
+  uint32_t *omax, *m1, *mh, *mx;   // [words]
+  float *z;                     // the last layer's stage 3: the head's z instead of x and mx
+  const float *w1;
+  float head_b1;
+};
+
+template <int D, int ST>
+constexpr size_t word_stage_lds() { return (size_t)(ST == 1 ? 1 : ST == 2 ? 4 : 8) * D * D + (size_t)11 * D * 4; }
+
+// max into the words' slots of m: v of token row0 + c (the same value in its four lanes)
+__device__ __forceinline__ void word_max(uint32_t *m, float v, bool ok, int64_t row0, int64_t last, int L, int c, int g) {
+  const int64_t w = row0 / L;
+  if (last / L == w) {          // the strip lies in one word
+    v = row16_max(ok ? v : 0.0f);
+    if (c == 0 && g == 0) atomicMax(m + w, __builtin_bit_cast(uint32_t, v));
+  } else if (ok && g == 0) {
+    atomicMax(m + (row0 + c) / L, __builtin_bit_cast(uint32_t, v));
+  }
+}
+
+template <int D, int ST>
+__global__ __launch_bounds__(kTbWaves * 64) void k_word_stage(WordStageArgs p) {
+  constexpr int V = D / 4, S = D / 32, TO = D / 16, TH = D / 4, SH = D / 8, NT = kTbWaves * 64;
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  constexpr size_t fb = (size_t)(ST == 1 ? 1 : ST == 2 ? 4 : 8) * D * D;
+  uint64_t *fa = (uint64_t *)smem, *f2 = fa + (size_t)TH * S * 64;   // O's (stage 1) or FF1's fragments, FF2's
+  float *lv = (float *)(smem + fb);
+  const auto stage = [&](const uint64_t *src, uint64_t *dst, int n) {
+#pragma unroll 4
+    for (int u = threadIdx.x; u < n / 2; u += NT) ((uint4 *)dst)[u] = ((const uint4 *)src)[u];
+  };
+  if constexpr (ST == 1) {
+    stage(p.fo, fa, TO * S * 64);
+  } else {
+    stage(p.f1, fa, TH * S * 64);
+    if constexpr (ST == 3) stage(p.f2, f2, TO * SH * 64);
+  }
+  for (int u = threadIdx.x; u < 6 * D; u += NT) lv[u] = p.vec[u];
+  for (int u = threadIdx.x; u < 4 * D; u += NT) lv[6 * D + u] = p.b1[u];
+  for (int u = threadIdx.x; u < D; u += NT) lv[10 * D + u] = p.w1[u];
+  __syncthreads();
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, c = lane & 15, g = lane >> 4;
+  const int64_t nstrips = (p.rows + 15) / 16, stride = (int64_t)gridDim.x * kTbWaves;
+  for (int64_t strip = (int64_t)blockIdx.x * kTbWaves + wave; strip < nstrips; strip += stride) {
+    const int64_t row0 = strip * 16, tok = row0 + c, last = (row0 + 15 < p.rows ? row0 + 16 : p.rows) - 1;
+    const bool ok = tok < p.rows;
+    const int64_t tl = ok ? tok : p.rows - 1, wd = tl / p.L;
+    // LayerNorm of the token's row x (vectors kg, kb of lv), in k_token_block's order; returns max |x|
+    auto norm = [&](float (&x)[V], int kg, int kb) {
+      const float mean = tb_token_sum<V>(x) / (float)D;
+      float sq[V];
+#pragma unroll
+      for (int v = 0; v < V; ++v) {
+        x[v] = x[v] - mean;
+        sq[v] = x[v] * x[v];
+      }
+      const float rho = ln_rsqrt(tb_token_sum<V>(sq) / (float)D + p.eps);
+      float am = 0.0f;
+#pragma unroll
+      for (int v = 0; v < V; ++v) {
+        x[v] = __builtin_fmaf(x[v] * rho, lv[kg * D + g * V + v], lv[kb * D + g * V + v]);
+        am = fmaxf(am, fabsf(x[v]));
+      }
+      return tb_token_max(am);
+    };
+    auto load = [&](const float *src, float (&x)[V]) {
+#pragma unroll
+      for (int u = 0; u < V; u += 4) {
+        const float4 r = *(const float4 *)(src + tl * D + g * V + u);
+        x[u] = r.x; x[u + 1] = r.y; x[u + 2] = r.z; x[u + 3] = r.w;
+      }
+    };
+    auto save = [&](float *dst, const float (&x)[V]) {
+      if (ok)
+#pragma unroll
+        for (int u = 0; u < V; u += 4) *(float4 *)(dst + tok * D + g * V + u) = make_float4(x[u], x[u + 1], x[u + 2], x[u + 3]);
+    };
+    if constexpr (ST == 1) {
+      float x[V];
+      load(p.x, x);
+      const float om = __builtin_bit_cast(float, p.omax[wd]), inv = inv127(om), sc = om * p.sq_o;
+      long bq[S];
+#pragma unroll
+      for (int s = 0; s < S; ++s) {
+        const float *of = p.o + tl * D + 32 * s + 8 * g;
+        const float4 a = *(const float4 *)of, b4 = *(const float4 *)(of + 4);
+        const uint32_t b[8] = {quant_bits(a.x, inv), quant_bits(a.y, inv), quant_bits(a.z, inv), quant_bits(a.w, inv),
+                               quant_bits(b4.x, inv), quant_bits(b4.y, inv), quant_bits(b4.z, inv), quant_bits(b4.w, inv)};
+        bq[s] = tb_pack8(b);
+      }
+#pragma unroll
+      for (int o = 0; o < TO; ++o) {
+        const v4i acc = mfma_i8_steps<S>([&](int s) { return (long)fa[(o * S + s) * 64 + lane]; }, [&](int s) { return bq[s]; },
+                                         v4i{0, 0, 0, 0});
+#pragma unroll
+        for (int i = 0; i < 4; ++i) x[4 * o + i] = x[4 * o + i] + __builtin_fmaf((float)acc[i], sc, lv[g * V + 4 * o + i]);
+      }
+      const float am = norm(x, 1, 2);
+      save(p.x1, x);
+      word_max(p.m1, am, ok, row0, last, p.L, c, g);
+    } else {
+      float x[V];
+      load(p.x1, x);
+      const float a1 = __builtin_bit_cast(float, p.m1[wd]), inv = inv127(a1), sc1 = a1 * p.sq_1;
+      long xb[S];
+#pragma unroll
+      for (int s = 0; s < S; ++s) {
+        uint32_t b[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) b[k] = quant_bits(x[8 * s + k], inv);
+        xb[s] = tb_pack8(b);
+      }
+      // hidden tile o's four values of this lane
+      const auto hidden = [&](int o, float (&f)[4]) {
+        const v4i acc = mfma_i8_steps<S>([&](int s) { return (long)fa[(o * S + s) * 64 + lane]; }, [&](int s) { return xb[s]; },
+                                         v4i{0, 0, 0, 0});
+        const float4 b = *(const float4 *)(lv + 6 * D + 16 * o + 4 * g);
+        f[0] = __builtin_fmaf((float)acc[0], sc1, b.x);
+        f[1] = __builtin_fmaf((float)acc[1], sc1, b.y);
+        f[2] = __builtin_fmaf((float)acc[2], sc1, b.z);
+        f[3] = __builtin_fmaf((float)acc[3], sc1, b.w);
+      };
+      if constexpr (ST == 2) {
+        float am = 0.0f;
+#pragma unroll 4
+        for (int o = 0; o < TH; ++o) {
+          float f[4];
+          hidden(o, f);
+          am = fmaxf(fmaxf(am, fmaxf(f[0], f[1])), fmaxf(f[2], f[3]));
+        }
+        word_max(p.mh, tb_token_max(am + 0.0f), ok, row0, last, p.L, c, g);   // +0: a -0 maximum becomes +0
+      } else {
+        const float ah = __builtin_bit_cast(float, p.mh[wd]), invh = inv127(ah), sc2 = ah * p.sq_2;
+        v4i acc2[TO];
+#pragma unroll
+        for (int o = 0; o < TO; ++o) acc2[o] = v4i{0, 0, 0, 0};
+#pragma unroll 1
+        for (int st = 0; st < SH; st += 2) {
+          long gb[2];
+#pragma unroll
+          for (int j = 0; j < 2; ++j) {
+            uint32_t w[2];
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+              float f[4];
+              hidden(2 * (st + j) + h, f);
+              w[h] = pack4_relu(quant_bits(f[0], invh), quant_bits(f[1], invh), quant_bits(f[2], invh), quant_bits(f[3], invh));
+            }
+            gb[j] = (long)(((uint64_t)w[1] << 32) | w[0]);
+          }
+#pragma unroll
+          for (int o = 0; o < TO; ++o)
+            acc2[o] = mfma_i8_16x16x64((long)f2[(o * SH + st) * 64 + lane], (long)f2[(o * SH + st + 1) * 64 + lane], gb[0],
+                                       gb[1], acc2[o]);
+        }
+#pragma unroll
+        for (int o = 0; o < TO; ++o)
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            x[4 * o + i] = x[4 * o + i] + __builtin_fmaf((float)acc2[o][i], sc2, lv[3 * D + g * V + 4 * o + i]);
+        const float am = norm(x, 4, 5);
+        if (p.z) {
+          float pr[V];
+#pragma unroll
+          for (int v = 0; v < V; ++v) pr[v] = x[v] * lv[10 * D + g * V + v];
+          const float zt = tb_token_sum<V>(pr) + p.head_b1;
+          if (ok && g == 0) p.z[tok] = zt;
+        } else {
+          save(p.x, x);
+          word_max(p.mx, am, ok, row0, last, p.L, c, g);
+        }
+      }
+    }
+  }
+}
+
+__global__ __launch_bounds__(256) void k_fill_zero(uint32_t *p, int64_t n) {
+  for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < n; e += (int64_t)gridDim.x * 256) p[e] = 0u;
+}
+
+// max |x| of each word's per_word floats into m; blocks (word, part of the word)
+__global__ __launch_bounds__(256) void k_word_absmax(const float *x, int64_t per_word, uint32_t *m) {
+  const float4 *xw = (const float4 *)(x + (int64_t)blockIdx.x * per_word);
+  float a = 0.0f;
+  for (int64_t e = (int64_t)blockIdx.y * 256 + threadIdx.x; e < per_word / 4; e += (int64_t)gridDim.y * 256) {
+    const float4 v = xw[e];
+    a = fmaxf(a, fmaxf(fmaxf(fabsf(v.x), fabsf(v.y)), fmaxf(fabsf(v.z), fabsf(v.w))));
+  }
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) a = fmaxf(a, __shfl_xor(a, o, 64));
+  if ((threadIdx.x & 63) == 0) atomicMax(m + blockIdx.x, __builtin_bit_cast(uint32_t, a));
+}
+
+// Eq. 2 codes of X (both in lane order) with the words' maxima m, and each row's alpha: a lane per
+// eight codes (step s, lane group g of a row)
+template <int D>
+__global__ __launch_bounds__(256) void k_word_codes(const float *x, int64_t rows, int L, const uint32_t *m, int8_t *xq, float *ax) {
+  constexpr int P = D / 8;
+  const int64_t u = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  const int64_t r = u / P;
+  if (r >= rows) return;
+  const int k = (int)(u - r * P), s = k >> 2, g = k & 3;
+  const float a = __builtin_bit_cast(float, m[r / L]), inv = inv127(a);
+  const float *xr = x + r * D + g * (D / 4) + 8 * s;
+  const float4 f = *(const float4 *)xr, h = *(const float4 *)(xr + 4);
+  const uint32_t b[8] = {quant_bits(f.x, inv), quant_bits(f.y, inv), quant_bits(f.z, inv), quant_bits(f.w, inv),
+                         quant_bits(h.x, inv), quant_bits(h.y, inv), quant_bits(h.z, inv), quant_bits(h.w, inv)};
+  *(long *)(xq + r * D + 32 * s + 8 * g) = tb_pack8(b);
+  if (k == 0) ax[r] = a;
+}
+
+// ------------------------------------------------------------------------------------------
 // Output head and hard decision (Section 3): one block per word.  z_i = W_{d->1} x_i + b1
 // (16 lanes per token, pairwise over features), then f_o = sum_i z_i W_o[i][o] + b_o in
 // ascending token order, bit = [y < 0] xor [f < 0].
@@ -2947,6 +3180,55 @@ hipError_t launch_token_block(const Model &M, int layer, const float *o, const i
   return M.d == 64 ? run_token_block_oq<64>(M, a, s) : run_token_block_oq<128>(M, a, s);
 }
 
+template <int D, int ST>
+static hipError_t run_word_stage(const Model &M, const WordStageArgs &a, hipStream_t s) {
+  constexpr size_t lds = word_stage_lds<D, ST>();
+  const int64_t groups = ((a.rows + 15) / 16 + kTbWaves - 1) / kTbWaves;
+  const int64_t per_cu = std::max<int64_t>(1, std::min<int64_t>(ST == 3 ? 2 : 3, (int64_t)(M.lds_max / lds)));
+  hipLaunchKernelGGL((k_word_stage<D, ST>), dim3((unsigned)std::min<int64_t>(groups, M.cu_count * per_cu)), dim3(kTbWaves * 64),
+                     lds, s, a);
+  return hipGetLastError();
+}
+
+hipError_t launch_word_clear(uint32_t *m, int64_t n, hipStream_t s) {
+  if (n <= 0) return hipSuccess;
+  hipLaunchKernelGGL(k_fill_zero, dim3((unsigned)std::min<int64_t>((n + 255) / 256, 1024)), dim3(256), 0, s, m, n);
+  return hipGetLastError();
+}
+
+hipError_t launch_word_absmax(const Model &M, const float *x, int64_t words, uint32_t *m, hipStream_t s) {
+  if (words <= 0) return hipSuccess;
+  const int64_t per_word = (int64_t)M.L * M.d;
+  // about eight blocks per compute unit, at least one pass of 1024 floats each
+  const int64_t parts = std::max<int64_t>(1, std::min<int64_t>((per_word + 1023) / 1024, 8 * (int64_t)M.cu_count / words));
+  hipLaunchKernelGGL(k_word_absmax, dim3((unsigned)words, (unsigned)parts), dim3(256), 0, s, x, per_word, m);
+  return hipGetLastError();
+}
+
+hipError_t launch_word_codes(const Model &M, const float *x, int64_t words, const uint32_t *m, int8_t *xq, float *ax, hipStream_t s) {
+  const int64_t rows = words * M.L;
+  if (rows <= 0) return hipSuccess;
+  const dim3 grid((unsigned)((rows * (M.d / 8) + 255) / 256));
+  if (M.d == 64) hipLaunchKernelGGL(k_word_codes<64>, grid, dim3(256), 0, s, x, rows, M.L, m, xq, ax);
+  else if (M.d == 128) hipLaunchKernelGGL(k_word_codes<128>, grid, dim3(256), 0, s, x, rows, M.L, m, xq, ax);
+  else return hipErrorInvalidValue;
+  return hipGetLastError();
+}
+
+hipError_t launch_word_stages(const Model &M, int layer, const float *o, float *x, float *x1, int64_t words, uint32_t *omax,
+                              uint32_t *m1, uint32_t *mh, uint32_t *mx, float *z, hipStream_t s) {
+  if (words <= 0) return hipSuccess;
+  if (!token_block_supported(M)) return hipErrorInvalidValue;
+  const LayerWeights &W = M.layer[layer];
+  const WordStageArgs a{o,       x,       x1,    W.tb_o,         W.tb_1, W.tb_2, W.tb_vec, W.b_ff1, W.sq[3], W.sq[4],
+                        W.sq[5], M.eps,   words * M.L, M.L,      omax,   m1,     mh,       mx,      z,       M.head_w1_lo,
+                        M.head_b1};
+  hipError_t e = M.d == 64 ? run_word_stage<64, 1>(M, a, s) : run_word_stage<128, 1>(M, a, s);
+  if (e == hipSuccess) e = M.d == 64 ? run_word_stage<64, 2>(M, a, s) : run_word_stage<128, 2>(M, a, s);
+  if (e == hipSuccess) e = M.d == 64 ? run_word_stage<64, 3>(M, a, s) : run_word_stage<128, 3>(M, a, s);
+  return e;
+}
+
 hipError_t launch_head_tiled(const Model &M, const float *x, const float *y, int64_t words, uint8_t *bits,
                              float *logits, bool lane_order, float *zbuf, hipStream_t s, bool z_ready) {
   if (words <= 0) return hipSuccess;
@@ -3020,6 +3302,8 @@ hipError_t set_layered_kernel_attributes(const Model &M) {
       token_block_kernel<128, 7>(), token_strip_kernel<128, 0>(), token_strip_kernel<128, 1>(),
       token_strip_kernel<128, 2>(), token_strip_kernel<128, 3>(), token_strip_kernel<128, 4>(),
       token_strip_kernel<128, 5>(), token_strip_kernel<128, 6>(), token_strip_kernel<128, 7>(),
+      (const void *)k_word_stage<64, 1>,  (const void *)k_word_stage<64, 2>,  (const void *)k_word_stage<64, 3>,
+      (const void *)k_word_stage<128, 1>, (const void *)k_word_stage<128, 2>, (const void *)k_word_stage<128, 3>,
       (const void *)k_embed_words<64>,
       (const void *)k_embed_words<128>};
   for (const void *f : fns) {

@@ -76,3 +76,35 @@ def test_fused_word_over_wavefronts_matches_one_wavefront(P, n, m, attention, si
         torch.cuda.synchronize()
         assert torch.equal(f, logits[batch - k:]) and torch.equal(b, bits[batch - k:])
     dec.close()
+
+
+@pytest.mark.parametrize("n,d,heads,attention,hf,sizes", [
+    (66, 64, 8, "hpsa", 4, (1, 3, 700)),        # 99 tokens: strips straddle words
+    (66, 64, 4, "casa", 2, (5,)),               # d_h = 16 at d = 64, positional table
+    (128, 64, 8, "hpsa", 4, (1, 520)),
+    (256, 128, 8, "casa", 2, (1, 40, 300)),     # lane pairs
+    (514, 128, 8, "hpsa", 4, (1, 20)),          # fp32 K, int16 V, 771 tokens
+    (398, 64, 8, "hpsa", 6, (1, 60)),           # int16 K and V
+])
+def test_word_scale_stages_match_separate_kernels(P, n, d, heads, attention, hf, sizes):
+    """One alpha per word: the fused attention with the maps in stages between the word maxima, against the
+    separate kernels (pinned to the oracle by test_gpu_parity.py), bit for bit."""
+    H = regular_ldpc_3_6(n, seed=1000 + n)
+    w = random_weights(n, n // 2, d, 2, heads, seed=n + d, first_ring_heads=hf, attention=attention, act_scale="word",
+                       with_pos=hf == 2)
+    y, _, _ = awgn_words(generator_from_parity(H), max(sizes), (2.0, 4.0), seed=n)
+    yd = torch.from_numpy(y).cuda()
+    staged, separate = P.Decoder(H, w), P.Decoder(H, w, layered_attention=P.LAYERED_ATTN_UNFUSED)
+    bits, logits = separate.decode(yd)
+    torch.cuda.synchronize()
+    assert np.isfinite(logits.cpu().numpy()).all()
+    for k in sizes:
+        print(f"[word] LDPC({n}) d {d} {attention}: {k} words", flush=True)
+        b, f = staged.decode(yd[:k].contiguous())
+        torch.cuda.synchronize()
+        assert torch.equal(f, logits[:k]) and torch.equal(b, bits[:k])
+    b, f = staged.decode_static(yd)
+    torch.cuda.synchronize()
+    assert torch.equal(f, logits) and torch.equal(b, bits)
+    staged.close()
+    separate.close()
