@@ -208,8 +208,9 @@ hipError_t train_embed(const float *y, int64_t rows, int n, int L, int d, const 
                        const int32_t *chk_idx, const float *E, const float *P, float *x, float *t, int8_t *xq, float *tx,
                        hipStream_t s);
 // A ternary matrix T [R][C] (fp32) laid out for the products that read it: int8 fragments for the forward
-// (R C bytes), bf16 fragments of T^T for the input gradients (2 R C bytes); R and C multiples of 32.
-enum TernPackMode { kTernI8 = 0, kTernI8Hidden = 1, kTernBf16T = 2 };
+// (R C bytes), bf16 fragments (2 R C bytes) or selector-byte ones (R C) of T^T for the input gradients; R
+// and C multiples of 32.
+enum TernPackMode { kTernI8 = 0, kTernI8Hidden = 1, kTernBf16T = 2, kTernSelT = 3 };
 struct TernPackJob {
   const float *T;
   int R, C, mode;
@@ -217,13 +218,13 @@ struct TernPackJob {
 };
 struct TernPackJobs { TernPackJob j[kTrainJobsPerLaunch]; int n; };
 hipError_t train_pack_tern(const TernPackJobs &jobs, hipStream_t s);
-// Input gradients on the bf16 matrix cores (fp32 A split exactly into three bf16 parts): C = D + sum_k
+// An input gradient on the bf16 matrix cores (fp32 A split exactly into three bf16 parts): C = D + sum_k
 // scale[k] (A[:, k kseg .. (k + 1) kseg) T_k^T) over nseg (<= 3) ternary matrices along A's row, D an
-// optional addend laid out like C; with mask (N a multiple of 128) the elements whose bit is 0 become 0.
-// N and kseg multiples of 32, A, C and D 16-byte aligned with lda and ldc multiples of 4.
+// optional addend laid out like C.  N and kseg multiples of 32, A, C and D 16-byte aligned with lda and ldc
+// multiples of 4.
 hipError_t train_gemm_tern(const float *A, int64_t lda, const void *const *frag, int nseg, int64_t kseg,
-                           const float *const *scale, const float *D, const uint32_t *mask, float *C, int64_t ldc,
-                           int64_t M, int64_t N, hipStream_t s);
+                           const float *const *scale, const float *D, float *C, int64_t ldc, int64_t M, int64_t N,
+                           hipStream_t s);
 // The query, key and value maps (Eq. 3) of codes xq with row scales tx (alpha / 127): qkv [rows][3 d].
 struct TrainQkv {
   const int8_t *xq;
@@ -237,7 +238,8 @@ hipError_t train_qkv(int d, const TrainQkv &a, int cu_count, size_t lds_max, hip
 // The token-local half of a layer's forward: Eq. 2 of O, output map, residual, LN1, Eq. 2, first
 // feed-forward map, ReLU, Eq. 2, second map, residual, LN2 and Eq. 2 of the next layer's input, leaving
 // what the backward reads: the codes and scales (alpha / 127) of every map's input, both normalised
-// rows and their 1 / sigma, and the ReLU mask (layout: GemmTern::mask).
+// rows and their 1 / sigma, and the ReLU mask: bit 4 (o mod 8) + i of word (row * 4 + g) d / 32 + o / 8 is
+// hidden feature 16 o + 4 g + i.
 struct TrainBlock {
   const float *o;                         // [rows][d]
   const float *res, *res_g, *res_b;       // X [rows][d], or (res_g not null) xn with X = xn res_g + res_b
@@ -255,7 +257,20 @@ struct TrainBlock {
   float *x;                               // the output X (the last layer), or null
 };
 hipError_t train_block(int d, const TrainBlock &a, int cu_count, size_t lds_max, hipStream_t s);
-hipError_t train_set_attributes(size_t lds_max);   // the current device's dynamic LDS for the two
+// The token-local half of a layer's backward, from dX: dR2 and dR1 (the LayerNorms' input gradients), dG (the
+// hidden gradient, masked), dO; lnpart [train_bwd_blocks][4][d]: partial column sums of LN2's and LN1's
+// gain and shift gradients.
+struct TrainBwd {
+  const float *dx, *xn2, *rho2, *xn1, *rho1, *g2, *g1;
+  const uint32_t *mask;
+  const uint64_t *f2, *f1, *fo;      // kTernSelT of the second, first feed-forward and output maps
+  const float *s2, *s1, *so;         // their Eq. 1 scales (device scalars)
+  float *dr2, *dg, *dr1, *dO, *lnpart;
+  int64_t rows;
+};
+int train_bwd_blocks(int64_t rows, int cu_count);
+hipError_t train_bwd(int d, const TrainBwd &a, int cu_count, hipStream_t s);
+hipError_t train_set_attributes(size_t lds_max);   // the current device's dynamic LDS for these kernels
 // Weight and bias gradients of a layer's maps in one launch and one reduction: dw = Xh^T dY with Xh = codes
 // q [rows][K] x scales t [rows], and the column sums of dY [rows][N] (rows ldy apart); column c goes
 // to gw[c / seg][K][seg] and gb[c / seg].  K, N and seg multiples of d.
@@ -270,6 +285,9 @@ struct TrainDwJob {
 struct TrainDwJobs {
   TrainDwJob j[kTrainDwJobs];
   int n;
+  const float *lnpart;           // train_bwd's partial sums of ln_blocks blocks, reduced to ln: LN2's gain
+  int ln_blocks;                 // and shift, LN1's gain and shift
+  float *ln[4];
   int tile0[kTrainDwJobs + 1];   // filled by the launcher from here on
   int64_t rows, chunk;
   int splits;
@@ -284,15 +302,9 @@ hipError_t train_gemm(bool ta, bool tb, const float *A, int64_t lda, const float
                       float *part, int64_t part_floats, int cu_count, hipStream_t s);
 // forward (o, lse) or backward (dqkv from dout, o and lse; Dv scratch)
 hipError_t train_attention(bool backward, int dh, const TrainAttn &a, size_t lds_max, hipStream_t s);
-hipError_t train_ln_bwd(const float *dy, const float *g, const float *xn, const float *rho, int64_t rows, int d,
-                        float *dR, hipStream_t s);
-// out[c] (+)= sum_r A[r][c] (B[r][c] if B) (w[r] if w), rows of A lda apart, B dense [rows][C]
-hipError_t train_colsum(const float *A, int64_t lda, const float *Bm, const float *w, int64_t rows, int C, float *out,
-                        bool accumulate, float *part, int64_t part_floats, hipStream_t s);
-// out_ab[c] = sum_r A[r][c] B[r][c] and out_a[c] = sum_r A[r][c] in one pass (a LayerNorm's gain and
-// shift gradients)
-hipError_t train_colsum_dual(const float *A, int64_t lda, const float *Bm, int64_t rows, int C, float *out_ab,
-                             float *out_a, float *part, int64_t part_floats, hipStream_t s);
+// out[c] = sum_r A[r][c] (w[r] if w), rows of A lda apart
+hipError_t train_colsum(const float *A, int64_t lda, const float *w, int64_t rows, int C, float *out, float *part,
+                        int64_t part_floats, hipStream_t s);
 hipError_t train_rowdot(const float *x, int64_t rows, int d, const float *w1, const float *b1, float *z, hipStream_t s);
 hipError_t train_outer(const float *dz, int64_t rows, const float *w1, int d, float *dx, hipStream_t s);
 hipError_t train_loss(const float *f, const float *y, const float *xs, int64_t count, float *df, float *part,

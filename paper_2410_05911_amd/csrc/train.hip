@@ -448,9 +448,6 @@ struct GemmTern {
   const float *D;
   int64_t M, N, K, lda, ldc;
   const float *scale[3];   // device scalar or null (1)
-  const uint32_t *mask;    // null, or which elements of C stay (the rest are 0): one bit each, word
-                           // (row * 4 + g) * N / 128 + n / 128, bit 4 ((n / 16) mod 8) + i of column
-                           // n = 16 (n / 16) + 4 g + i (N a multiple of 128, blocks of 128 columns)
   int kseg;                // k-steps per k segment (K / 32 when there is one)
 };
 
@@ -460,7 +457,9 @@ __device__ __forceinline__ T pick3(const T (&v)[3], int i) {   // a selected ker
 }
 
 // Ternary matrix T [R][C] (fp32 -1 / 0 / +1, row-major), one job per blockIdx.y, as
-//   kTernBf16T: bf16 B fragments of T^T (k = column, n = row) for the input gradients;
+//   kTernBf16T: bf16 B fragments of T^T (k = column, n = row) for the input gradient of Q | K | V;
+//   kTernSelT: selector-byte A fragments of T^T (output rows = rows of T, k = columns of T in the order
+//   of Hidden below) for k_train_bwd;
 //   kTernI8, kTernI8Hidden: int8 A fragments of the transposed forward products (output rows = columns
 //   of T, k = rows of T): fragment (t, s), lane l: output 16 t + (l & 15), k-slots 8 (l >> 4) + e in
 //   byte e.  Slot k of step s reads input 32 s + k, or (Hidden) input 32 s + 16 (e >> 2) + 4 (l >> 4) +
@@ -484,8 +483,18 @@ __global__ __launch_bounds__(kThreads) void k_pack_tern(TernPackJobs jobs) {
     ((uint4 *)J.out)[u] = make_uint4(h[0] | h[1] << 16, h[2] | h[3] << 16, h[4] | h[5] << 16, h[6] | h[7] << 16);
     return;
   }
-  const int S = R / 32, t = f / S, s = f - t * S, c = 16 * t + (l & 15);
   uint64_t w = 0;
+  if (J.mode == kTernSelT) {
+    const int S = Cc / 32, t = f / S, s = f - t * S, r = 16 * t + (l & 15);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const float v = T[(int64_t)r * Cc + 32 * s + 16 * (e >> 2) + 4 * g + (e & 3)];
+      w |= (uint64_t)(v > 0.0f ? 1u : (v < 0.0f ? 2u : 0u)) << (8 * e);
+    }
+    ((uint64_t *)J.out)[u] = w;
+    return;
+  }
+  const int S = R / 32, t = f / S, s = f - t * S, c = 16 * t + (l & 15);
 #pragma unroll
   for (int e = 0; e < 8; ++e) {
     const int k = 32 * s + (J.mode == kTernI8Hidden ? 16 * (e >> 2) + 4 * g + (e & 3) : 8 * g + e);
@@ -586,18 +595,6 @@ __global__ __launch_bounds__(kThreads) void k_gemm_tern(GemmTern g) {
     }
   }
   if (r >= g.M) return;
-  if constexpr (NJ == 8) {
-    if (g.mask) {
-      const uint32_t keep = g.mask[(r * 4 + grp) * (g.N / 128) + blockIdx.x];
-#pragma unroll
-      for (int j = 0; j < NJ; ++j) {
-        o[j].x = (keep >> (4 * j)) & 1u ? o[j].x : 0.0f;
-        o[j].y = (keep >> (4 * j + 1)) & 1u ? o[j].y : 0.0f;
-        o[j].z = (keep >> (4 * j + 2)) & 1u ? o[j].z : 0.0f;
-        o[j].w = (keep >> (4 * j + 3)) & 1u ? o[j].w : 0.0f;
-      }
-    }
-  }
   float *crow = g.C + r * g.ldc + n0 + 4 * grp;
   const float *drow = g.D ? g.D + r * g.ldc + n0 + 4 * grp : nullptr;
 #pragma unroll
@@ -905,6 +902,178 @@ __global__ __launch_bounds__(kTbWaves * 64) void k_train_block(TrainBlock p) {
 }
 
 // ------------------------------------------------------------------------------------------
+// The token-local half of a layer's backward: LN2, second feed-forward map, ReLU mask, first map, residual,
+// LN1, output map, from dX to the gradients of the maps' outputs (dR2, dG, dR1, which the weight
+// gradients read) and of O, with both LayerNorms' gain and shift gradients summed on the way.  One
+// wavefront per strip, lanes as in k_train_block.  A gradient times a ternary matrix: fp32 splits exactly
+// into three bf16 parts whose products are exact (as k_gemm_tern).  The 9 d^2 ternary entries sit in LDS as
+// one selector byte each and become bf16 by byte permutes, eight per eight entries, behind the three
+// MFMAs they feed; as bf16 they would not fit, and from the L2 their 18 d^2 bytes a strip were what
+// k_gemm_tern spent most of its time on.  Separate kernels passed dX1, dR and dG through memory twice
+// more and read X-hat twice (LDPC(256,128), 256 words: 385 us a layer against 512 MB of inputs and outputs,
+// 100 us at the copy's rate).
+// ------------------------------------------------------------------------------------------
+template <int D>
+constexpr size_t bwd_lds() { return (size_t)9 * D * D + (size_t)2 * D * 4; }
+
+// selector bytes (0, 1, 2) of ternary entries 0, +1, -1 to bf16: byte k of w selects the high byte 00, 3F,
+// BF and the low byte 00, 80, 80
+__device__ __forceinline__ bf16x8 sel_bf16(uint64_t w) {
+  const uint32_t a = (uint32_t)w, b = (uint32_t)(w >> 32);
+  const uint32_t ha = __builtin_amdgcn_perm(0u, 0x00BF3F00u, a), la = __builtin_amdgcn_perm(0u, 0x00808000u, a);
+  const uint32_t hb = __builtin_amdgcn_perm(0u, 0x00BF3F00u, b), lb = __builtin_amdgcn_perm(0u, 0x00808000u, b);
+  uint4 r;
+  r.x = __builtin_amdgcn_perm(ha, la, 0x05010400u);
+  r.y = __builtin_amdgcn_perm(ha, la, 0x07030602u);
+  r.z = __builtin_amdgcn_perm(hb, lb, 0x05010400u);
+  r.w = __builtin_amdgcn_perm(hb, lb, 0x07030602u);
+  return __builtin_bit_cast(bf16x8, r);
+}
+
+template <int D>
+__global__ __launch_bounds__(kTbWaves * 64) void k_train_bwd(TrainBwd p) {
+  constexpr int V = D / 4, S = D / 32, TO = D / 16, TH = D / 4, SH = D / 8, MW = D / 32, NC = (V + 15) / 16;
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, c = lane & 15, g = lane >> 4;
+  uint64_t *f2 = (uint64_t *)smem, *f1 = f2 + (size_t)TH * S * 64, *fo = f1 + (size_t)TO * SH * 64;
+  float *lv = (float *)(smem + (size_t)9 * D * D);   // gains of LN2, LN1
+  stage16(p.f2, f2, D * D / 4, tid);
+  stage16(p.f1, f1, D * D / 4, tid);
+  stage16(p.fo, fo, D * D / 16, tid);
+  stage_vec(p.g2, lv, D, tid);
+  stage_vec(p.g1, lv + D, D, tid);
+  __syncthreads();
+  const float s2 = *p.s2, s1 = *p.s1, so = *p.so;
+  // the lane's fragments from opaque byte offsets: one running address per array, the rest of a read's
+  // address in its immediate offset
+  uint32_t o2 = (uint32_t)lane * 8u, o1 = (uint32_t)(4 * D * D) + o2, oo = (uint32_t)(8 * D * D) + o2;
+  asm volatile("" : "+v"(o2), "+v"(o1), "+v"(oo));
+  const uint64_t *f2l = (const uint64_t *)(smem + o2), *f1l = (const uint64_t *)(smem + o1), *fol = (const uint64_t *)(smem + oo);
+  // column sums over this wavefront's tokens: lane c of a row of 16 keeps the features v with v mod 16 = c
+  float cs[4][NC] = {};
+  const int64_t nstrips = (p.rows + 15) / 16, stride = (int64_t)gridDim.x * kTbWaves;
+  for (int64_t strip = (int64_t)blockIdx.x * kTbWaves + wave; strip < nstrips; strip += stride) {
+    const int64_t tok = strip * 16 + c;
+    const bool ok = tok < p.rows;
+    const int64_t tl = ok ? tok : p.rows - 1;   // padding columns: a copy, never stored or summed
+    // x := the LayerNorm's input gradient from its output gradient x: rho (x g - mean(x g) - xn mean(x g xn));
+    // the sums of x xn and x over the strip's tokens to cs[q], cs[q + 1]
+    auto norm_bwd = [&](float (&x)[V], const float *xnp, const float *rhop, uint32_t og, int q) {
+      asm volatile("" : "+v"(og));   // the gains are read here, not kept from the kernel's start
+      const float *gain = (const float *)(smem + og);
+      float xn[V], a[V];
+#pragma unroll
+      for (int t = 0; t < TO; ++t) {
+        const float4 f = *(const float4 *)(xnp + tl * D + 16 * t + 4 * g);
+        xn[4 * t] = f.x; xn[4 * t + 1] = f.y; xn[4 * t + 2] = f.z; xn[4 * t + 3] = f.w;
+      }
+      const float rho = rhop[tl];
+#pragma unroll
+      for (int v = 0; v < V; ++v) {
+        const float sa = row16_sum(ok ? x[v] * xn[v] : 0.0f), sb = row16_sum(ok ? x[v] : 0.0f);
+        const bool mine = (v & 15) == c;
+        cs[q][v >> 4] += mine ? sa : 0.0f;
+        cs[q + 1][v >> 4] += mine ? sb : 0.0f;
+        asm volatile("" : "+v"(cs[q][v >> 4]), "+v"(cs[q + 1][v >> 4]));   // added now, not kept for later
+        x[v] *= gain[16 * (v >> 2) + (v & 3)];
+        a[v] = x[v] * xn[v];
+        if ((v & 3) == 3) __builtin_amdgcn_sched_barrier(0);
+      }
+      const float m1 = tb_token_sum<V>(x) / (float)D, m2 = tb_token_sum<V>(a) / (float)D;
+#pragma unroll
+      for (int v = 0; v < V; ++v) x[v] = rho * (x[v] - m1 - xn[v] * m2);
+    };
+    auto put = [&](float *dst, const float (&x)[V]) {
+      if (ok)
+#pragma unroll
+        for (int t = 0; t < TO; ++t)
+          *(float4 *)(dst + tok * D + 16 * t + 4 * g) = make_float4(x[4 * t], x[4 * t + 1], x[4 * t + 2], x[4 * t + 3]);
+    };
+    // the three bf16 parts of a row's values as B operands, smallest part last
+    auto parts = [&](const float (&x)[V], bf16x8 (&b)[S][3]) {
+#pragma unroll
+      for (int s = 0; s < S; ++s)
+        split_bf16x3(make_float4(x[8 * s], x[8 * s + 1], x[8 * s + 2], x[8 * s + 3]),
+                     make_float4(x[8 * s + 4], x[8 * s + 5], x[8 * s + 6], x[8 * s + 7]), b[s][0], b[s][1], b[s][2]);
+    };
+    auto mac = [&](uint64_t w, const bf16x8 (&b)[3], f32x4 acc) {
+      const bf16x8 a = sel_bf16(w);
+      acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b[2], acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b[1], acc, 0, 0, 0);
+      return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b[0], acc, 0, 0, 0);
+    };
+    float x[V];
+#pragma unroll
+    for (int t = 0; t < TO; ++t) {
+      const float4 f = *(const float4 *)(p.dx + tl * D + 16 * t + 4 * g);
+      x[4 * t] = f.x; x[4 * t + 1] = f.y; x[4 * t + 2] = f.z; x[4 * t + 3] = f.w;
+    }
+    norm_bwd(x, p.xn2, p.rho2, (uint32_t)(9 * D * D) + 16u * (uint32_t)g, 0);
+    put(p.dr2, x);
+    bf16x8 b[S][3];
+    parts(x, b);
+    f32x4 acc2[TO];
+#pragma unroll
+    for (int o = 0; o < TO; ++o) acc2[o] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll 1
+    for (int st = 0; st < SH; ++st) {   // hidden tiles 2 st, 2 st + 1: the hidden gradient, then its share of dX1
+      const uint32_t keep = p.mask[(tl * 4 + g) * MW + (st >> 2)] >> (8 * (st & 3));
+      float4 h[2];
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        f32x4 acc = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int s = 0; s < S; ++s) acc = mac(f2l[((2 * st + k) * S + s) * 64], b[s], acc);
+        __builtin_amdgcn_sched_barrier(0);   // fragments read and expanded further ahead would spill
+        h[k] = make_float4((keep >> (4 * k)) & 1u ? s2 * acc[0] : 0.0f, (keep >> (4 * k + 1)) & 1u ? s2 * acc[1] : 0.0f,
+                           (keep >> (4 * k + 2)) & 1u ? s2 * acc[2] : 0.0f, (keep >> (4 * k + 3)) & 1u ? s2 * acc[3] : 0.0f);
+        if (ok) *(float4 *)(p.dg + tok * 4 * D + 16 * (2 * st + k) + 4 * g) = h[k];
+      }
+      bf16x8 hb[3];
+      split_bf16x3(h[0], h[1], hb[0], hb[1], hb[2]);
+#pragma unroll
+      for (int o = 0; o < TO; ++o) {
+        acc2[o] = mac(f1l[(o * SH + st) * 64], hb, acc2[o]);
+        if (o & 1) __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+#pragma unroll
+    for (int o = 0; o < TO; ++o)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) x[4 * o + i] += s1 * acc2[o][i];
+    norm_bwd(x, p.xn1, p.rho1, (uint32_t)(9 * D * D + 4 * D) + 16u * (uint32_t)g, 2);
+    put(p.dr1, x);
+    parts(x, b);
+#pragma unroll
+    for (int o = 0; o < TO; ++o) {
+      f32x4 acc = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+      for (int s = 0; s < S; ++s) acc = mac(fol[(o * S + s) * 64], b[s], acc);
+      __builtin_amdgcn_sched_barrier(0);
+      if (ok) *(float4 *)(p.dO + tok * D + 16 * o + 4 * g) = make_float4(so * acc[0], so * acc[1], so * acc[2], so * acc[3]);
+    }
+    __builtin_amdgcn_sched_barrier(0);   // strips do not overlap (their registers would not fit)
+  }
+  // the block's column sums: LN2's gain and shift, LN1's gain and shift
+  __syncthreads();
+  float (*red)[4 * D] = (float (*)[4 * D])smem;
+#pragma unroll
+  for (int q = 0; q < 4; ++q)
+#pragma unroll
+    for (int k = 0; k < NC; ++k) {
+      const int v = 16 * k + c;
+      if (v < V) red[wave][q * D + 16 * (v >> 2) + 4 * g + (v & 3)] = cs[q][k];
+    }
+  __syncthreads();
+  for (int u = tid; u < 4 * D; u += kTbWaves * 64) {
+    float s = 0.0f;
+#pragma unroll
+    for (int w = 0; w < kTbWaves; ++w) s += red[w][u];
+    p.lnpart[(int64_t)blockIdx.x * 4 * D + u] = s;
+  }
+}
+
+// ------------------------------------------------------------------------------------------
 // Weight gradients G = Xh^T dY of every map of a layer, Xh = q t per row (codes and scales): the codes
 // are exact in bf16 and fp32(t dY) splits exactly into three bf16 parts, so three bf16 MFMAs form fp32
 // sums of exact products (as k_gemm_tern), at 16 times the fp32 matrix rate each.  A block takes a
@@ -1012,11 +1181,27 @@ __global__ __launch_bounds__(kThreads, 2) void k_train_dw(TrainDwJobs J) {
 }
 
 // The partial sums of k_train_dw added over the row ranges in order: per tile D D / 256 blocks of its
-// elements, then one of its column sums.
+// elements, then one of its column sums; then the LayerNorm sums of k_train_bwd's blocks.
 template <int D>
 __global__ __launch_bounds__(kThreads) void k_train_dw_reduce(TrainDwJobs J) {
   constexpr int EB = D * D / kThreads;
   const int tile = (int)blockIdx.x / (EB + 1), eb = (int)blockIdx.x - tile * (EB + 1), tid = threadIdx.x;
+  if (tile >= J.tile0[J.n]) {   // the LayerNorms' column sums: 16 columns a block, 16 lanes each
+    __shared__ float red[16][17];
+    const int u = 16 * ((int)blockIdx.x - J.tile0[J.n] * (EB + 1)) + (tid & 15), rl = tid >> 4;
+    float s = 0.0f;
+    for (int b = rl; b < J.ln_blocks; b += 16) s += J.lnpart[(int64_t)b * 4 * D + u];
+    red[rl][tid & 15] = s;
+    __syncthreads();
+    if (rl == 0) {
+#pragma unroll
+      for (int k = 1; k < 16; ++k) s += red[k][tid & 15];
+      const int q = u / D;
+      float *const o = q == 0 ? J.ln[0] : (q == 1 ? J.ln[1] : (q == 2 ? J.ln[2] : J.ln[3]));
+      o[u - q * D] = s;
+    }
+    return;
+  }
   int ji = 0;
   while (ji + 1 < J.n && tile >= J.tile0[ji + 1]) ++ji;
   const TrainDwJob &j = J.j[ji];
@@ -1353,68 +1538,22 @@ __global__ __launch_bounds__(1024) void k_attn_bwd_lds(AttnT p) {
 }
 
 // ------------------------------------------------------------------------------------------
-// LayerNorm backward (Post-LN block, Section 6), one wavefront per row: dR = rho (dxn - mean dxn - xn
-// mean(dxn xn)) with dxn = dy g, xn the normalised row and rho its 1 / sqrt(var + eps).
+// Column sums over rows (the head's), deterministic in two passes: A[r][c] (x w[r]) summed over r for each
+// of A's C columns.  A block covers cw columns (a power of two up to 64) with 256 / cw row lanes; lane l
+// of a block sums the rows l, l + lanes, ... of its chunk (four interleaved partial sums), the lanes are
+// combined by a fixed tree in LDS.  Pass one writes a partial row per chunk, pass two sums the partial
+// rows with the same kernel.
 // ------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(kThreads) void k_ln_bwd(const float *dy, const float *g, const float *xn,
-                                                     const float *rho, int64_t rows, int d, float *dR) {
-  const int64_t r = (int64_t)blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6);
-  const int lane = threadIdx.x & 63;
-  if (r >= rows) return;
-  float dx[2], x[2], s1 = 0.0f, s2 = 0.0f;
-#pragma unroll
-  for (int u = 0; u < 2; ++u) {
-    const int c = lane + 64 * u;
-    dx[u] = c < d ? dy[r * d + c] * g[c] : 0.0f;
-    x[u] = c < d ? xn[r * d + c] : 0.0f;
-    s1 += dx[u];
-    s2 = fmaf(dx[u], x[u], s2);
-  }
-  const float m1 = wave_sum(s1) / (float)d, m2 = wave_sum(s2) / (float)d;
-  const float rh = rho[r];
-#pragma unroll
-  for (int u = 0; u < 2; ++u) {
-    const int c = lane + 64 * u;
-    if (c < d) dR[r * d + c] = rh * (dx[u] - m1 - x[u] * m2);
-  }
-}
-
-// ------------------------------------------------------------------------------------------
-// Column sums over rows, deterministic in two passes: v(r, c) = A[r][c] (x B[r][c]) (x w[r]) summed
-// over r for each of A's C columns.  With dual (B given) each column also sums A alone, as column
-// C + c of the result.  Result column c goes to o[c / seg][c % seg] (several bias vectors from one
-// pass over a packed matrix, or the two sums of the dual form to two vectors).  A block covers cw
-// columns (a power of two up to 64) with 256 / cw row lanes; lane l of a block sums the rows l,
-// l + lanes, ... of its chunk (four interleaved partial sums; the factors present and the dual
-// form are template parameters, as a run-time test between one row's loads and the next row's
-// held each load until the previous one had landed), the lanes are combined by a fixed tree in LDS.  Pass one writes a
-// partial row per chunk, pass two sums the partial rows with the same kernel.
-// ------------------------------------------------------------------------------------------
-struct ColOut {
-  float *o[3];
-  int seg;
-  int64_t ld;   // distance between the rows of partial sums (pass one); 0 for the final sums
-};
-
-template <bool HB, bool HW, bool DUAL>
-__global__ __launch_bounds__(kThreads) void k_colsum(const float *A, int64_t lda, const float *Bm, const float *w,
-                                                     int64_t rows, int C, int cw_log2, int64_t chunk, ColOut out,
-                                                     int accumulate) {
-  constexpr int nv = DUAL ? 2 : 1;
-  __shared__ float red[nv][kThreads];
+template <bool HW>
+__global__ __launch_bounds__(kThreads) void k_colsum(const float *A, int64_t lda, const float *w, int64_t rows, int C,
+                                                     int cw_log2, int64_t chunk, float *out, int64_t ldo) {
+  __shared__ float red[kThreads];
   const int cw = 1 << cw_log2, lanes = kThreads >> cw_log2;
   const int cl = threadIdx.x & (cw - 1), rl = threadIdx.x >> cw_log2;
   const int c = blockIdx.x * cw + cl;
   const int64_t r0 = (int64_t)blockIdx.y * chunk, r1 = std::min<int64_t>(rows, r0 + chunk);
-  float s[nv][4] = {};
-  auto add = [&](int k, int64_t r) {
-    const float a = A[r * lda + c];
-    float v = a;
-    if (HB) v *= Bm[r * C + c];
-    if (HW) v *= w[r];
-    s[0][k] += v;
-    if (DUAL) s[nv - 1][k] += a;
-  };
+  float s[4] = {};
+  auto add = [&](int k, int64_t r) { s[k] += HW ? A[r * lda + c] * w[r] : A[r * lda + c]; };
   if (c < C) {
     int64_t r = r0 + rl;
     for (; r + 3 * lanes < r1; r += 4 * lanes) {
@@ -1425,22 +1564,13 @@ __global__ __launch_bounds__(kThreads) void k_colsum(const float *A, int64_t lda
     }
     for (; r < r1; r += lanes) add(0, r);
   }
-#pragma unroll
-  for (int k = 0; k < nv; ++k) red[k][threadIdx.x] = (s[k][0] + s[k][1]) + (s[k][2] + s[k][3]);
+  red[threadIdx.x] = (s[0] + s[1]) + (s[2] + s[3]);
   __syncthreads();
   for (int st = lanes >> 1; st > 0; st >>= 1) {
-    if (rl < st)
-#pragma unroll
-      for (int k = 0; k < nv; ++k) red[k][threadIdx.x] += red[k][threadIdx.x + (st << cw_log2)];
+    if (rl < st) red[threadIdx.x] += red[threadIdx.x + (st << cw_log2)];
     __syncthreads();
   }
-  if (rl == 0 && c < C)
-#pragma unroll
-    for (int k = 0; k < nv; ++k) {
-      const int cc = c + k * C;
-      float *o = out.o[cc / out.seg] + (int64_t)blockIdx.y * out.ld + cc % out.seg;
-      *o = accumulate ? *o + red[k][threadIdx.x] : red[k][threadIdx.x];
-    }
+  if (rl == 0 && c < C) out[(int64_t)blockIdx.y * ldo + c] = red[threadIdx.x];
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1648,14 +1778,13 @@ hipError_t train_pack_tern(const TernPackJobs &jobs, hipStream_t s) {
 }
 
 hipError_t train_gemm_tern(const float *A, int64_t lda, const void *const *frag, int nseg, int64_t kseg,
-                           const float *const *scale, const float *D, const uint32_t *mask, float *C, int64_t ldc,
-                           int64_t M, int64_t N, hipStream_t s) {
+                           const float *const *scale, const float *D, float *C, int64_t ldc, int64_t M, int64_t N,
+                           hipStream_t s) {
   if (M <= 0 || N <= 0) return hipSuccess;
   const auto al16 = [](const void *q) { return ((uintptr_t)q & 15u) == 0; };   // 16-byte rows of A, C, D
-  if (nseg < 1 || nseg > 3 || kseg <= 0 || kseg % 32 || N % 32 || lda % 4 || ldc % 4 || !al16(A) || !al16(C) || !al16(D) ||
-      (mask && N % 128))
+  if (nseg < 1 || nseg > 3 || kseg <= 0 || kseg % 32 || N % 32 || lda % 4 || ldc % 4 || !al16(A) || !al16(C) || !al16(D))
     return hipErrorInvalidValue;
-  train::GemmTern g{A, {}, C, D, M, N, kseg * nseg, lda, ldc, {}, mask, (int)(kseg / 32)};
+  train::GemmTern g{A, {}, C, D, M, N, kseg * nseg, lda, ldc, {}, (int)(kseg / 32)};
   for (int k = 0; k < nseg; ++k) {
     g.B[k] = (const uint4 *)frag[k];
     g.scale[k] = scale[k];
@@ -1696,7 +1825,8 @@ hipError_t train_set_attributes(size_t lds_max) {
   const void *fns[] = {(const void *)train::k_train_qkv<32>,   (const void *)train::k_train_qkv<64>,
                        (const void *)train::k_train_qkv<128>,  (const void *)train::k_train_block<32>,
                        (const void *)train::k_train_block<64>, (const void *)train::k_train_block<128>,
-                       (const void *)train::k_attn_fwd_lds<4>, (const void *)train::k_attn_fwd_lds<8>,
+                       (const void *)train::k_train_bwd<32>,   (const void *)train::k_train_bwd<64>,
+                       (const void *)train::k_train_bwd<128>,  (const void *)train::k_attn_fwd_lds<4>, (const void *)train::k_attn_fwd_lds<8>,
                        (const void *)train::k_attn_fwd_lds<16>, (const void *)train::k_attn_bwd_lds<4>,
                        (const void *)train::k_attn_bwd_lds<8>, (const void *)train::k_attn_bwd_lds<16>};
   if (lds_max < train::block_lds<128>()) return hipErrorInvalidValue;
@@ -1705,6 +1835,29 @@ hipError_t train_set_attributes(size_t lds_max) {
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
+}
+
+namespace {
+template <int D>
+hipError_t bwd_go(const TrainBwd &a, int blocks, hipStream_t s) {
+  hipLaunchKernelGGL(train::k_train_bwd<D>, dim3((unsigned)blocks), dim3(train::kTbWaves * 64), train::bwd_lds<D>(), s, a);
+  return hipGetLastError();
+}
+}  // namespace
+
+int train_bwd_blocks(int64_t rows, int cu_count) {
+  return (int)std::max<int64_t>(1, std::min<int64_t>(((rows + 15) / 16 + train::kTbWaves - 1) / train::kTbWaves, cu_count));
+}
+
+hipError_t train_bwd(int d, const TrainBwd &a, int cu_count, hipStream_t s) {
+  if (a.rows <= 0) return hipSuccess;
+  const int blocks = train_bwd_blocks(a.rows, cu_count);
+  switch (d) {
+    case 32: return bwd_go<32>(a, blocks, s);
+    case 64: return bwd_go<64>(a, blocks, s);
+    case 128: return bwd_go<128>(a, blocks, s);
+  }
+  return hipErrorInvalidValue;
 }
 
 hipError_t train_qkv(int d, const TrainQkv &a, int cu_count, size_t lds_max, hipStream_t s) {
@@ -1750,7 +1903,7 @@ hipError_t train_weight_grads(int d, TrainDwJobs &J, int cu_count, float *part, 
   J.part = part;
   J.cpart = part + splits * tiles * d * d;
   if (splits * tiles * (int64_t)d * (d + 1) > part_floats) return hipErrorInvalidValue;
-  const dim3 grid((unsigned)tiles, (unsigned)splits), rgrid((unsigned)(tiles * (d * d / train::kThreads + 1)));
+  const dim3 grid((unsigned)tiles, (unsigned)splits), rgrid((unsigned)(tiles * (d * d / train::kThreads + 1) + 4 * d / 16));
   switch (d) {
     case 32:
       hipLaunchKernelGGL(train::k_train_dw<32>, grid, dim3(train::kThreads), 0, s, J);
@@ -1801,61 +1954,28 @@ hipError_t train_attention(bool backward, int dh, const TrainAttn &p, size_t lds
   return hipErrorInvalidValue;
 }
 
-hipError_t train_ln_bwd(const float *dy, const float *g, const float *xn, const float *rho, int64_t rows, int d,
-                        float *dR, hipStream_t s) {
-  if (rows <= 0) return hipSuccess;
-  if (d > 128) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(train::k_ln_bwd, dim3(blocks_for(rows, 4)), dim3(train::kThreads), 0, s, dy, g, xn, rho, rows, d, dR);
-  return hipGetLastError();
-}
-
-namespace {
-// C columns of A summed into the Ct = C (or 2 C, dual) result columns of fin
-hipError_t colsum_run(const float *A, int64_t lda, const float *Bm, const float *w, int64_t rows, int C, bool dual,
-                      const train::ColOut &fin, bool accumulate, float *part, int64_t part_floats, hipStream_t s) {
+hipError_t train_colsum(const float *A, int64_t lda, const float *w, int64_t rows, int C, float *out, float *part,
+                        int64_t part_floats, hipStream_t s) {
   if (C <= 0) return hipSuccess;
-  const int Ct = dual ? 2 * C : C;
   int cwl = 0;
   while ((1 << cwl) < C && cwl < 6) ++cwl;
   const int lanes = train::kThreads >> cwl;
   const unsigned cblocks = blocks_for(C, 1 << cwl);
   // about 1024 blocks in all, each lane summing at least 8 rows
   int64_t chunks = std::min<int64_t>((rows + 8 * lanes - 1) / (8 * lanes), std::max<int64_t>(1, 1024 / cblocks));
-  chunks = std::max<int64_t>(1, std::min<int64_t>(chunks, part_floats / Ct));
+  chunks = std::max<int64_t>(1, std::min<int64_t>(chunks, part_floats / C));
   const int64_t chunk = std::max<int64_t>(1, (rows + chunks - 1) / chunks);
   chunks = std::max<int64_t>(1, (rows + chunk - 1) / chunk);
-  using K = decltype(&train::k_colsum<false, false, false>);
-  K pass1 = dual ? (w ? train::k_colsum<true, true, true> : train::k_colsum<true, false, true>)
-                 : Bm ? (w ? train::k_colsum<true, true, false> : train::k_colsum<true, false, false>)
-                      : (w ? train::k_colsum<false, true, false> : train::k_colsum<false, false, false>);
-  if (chunks == 1) {
-    hipLaunchKernelGGL(pass1, dim3(cblocks, 1), dim3(train::kThreads), 0, s, A, lda, Bm, w, rows, C, cwl, chunk, fin,
-                       accumulate ? 1 : 0);
-    return hipGetLastError();
-  }
-  const train::ColOut pt{{part, nullptr, nullptr}, Ct, (int64_t)Ct};
-  hipLaunchKernelGGL(pass1, dim3(cblocks, (unsigned)chunks), dim3(train::kThreads), 0, s, A, lda, Bm, w, rows, C, cwl,
-                     chunk, pt, 0);
+  const auto pass1 = w ? train::k_colsum<true> : train::k_colsum<false>;
+  float *o = chunks == 1 ? out : part;
+  hipLaunchKernelGGL(pass1, dim3(cblocks, (unsigned)chunks), dim3(train::kThreads), 0, s, A, lda, w, rows, C, cwl, chunk, o,
+                     (int64_t)C);
   // pass two over the partial rows: a block per column, its 256 lanes over the partial rows (a few
   // loads a lane, then the LDS tree), which takes a fraction of the 16-lanes-a-column form's time
-  hipLaunchKernelGGL((train::k_colsum<false, false, false>), dim3((unsigned)Ct, 1), dim3(train::kThreads), 0, s, (const float *)part,
-                     (int64_t)Ct, (const float *)nullptr, (const float *)nullptr, chunks, Ct, 0, chunks, fin,
-                     accumulate ? 1 : 0);
+  if (chunks > 1)
+    hipLaunchKernelGGL(train::k_colsum<false>, dim3((unsigned)C, 1), dim3(train::kThreads), 0, s, (const float *)part, (int64_t)C,
+                       (const float *)nullptr, chunks, C, 0, chunks, out, (int64_t)C);
   return hipGetLastError();
-}
-}  // namespace
-
-hipError_t train_colsum(const float *A, int64_t lda, const float *Bm, const float *w, int64_t rows, int C, float *out,
-                        bool accumulate, float *part, int64_t part_floats, hipStream_t s) {
-  return colsum_run(A, lda, Bm, w, rows, C, false, train::ColOut{{out, nullptr, nullptr}, std::max(C, 1), 0},
-                    accumulate, part, part_floats, s);
-}
-
-hipError_t train_colsum_dual(const float *A, int64_t lda, const float *Bm, int64_t rows, int C, float *out_ab,
-                             float *out_a, float *part, int64_t part_floats, hipStream_t s) {
-  if (!Bm) return hipErrorInvalidValue;
-  return colsum_run(A, lda, Bm, nullptr, rows, C, true, train::ColOut{{out_ab, out_a, nullptr}, std::max(C, 1), 0},
-                    false, part, part_floats, s);
 }
 
 hipError_t train_rowdot(const float *x, int64_t rows, int d, const float *w1, const float *b1, float *z, hipStream_t s) {

@@ -32,7 +32,7 @@ struct TrainWs {
   // attention's output and log-sum-exp, both normalised rows with their 1 / sigma, the ReLU mask
   struct Layer { size_t xq, tx, qkv, lse, o, oq, to, xn1, rho1, x1q, t1, mask, gq, tg, xn2, rho2; };
   std::vector<Layer> layer;
-  size_t t, x, z, fo, df, dz, tw, tpk, gam, sc, lpart, dx, dr2, dr1, dx1, dg, dO, dqkv, dv, part;
+  size_t t, x, z, fo, df, dz, tw, tpk, gam, sc, lpart, lnpart, dx, dr2, dr1, dg, dO, dqkv, dv, part;
   size_t part_floats, total_bytes;
 };
 
@@ -75,14 +75,14 @@ TrainWs train_ws(const aecct_trainer &T, int64_t batch) {
   w.df = take((size_t)batch * T.n);
   w.dz = take(R);
   w.tw = take(weight_floats(T));
-  w.tpk = take(weight_floats(T));   // every ternary matrix as int8 fragments, then as bf16 ones of T^T
+  w.tpk = take(weight_floats(T));   // every ternary matrix as int8 fragments, then T^T's
   w.gam = take((size_t)T.N * 6);
   w.sc = take((size_t)T.N * 6);
   w.lpart = take(((size_t)batch * T.n + 255) / 256 + 1);
+  w.lnpart = take((size_t)aecct::train_bwd_blocks((int64_t)R, T.cu_count) * 4 * d);
   w.dx = take(R * d);
   w.dr2 = take(R * d);
   w.dr1 = take(R * d);
-  w.dx1 = take(R * d);
   w.dg = take(R * dff);
   w.dO = take(R * d);
   w.dqkv = take(R * 3 * d);
@@ -228,8 +228,8 @@ aecct_status aecct_train_grad(const aecct_trainer *tr, const aecct_train_params 
     return ws + o;
   };
   float *gam = ws + W.gam, *sc = ws + W.sc;
-  // a ternary matrix's packed forms: int8 fragments (the forward maps), bf16 fragments of T^T (the input
-  // gradients)
+  // a ternary matrix's packed forms: int8 fragments (the forward maps), then T^T for the input gradients,
+  // as bf16 fragments (query, key, value) or selector bytes (the other three)
   auto tpk = [&](int l, int k, bool trans) {
     size_t o = 0;   // in bytes
     for (int ll = 0; ll < l; ++ll)
@@ -261,7 +261,7 @@ aecct_status aecct_train_grad(const aecct_trainer *tr, const aecct_train_params 
     for (int l = l0; l < std::min(N, l0 + kTrainJobsPerLaunch / 12); ++l)
       for (int k = 0; k < 6; ++k) {
         pj.j[pj.n++] = TernPackJob{tmat(l, k), (int)K_in[k], (int)K_out[k], k < 4 ? kTernI8 : kTernI8Hidden, tpk(l, k, false)};
-        pj.j[pj.n++] = TernPackJob{tmat(l, k), (int)K_in[k], (int)K_out[k], kTernBf16T, tpk(l, k, true)};
+        pj.j[pj.n++] = TernPackJob{tmat(l, k), (int)K_in[k], (int)K_out[k], k < 3 ? kTernBf16T : kTernSelT, tpk(l, k, true)};
       }
     AECCT_TRY(train_pack_tern(pj, s));
   }
@@ -333,46 +333,42 @@ aecct_status aecct_train_grad(const aecct_trainer *tr, const aecct_train_params 
   AECCT_TRY(train_loss(fo, y, xs, B * T.n, df, ws + W.lpart, loss, s));
 
   // ---- backward ------------------------------------------------------------------------------
-  auto colsum = [&](const float *A, int64_t lda, const float *Bm, const float *wr, int64_t rows, int C, float *o) {
-    return train_colsum(A, lda, Bm, wr, rows, C, o, false, part, (int64_t)PF, s);
+  auto colsum = [&](const float *A, int64_t lda, const float *wr, int64_t rows, int C, float *o) {
+    return train_colsum(A, lda, wr, rows, C, o, part, (int64_t)PF, s);
   };
-  AECCT_TRY(colsum(df, T.n, nullptr, nullptr, B, T.n, g->head_bo));
+  AECCT_TRY(colsum(df, T.n, nullptr, B, T.n, g->head_bo));
   AECCT_TRY(gemm(true, false, z, T.L, df, T.n, g->head_wo, T.n, T.L, T.n, B, nullptr, nullptr, false));
   AECCT_TRY(gemm(false, true, df, T.n, p->head_wo, T.n, dz, T.L, B, T.L, T.n, nullptr, nullptr, false));
-  AECCT_TRY(colsum(dz, 1, nullptr, nullptr, R, 1, g->head_b1));
-  AECCT_TRY(colsum(X, d, nullptr, dz, R, d, g->head_w1));
-  float *dX = ws + W.dx, *dR2 = ws + W.dr2, *dR1 = ws + W.dr1, *dX1 = ws + W.dx1, *dG = ws + W.dg, *dO = ws + W.dO,
+  AECCT_TRY(colsum(dz, 1, nullptr, R, 1, g->head_b1));
+  AECCT_TRY(colsum(X, d, dz, R, d, g->head_w1));
+  float *dX = ws + W.dx, *dR2 = ws + W.dr2, *dR1 = ws + W.dr1, *dG = ws + W.dg, *dO = ws + W.dO,
         *dQKV = ws + W.dqkv;
   AECCT_TRY(train_outer(dz, R, p->head_w1, d, dX, s));
-  // C = D + scale (A T^T) (masked) for ternary matrix k of layer l
-  auto tgrad = [&](int l, int k, const float *A, const float *D, const uint32_t *mask, float *C) {
-    const void *f = tpk(l, k, true);
-    const float *sk = sc + 6 * l + k;
-    return train_gemm_tern(A, K_out[k], &f, 1, K_out[k], &sk, D, mask, C, K_in[k], R, K_in[k], s);
-  };
   for (int l = N - 1; l >= 0; --l) {
     const TrainWs::Layer &q = W.layer[l];
     const size_t ld_ = (size_t)l * d;
-    // LN2, second feed-forward map, ReLU (the Eq. 2 code of the hidden row passes straight through), first map
-    AECCT_TRY(train_ln_bwd(dX, p->ln2_g + ld_, ws + q.xn2, ws + q.rho2, R, d, dR2, s));
-    AECCT_TRY(train_colsum_dual(dX, d, ws + q.xn2, R, d, g->ln2_g + ld_, g->ln2_b + ld_, part, (int64_t)PF, s));
-    AECCT_TRY(tgrad(l, 5, dR2, nullptr, (const uint32_t *)(ws + q.mask), dG));
-    AECCT_TRY(tgrad(l, 4, dG, dR2, nullptr, dX1));
-    // LN1, output map
-    AECCT_TRY(train_ln_bwd(dX1, p->ln1_g + ld_, ws + q.xn1, ws + q.rho1, R, d, dR1, s));
-    AECCT_TRY(train_colsum_dual(dX1, d, ws + q.xn1, R, d, g->ln1_g + ld_, g->ln1_b + ld_, part, (int64_t)PF, s));
-    AECCT_TRY(tgrad(l, 3, dR1, nullptr, nullptr, dO));
+    // LN2, second feed-forward map, ReLU (the Eq. 2 code of the hidden row passes straight through), first
+    // map, LN1, output map
+    TrainBwd bw{dX, ws + q.xn2, ws + q.rho2, ws + q.xn1, ws + q.rho1, p->ln2_g + ld_, p->ln1_g + ld_,
+                (const uint32_t *)(ws + q.mask), (const uint64_t *)tpk(l, 5, true), (const uint64_t *)tpk(l, 4, true),
+                (const uint64_t *)tpk(l, 3, true), sc + 6 * l + 5, sc + 6 * l + 4, sc + 6 * l + 3, dR2, dG, dR1, dO,
+                ws + W.lnpart, R};
+    AECCT_TRY(train_bwd(d, bw, T.cu_count, s));
     // attention, then the query, key and value maps: one product over their packed gradient
     TrainAttn at{ws + q.qkv, R, T.L, d, T.heads, T.hf, T.m1_ptr, T.m1_idx, T.m2_ptr, T.m2_idx, ws + q.o, ws + q.lse,
                  dO, dQKV, ws + W.dv};
     AECCT_TRY(train_attention(true, T.dh, at, T.lds_max, s));
     const void *fq[3] = {tpk(l, 0, true), tpk(l, 1, true), tpk(l, 2, true)};
     const float *sq[3] = {sc + 6 * l, sc + 6 * l + 1, sc + 6 * l + 2};
-    AECCT_TRY(train_gemm_tern(dQKV, 3 * d, fq, 3, d, sq, dR1, nullptr, dX, d, R, d, s));
+    AECCT_TRY(train_gemm_tern(dQKV, 3 * d, fq, 3, d, sq, dR1, dX, d, R, d, s));
     // every weight and bias gradient of the layer
     TrainDwJobs dw{};
     dw.rows = R;
     dw.n = kTrainDwJobs;
+    dw.lnpart = ws + W.lnpart;
+    dw.ln_blocks = train_bwd_blocks(R, T.cu_count);
+    float *const lng[4] = {g->ln2_g + ld_, g->ln2_b + ld_, g->ln1_g + ld_, g->ln1_b + ld_};
+    for (int k = 0; k < 4; ++k) dw.ln[k] = lng[k];
     dw.j[0] = TrainDwJob{i8(q.gq), ws + q.tg, dR2, d, dff, d, d, {gw[5] + wofs(l, 5)}, {gb[5] + ld_}};
     dw.j[1] = TrainDwJob{i8(q.x1q), ws + q.t1, dG, dff, d, dff, dff, {gw[4] + wofs(l, 4)}, {gb[4] + (size_t)l * dff}};
     dw.j[2] = TrainDwJob{i8(q.oq), ws + q.to, dR1, d, d, d, d, {gw[3] + wofs(l, 3)}, {gb[3] + ld_}};
