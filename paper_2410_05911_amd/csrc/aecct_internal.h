@@ -198,8 +198,8 @@ struct TrainAttn {
   float *dqkv;          // [rows][3d] gradients of Q | K | V (backward)
   float *Dv;            // [rows][heads] dO . O (backward)
 };
-// the six maps of up to eight layers per launch (one block per matrix), passed by value
-constexpr int kTrainJobsPerLaunch = 48;
+// the six maps of up to ten layers per launch (one block per matrix, at most 64 Ki entries), passed by value
+constexpr int kTrainJobsPerLaunch = 60;
 struct TrainAapJobs { TrainAapJob j[kTrainJobsPerLaunch]; int n; };
 struct TrainDeltaJobs { TrainDeltaJob j[kTrainJobsPerLaunch]; int n; };
 hipError_t train_aap(const TrainAapJobs &jobs, float eps, hipStream_t s);
@@ -293,7 +293,7 @@ struct TrainDwJobs {
   int splits;
   float *part, *cpart;
 };
-int train_dw_splits(int64_t rows, int tiles, int cu_count);   // at most; scratch: splits x tiles x d (d + 1) floats
+int train_dw_splits(int d, int64_t rows, int tiles, int cu_count);   // at most; scratch: splits x tiles x d (d + 1) floats
 hipError_t train_weight_grads(int d, TrainDwJobs &jobs, int cu_count, float *part, int64_t part_floats, hipStream_t s);
 // C[M][N] = (accumulate ? C : 0) + scale (op(A) op(B)) + bias; ta: A stored [K][M]; tb: B stored [N][K].
 // part: scratch of part_floats floats for split reductions over K.

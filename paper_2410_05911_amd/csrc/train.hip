@@ -38,82 +38,88 @@ __device__ __forceinline__ float wave_max(float v) {
 // double and rounded once to fp32), s = fp32(gamma * delta), T = RoundClip(W / fp32(s + eps),
 // -1, 1) with rounding half to even (a zero denominator maps a weight to its sign).  The order
 // statistics come from a radix selection over the bit patterns of |W| (non-negative floats order
-// like their bits), one 8-bit digit per pass.
+// like their bits) in digits of 12, 10 and 9 bits: the first takes the exponent and four mantissa bits, as
+// the exponent alone leaves a wavefront's 64 keys in a few counters whose atomics then run one after the
+// other.  A thread holds its keys (up to 64 Ki per matrix) in registers between the passes.  Eight-bit
+// digits read from memory per pass took 95 us on 128 x 512 matrices.
 // ------------------------------------------------------------------------------------------
 using AapJob = TrainAapJob;
-constexpr int kAapThreads = 1024, kAapWaves = kAapThreads / 64;
+constexpr int kAapThreads = 1024, kAapWaves = kAapThreads / 64, kAapBins = 4096;
 
-// Bucket b's running total over the wave histograms, and the bucket holding the k-th key (k
-// counted from 0 among the keys matching the current prefix) with k's rank inside it: wave 0
-// scans the 256 buckets as four per lane.
-__device__ void select_bucket(const uint32_t (*hist)[256], uint32_t k, uint32_t *pick) {
-  if (threadIdx.x >= 64) return;
-  const int lane = threadIdx.x;
-  uint32_t c[4], t = 0;
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    uint32_t v = 0;
-    for (int w = 0; w < kAapWaves; ++w) v += hist[w][4 * lane + j];
-    c[j] = v;
-    t += v;
-  }
+// The bucket of hist[0 .. bins) (bins a multiple of 512, at most 4096) holding the k-th counted key, and the
+// key's rank inside it, to pick.  Every thread sums bins / 1024 or fewer buckets; wavefront totals through ws.
+__device__ void select_bucket(const uint32_t *hist, int bins, uint32_t k, uint32_t *ws, uint32_t *pick) {
+  const int per = bins > kAapThreads ? bins / kAapThreads : 1, first = threadIdx.x * per;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  uint32_t t = 0;
+  for (int b = 0; b < per; ++b) t += first + b < bins ? hist[first + b] : 0u;
   uint32_t incl = t;
 #pragma unroll
   for (int o = 1; o < 64; o <<= 1) {
     const uint32_t up = __shfl_up(incl, o, 64);
     if (lane >= o) incl += up;
   }
-  const uint32_t excl = incl - t;
-  if (excl <= k && k < incl) {
+  if (lane == 63) ws[wave] = incl;
+  __syncthreads();
+  uint32_t before = 0;
+  for (int w = 0; w < wave; ++w) before += ws[w];
+  const uint32_t excl = before + incl - t;
+  if (excl <= k && k < excl + t) {   // one thread
     uint32_t kk = k - excl;
-    int j = 0;
-    while (j < 3 && kk >= c[j]) kk -= c[j++];
-    pick[0] = 4 * lane + j;
+    int b = first;
+    while (kk >= hist[b]) kk -= hist[b++];
+    pick[0] = b;
     pick[1] = kk;
   }
+  __syncthreads();
 }
 
-// The k-th smallest |w| (k from 0) as a bit pattern: non-negative floats order like their bits,
-// so four passes pick its 8-bit digits from the most significant down, each pass counting the
-// keys that match the digits found so far into per-wave histograms.
-__device__ uint32_t radix_select(const float *w, int64_t count, uint32_t k, uint32_t (*hist)[256], uint32_t *pick) {
-  uint32_t prefix = 0, mask = 0;
-  uint32_t *flat = &hist[0][0];
-  const int wave = threadIdx.x >> 6;
-  for (int shift = 24; shift >= 0; shift -= 8) {
-    for (int b = threadIdx.x; b < kAapWaves * 256; b += kAapThreads) flat[b] = 0;
+// HELD: the launch's largest matrix in multiples of 1024 entries, rounded up to 4, 16 or 64
+template <int HELD>
+__global__ __launch_bounds__(kAapThreads) void k_aap(TrainAapJobs jobs, float eps) {
+  __shared__ uint32_t hist[kAapBins];
+  __shared__ uint32_t pick[2], ws[kAapWaves], wgt[kAapWaves];
+  __shared__ float sden;
+  const AapJob J = jobs.j[blockIdx.x];
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, count = (int)J.count;
+  const uint32_t lo = (uint32_t)((count - 1) / 2);
+  const int held = count / kAapThreads;   // whole: d x d and d x 4 d entries of d = 32, 64, 128
+  float w[HELD];
+#pragma unroll
+  for (int e = 0; e < HELD; ++e) {
+    w[e] = 0.0f;
+    if (e < held) w[e] = J.w[tid + e * kAapThreads];
+  }
+  uint32_t prefix = 0, mask = 0, k = lo;
+#pragma unroll
+  for (int pass = 0; pass < 3; ++pass) {
+    const int shift = pass == 0 ? 19 : (pass == 1 ? 9 : 0), bins = pass == 0 ? 4096 : (pass == 1 ? 1024 : 512);
+    for (int b = tid; b < bins; b += kAapThreads) hist[b] = 0;
     __syncthreads();
-    for (int64_t e = threadIdx.x; e < count; e += kAapThreads) {
+#pragma unroll
+    for (int e = 0; e < HELD; ++e) {
       const uint32_t key = __float_as_uint(fabsf(w[e]));
-      if ((key & mask) == prefix) atomicAdd(&hist[wave][(key >> shift) & 255u], 1u);
+      if (e < held && (key & mask) == prefix) atomicAdd(&hist[(key >> shift) & (bins - 1)], 1u);
+      if ((e & 3) == 3) __builtin_amdgcn_sched_barrier(0);   // few keys in the making: the held ones fill the registers
     }
     __syncthreads();
-    select_bucket(hist, k, pick);
-    __syncthreads();
+    select_bucket(hist, bins, k, ws, pick);
     prefix |= pick[0] << shift;
-    mask |= 255u << shift;
+    mask |= (uint32_t)(bins - 1) << shift;
     k = pick[1];
     __syncthreads();
   }
-  return prefix;
-}
-
-__global__ __launch_bounds__(kAapThreads) void k_aap(TrainAapJobs jobs, float eps) {
-  __shared__ uint32_t hist[kAapWaves][256];
-  __shared__ uint32_t pick[2];
-  __shared__ uint32_t wle[kAapWaves], wgt[kAapWaves];
-  __shared__ float sden;
-  const AapJob J = jobs.j[blockIdx.x];
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const uint32_t lo = (uint32_t)((J.count - 1) / 2);
-  const uint32_t a_lo = radix_select(J.w, J.count, lo, hist, pick);
+  const uint32_t a_lo = prefix;
   // the next order statistic: a_lo again if more than lo + 1 keys are <= a_lo, else the least
   // key above it
   uint32_t le = 0, gt = 0xffffffffu;
-  for (int64_t e = threadIdx.x; e < J.count; e += kAapThreads) {
-    const uint32_t key = __float_as_uint(fabsf(J.w[e]));
-    if (key <= a_lo) ++le;
-    else gt = min(gt, key);
+#pragma unroll
+  for (int e = 0; e < HELD; ++e) {
+    const uint32_t key = __float_as_uint(fabsf(w[e]));
+    if (e < held) {
+      if (key <= a_lo) ++le;
+      else gt = min(gt, key);
+    }
   }
 #pragma unroll
   for (int o = 32; o >= 1; o >>= 1) {
@@ -121,18 +127,18 @@ __global__ __launch_bounds__(kAapThreads) void k_aap(TrainAapJobs jobs, float ep
     gt = min(gt, (uint32_t)__shfl_xor(gt, o, 64));
   }
   if (lane == 0) {
-    wle[wave] = le;
+    ws[wave] = le;
     wgt[wave] = gt;
   }
   __syncthreads();
-  if (threadIdx.x == 0) {
+  if (tid == 0) {
     uint32_t n_le = 0, g = 0xffffffffu;
-    for (int w = 0; w < kAapWaves; ++w) {
-      n_le += wle[w];
-      g = min(g, wgt[w]);
+    for (int u = 0; u < kAapWaves; ++u) {
+      n_le += ws[u];
+      g = min(g, wgt[u]);
     }
-    const uint32_t a_hi = ((int64_t)lo + 1 >= J.count || n_le > lo + 1) ? a_lo : g;
-    const double pos = 0.5 * (double)(J.count - 1);
+    const uint32_t a_hi = (lo + 1 >= (uint32_t)count || n_le > lo + 1) ? a_lo : g;
+    const double pos = 0.5 * (double)(count - 1);
     const double frac = pos - (double)lo;
     const double flo = (double)__uint_as_float(a_lo), fhi = (double)__uint_as_float(a_hi);
     const float gamma = (float)(flo + frac * (fhi - flo));
@@ -143,10 +149,14 @@ __global__ __launch_bounds__(kAapThreads) void k_aap(TrainAapJobs jobs, float ep
   }
   __syncthreads();
   const float den = sden;
-  for (int64_t e = threadIdx.x; e < J.count; e += kAapThreads) {
-    const float x = J.w[e];
-    float r = den == 0.0f ? (x > 0.0f ? 1.0f : (x < 0.0f ? -1.0f : 0.0f)) : rintf(x / den);
-    J.t[e] = fminf(1.0f, fmaxf(-1.0f, r));
+#pragma unroll
+  for (int e = 0; e < HELD; ++e) {
+    if (e < held) {
+      const float x = w[e];
+      float r = den == 0.0f ? (x > 0.0f ? 1.0f : (x < 0.0f ? -1.0f : 0.0f)) : rintf(x / den);
+      J.t[tid + e * kAapThreads] = fminf(1.0f, fmaxf(-1.0f, r));
+    }
+    if ((e & 3) == 3) __builtin_amdgcn_sched_barrier(0);
   }
 }
 
@@ -197,10 +207,13 @@ __global__ __launch_bounds__(kThreads) void k_embed(const float *y, int64_t rows
 // ------------------------------------------------------------------------------------------
 // fp32 GEMM: C[M][N] = beta C + scale (op(A) op(B)) + bias[N], op(A) = A [M][K] (lda) or, with TA,
 // the transpose of A stored [K][M]; op(B) = B [K][N] (ldb) or, with TB, the transpose of B stored
-// [N][K].  64 x 64 output tiles, 16-deep K steps through LDS, 4 x 4 outputs per thread, FMAs in
-// ascending k.  With gridDim.z > 1 each z takes one contiguous k range and writes its raw sum to
+// [N][K].  64 x 64 output tiles, 64-deep K steps through LDS (the head's short products take one or two:
+// 16-deep steps, each with a memory latency of its own, took 39 us in all on BCH(31,16), 128 words),
+// 4 x 4 outputs per thread, FMAs in ascending k.  With gridDim.z > 1 each z takes one contiguous k range and writes its raw sum to
 // part[z][M][N]; k_gemm_reduce then adds the ranges in index order and applies the epilogue.
 // ------------------------------------------------------------------------------------------
+constexpr int kVgK = 64;
+
 struct GemmF32 {
   const float *A, *B;
   float *C;
@@ -215,32 +228,34 @@ struct GemmF32 {
 
 template <bool TA, bool TB>
 __global__ __launch_bounds__(kThreads) void k_gemm(GemmF32 g) {
-  __shared__ float As[16][64 + 4];
-  __shared__ float Bs[16][64 + 4];
+  __shared__ float As[kVgK][64 + 4];
+  __shared__ float Bs[kVgK][64 + 4];
   const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
   const int64_t m0 = (int64_t)blockIdx.y * 64, n0 = (int64_t)blockIdx.x * 64;
   const int64_t kb = (int64_t)blockIdx.z * g.kchunk, ke = std::min<int64_t>(g.K, kb + g.kchunk);
   float acc[4][4] = {};
-  for (int64_t k0 = kb; k0 < ke; k0 += 16) {
+  for (int64_t k0 = kb; k0 < ke; k0 += kVgK) {
+    float va[kVgK / 4], vb[kVgK / 4];   // every load of the step before its first LDS store
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
+    for (int u = 0; u < kVgK / 4; ++u) {
       const int idx = tid + kThreads * u;
-      int mm, kk;
-      if (TA) { kk = idx >> 6; mm = idx & 63; } else { mm = idx >> 4; kk = idx & 15; }
-      const int64_t gm = m0 + mm, gk = k0 + kk;
-      float v = 0.0f;
-      if (gm < g.M && gk < ke) v = TA ? g.A[gk * g.lda + gm] : g.A[gm * g.lda + gk];
-      As[kk][mm] = v;
-      int nn;
-      if (TB) { nn = idx >> 4; kk = idx & 15; } else { kk = idx >> 6; nn = idx & 63; }
-      const int64_t gn = n0 + nn, gk2 = k0 + kk;
-      float w = 0.0f;
-      if (gn < g.N && gk2 < ke) w = TB ? g.B[gn * g.ldb + gk2] : g.B[gk2 * g.ldb + gn];
-      Bs[kk][nn] = w;
+      const int ma = TA ? idx & 63 : idx / kVgK, ka = TA ? idx >> 6 : idx % kVgK;
+      const int64_t gm = m0 + ma, gk = k0 + ka;
+      va[u] = gm < g.M && gk < ke ? (TA ? g.A[gk * g.lda + gm] : g.A[gm * g.lda + gk]) : 0.0f;
+      const int nb = TB ? idx / kVgK : idx & 63, kb2 = TB ? idx % kVgK : idx >> 6;
+      const int64_t gn = n0 + nb, gk2 = k0 + kb2;
+      vb[u] = gn < g.N && gk2 < ke ? (TB ? g.B[gn * g.ldb + gk2] : g.B[gk2 * g.ldb + gn]) : 0.0f;
+    }
+#pragma unroll
+    for (int u = 0; u < kVgK / 4; ++u) {
+      const int idx = tid + kThreads * u;
+      As[TA ? idx >> 6 : idx % kVgK][TA ? idx & 63 : idx / kVgK] = va[u];
+      Bs[TB ? idx % kVgK : idx >> 6][TB ? idx / kVgK : idx & 63] = vb[u];
     }
     __syncthreads();
-#pragma unroll
-    for (int kk = 0; kk < 16; ++kk) {
+    const int kn = (int)std::min<int64_t>(kVgK, ke - k0);
+#pragma unroll 8
+    for (int kk = 0; kk < kn; ++kk) {
       float a[4], b[4];
 #pragma unroll
       for (int i = 0; i < 4; ++i) a[i] = As[kk][4 * ty + i];
@@ -1090,12 +1105,17 @@ __global__ __launch_bounds__(kThreads, 2) void k_train_dw(TrainDwJobs J) {
   constexpr int CP = D / 2, RG = kThreads / CP, RS = 8 * RG, TM = D / 32;
   __shared__ uint4 As[RG][D], Bs[3][RG][D];   // eight rows of a column as bf16
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, fr = lane >> 4, fc = lane & 15;
-  const int cp = tid % CP, rg = tid / CP;
+  const int cp = tid % CP, rg = CP == 64 ? __builtin_amdgcn_readfirstlane(wave) : tid / CP;   // (scalar loads of t)
+  // Block to (row range, tile): blocks go to the eight XCDs in turn, and the tiles of a row range read the
+  // same rows (dR2 and x1's codes four times each), so they take blocks b, b + 8, ... of one XCD where the
+  // ranges are a multiple of eight.
+  const int tiles = J.tile0[J.n], b = (int)blockIdx.x, k8 = b >> 3;
+  const int split = J.splits % 8 ? b / tiles : k8 / tiles * 8 + (b & 7), bt = J.splits % 8 ? b % tiles : k8 % tiles;
   int ji = 0;
-  while (ji + 1 < J.n && (int)blockIdx.x >= J.tile0[ji + 1]) ++ji;
+  while (ji + 1 < J.n && bt >= J.tile0[ji + 1]) ++ji;
   const TrainDwJob &j = J.j[ji];
-  const int tile = (int)blockIdx.x - J.tile0[ji], kts = j.K / D, nt = tile / kts, kt = tile - nt * kts;
-  const int64_t r0 = (int64_t)blockIdx.y * J.chunk, r1 = std::min<int64_t>(J.rows, r0 + J.chunk);
+  const int tile = bt - J.tile0[ji], kts = j.K / D, nt = tile / kts, kt = tile - nt * kts;
+  const int64_t r0 = (int64_t)split * J.chunk, r1 = std::min<int64_t>(J.rows, r0 + J.chunk);
   const int8_t *qp = j.q + kt * D + 2 * cp;
   const float *yp = j.dy + nt * D + 2 * cp;
   const float *tp = j.t;
@@ -1158,7 +1178,7 @@ __global__ __launch_bounds__(kThreads, 2) void k_train_dw(TrainDwJobs J) {
     }
     __syncthreads();
   }
-  const int64_t slot = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
+  const int64_t slot = (int64_t)split * tiles + bt;
   float *out = J.part + slot * D * D;
 #pragma unroll
   for (int a = 0; a < TM; ++a)
@@ -1629,15 +1649,32 @@ __global__ __launch_bounds__(64) void k_loss_final(const float *part, int n, flo
   *loss = s * inv_count;
 }
 
-// dE[i][c] = sum_b t[b L + i] dX[b L + i][c] (the embedding is t_i E_i)
+// dE[i][c] = sum_b t[b L + i] dX[b L + i][c] (the embedding is t_i E_i): a block takes 32 columns of a token,
+// eight lanes over the words per column, added in lane order (one lane per element walked the words
+// alone: 104 us at 256 words of LDPC(256,128), 35 us at 128 of BCH(31,16)).
 __global__ __launch_bounds__(kThreads) void k_embed_grad(const float *t, const float *dx, int64_t words, int L, int d,
                                                          float *de) {
-  const int64_t e = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-  if (e >= (int64_t)L * d) return;
-  const int64_t i = e / d, c = e - i * d;
-  float s = 0.0f;
-  for (int64_t b = 0; b < words; ++b) s = fmaf(t[b * L + i], dx[(b * L + i) * d + c], s);
-  de[e] = s;
+  __shared__ float red[kThreads / 32][32];
+  const int cl = threadIdx.x & 31, bl = threadIdx.x >> 5, c = blockIdx.y * 32 + cl;   // d a multiple of 32
+  const int64_t i = blockIdx.x;
+  constexpr int kLanes = kThreads / 32;
+  float s[4] = {};
+  int64_t b = bl;
+  for (; b + 3 * kLanes < words; b += 4 * kLanes)
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int64_t r = (b + u * kLanes) * L + i;
+      s[u] = fmaf(t[r], dx[r * d + c], s[u]);
+    }
+  for (; b < words; b += kLanes) s[0] = fmaf(t[b * L + i], dx[(b * L + i) * d + c], s[0]);
+  red[bl][cl] = (s[0] + s[1]) + (s[2] + s[3]);
+  __syncthreads();
+  if (bl == 0) {
+    float v = red[0][cl];
+#pragma unroll
+    for (int k = 1; k < kLanes; ++k) v += red[k][cl];
+    de[i * d + c] = v;
+  }
 }
 
 // The straight-through Eq. 1 gradients of one matrix, one block per matrix: G = Xh^T dY arrives in
@@ -1695,7 +1732,16 @@ inline unsigned blocks_for(int64_t n, int per) { return (unsigned)((n + per - 1)
 
 hipError_t train_aap(const TrainAapJobs &jobs, float eps, hipStream_t s) {
   if (jobs.n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(train::k_aap, dim3((unsigned)jobs.n), dim3(train::kAapThreads), 0, s, jobs, eps);
+  int64_t most = 0;
+  for (int k = 0; k < jobs.n; ++k) {
+    if (jobs.j[k].count <= 0 || jobs.j[k].count % train::kAapThreads) return hipErrorInvalidValue;
+    most = std::max(most, jobs.j[k].count / train::kAapThreads);
+  }
+  const dim3 grid((unsigned)jobs.n), block(train::kAapThreads);
+  if (most <= 4) hipLaunchKernelGGL(train::k_aap<4>, grid, block, 0, s, jobs, eps);
+  else if (most <= 16) hipLaunchKernelGGL(train::k_aap<16>, grid, block, 0, s, jobs, eps);
+  else if (most <= 64) hipLaunchKernelGGL(train::k_aap<64>, grid, block, 0, s, jobs, eps);
+  else return hipErrorInvalidValue;
   return hipGetLastError();
 }
 
@@ -1733,7 +1779,7 @@ hipError_t train_gemm(bool ta, bool tb, const float *A, int64_t lda, const float
   int64_t splits = std::max<int64_t>(1, std::min<int64_t>((2 * (int64_t)cu_count + tiles - 1) / tiles, (K + 127) / 128));
   splits = std::min<int64_t>(splits, part_floats / (M * N));
   if (splits < 1) splits = 1;
-  const int64_t kq = mfma ? train::kMfK : 16;
+  const int64_t kq = mfma ? train::kMfK : train::kVgK;
   g.kchunk = (((K + splits - 1) / splits) + kq - 1) / kq * kq;
   if (g.kchunk < kq) g.kchunk = kq;
   splits = (K + g.kchunk - 1) / g.kchunk;
@@ -1880,9 +1926,11 @@ hipError_t train_block(int d, const TrainBlock &a, int cu_count, size_t lds_max,
   return hipErrorInvalidValue;
 }
 
-int train_dw_splits(int64_t rows, int tiles, int cu_count) {
-  // about two blocks per compute unit over all tiles, at least 128 rows each
-  const int64_t want = (2 * (int64_t)cu_count + tiles - 1) / tiles;
+int train_dw_splits(int d, int64_t rows, int tiles, int cu_count) {
+  // three blocks per compute unit at d = 128, as many as the register file holds (LDPC(256,128), 256 words:
+  // 7.78 ms a step, with two 8.04), two below (LDPC(128,64), 125 words: 0.93 ms, with three or four 0.94: more
+  // partial sums), at least 128 rows each
+  const int64_t want = ((d == 128 ? 3 : 2) * (int64_t)cu_count + tiles - 1) / tiles;
   return (int)std::max<int64_t>(1, std::min<int64_t>(want, (rows + 127) / 128));
 }
 
@@ -1896,14 +1944,15 @@ hipError_t train_weight_grads(int d, TrainDwJobs &J, int cu_count, float *part, 
   }
   const int tiles = J.tile0[J.n];
   const int rs = 4096 / d;   // rows of one step of the kernel
-  int64_t splits = train_dw_splits(J.rows, tiles, cu_count);
+  int64_t splits = train_dw_splits(d, J.rows, tiles, cu_count);
+  if (splits > 8) splits = splits / 8 * 8;
   J.chunk = ((J.rows + splits - 1) / splits + rs - 1) / rs * rs;
   splits = (J.rows + J.chunk - 1) / J.chunk;
   J.splits = (int)splits;
   J.part = part;
   J.cpart = part + splits * tiles * d * d;
   if (splits * tiles * (int64_t)d * (d + 1) > part_floats) return hipErrorInvalidValue;
-  const dim3 grid((unsigned)tiles, (unsigned)splits), rgrid((unsigned)(tiles * (d * d / train::kThreads + 1) + 4 * d / 16));
+  const dim3 grid((unsigned)(tiles * splits)), rgrid((unsigned)(tiles * (d * d / train::kThreads + 1) + 4 * d / 16));
   switch (d) {
     case 32:
       hipLaunchKernelGGL(train::k_train_dw<32>, grid, dim3(train::kThreads), 0, s, J);
@@ -2002,8 +2051,8 @@ hipError_t train_loss(const float *f, const float *y, const float *xs, int64_t c
 }
 
 hipError_t train_embed_grad(const float *t, const float *dx, int64_t words, int L, int d, float *de, hipStream_t s) {
-  hipLaunchKernelGGL(train::k_embed_grad, dim3(blocks_for((int64_t)L * d, train::kThreads)), dim3(train::kThreads), 0, s,
-                     t, dx, words, L, d, de);
+  hipLaunchKernelGGL(train::k_embed_grad, dim3((unsigned)L, (unsigned)(d / 32)), dim3(train::kThreads), 0, s, t, dx, words, L, d,
+                     de);
   return hipGetLastError();
 }
 

@@ -89,7 +89,7 @@ TrainWs train_ws(const aecct_trainer &T, int64_t batch) {
   w.dv = take(R * h);
   w.part_floats = std::max<size_t>(size_t(1) << 22, 4 * std::max<size_t>((size_t)T.L * T.n, d * dff));
   w.part_floats = std::max<size_t>(
-      w.part_floats, (size_t)aecct::train_dw_splits((int64_t)R, kDwTiles, T.cu_count) * kDwTiles * d * (d + 1));
+      w.part_floats, (size_t)aecct::train_dw_splits((int)d, (int64_t)R, kDwTiles, T.cu_count) * kDwTiles * d * (d + 1));
   w.part = take(w.part_floats);
   w.total_bytes = off;
   return w;
@@ -247,7 +247,7 @@ aecct_status aecct_train_grad(const aecct_trainer *tr, const aecct_train_params 
 
   // ---- forward -------------------------------------------------------------------------------
   // Eq. 1 of every layer's six matrices first (they depend on the weights only), a launch per
-  // eight layers
+  // ten layers
   for (int l0 = 0; l0 < N; l0 += kTrainJobsPerLaunch / 6) {
     TrainAapJobs jobs{};
     for (int l = l0; l < std::min(N, l0 + kTrainJobsPerLaunch / 6); ++l)
@@ -256,7 +256,7 @@ aecct_status aecct_train_grad(const aecct_trainer *tr, const aecct_train_params 
                                        gam + 6 * l + k, sc + 6 * l + k};
     AECCT_TRY(train_aap(jobs, T.aap_eps, s));
   }
-  for (int l0 = 0; l0 < N; l0 += kTrainJobsPerLaunch / 12) {   // both layouts of every matrix, a launch per four layers
+  for (int l0 = 0; l0 < N; l0 += kTrainJobsPerLaunch / 12) {   // both layouts of every matrix, a launch per five layers
     TernPackJobs pj{};
     for (int l = l0; l < std::min(N, l0 + kTrainJobsPerLaunch / 12); ++l)
       for (int k = 0; k < 6; ++k) {
@@ -377,7 +377,7 @@ aecct_status aecct_train_grad(const aecct_trainer *tr, const aecct_train_params 
     AECCT_TRY(train_weight_grads(d, dw, T.cu_count, part, (int64_t)PF, s));
   }
   // the straight-through Eq. 1 gradients of every matrix from its G = Xh^T dY (nothing in the
-  // backward reads G once it is formed), a launch per eight layers
+  // backward reads G once it is formed), a launch per ten layers
   for (int l0 = 0; l0 < N; l0 += kTrainJobsPerLaunch / 6) {
     TrainDeltaJobs dj{};
     for (int l = l0; l < std::min(N, l0 + kTrainJobsPerLaunch / 6); ++l)
