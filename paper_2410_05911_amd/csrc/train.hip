@@ -661,7 +661,9 @@ __global__ __launch_bounds__(kThreads) void k_gemm_reduce(GemmF32 g, int splits)
 // k_train_block is the inference path's token block with the backward's inputs written on the way.  The
 // separate kernels it stands for (quantise O, output map, LayerNorm, first map, ReLU and quantise,
 // second map, LayerNorm) passed every activation through memory in fp32 and wrote the dequantised
-// codes as fp32: LDPC(256,128), 256 words, 440 us a layer; this one moves 3 KB a token.
+// codes as fp32: LDPC(256,128), 256 words, 440 us a layer; this one moves 3 KB a token and takes 93 us (57 at
+// the copy's rate).  Strips go out wavefront-major, so that a batch of fewer strips than the card has
+// wavefronts spreads over every compute unit (BCH(31,16), 128 words: step 0.42 -> 0.40 ms).
 // ------------------------------------------------------------------------------------------
 constexpr int kTbWaves = 8;
 
@@ -701,7 +703,7 @@ __global__ __launch_bounds__(kTbWaves * 64) void k_train_qkv(TrainQkv p) {
   __syncthreads();
   const float sq[3] = {*p.s[0], *p.s[1], *p.s[2]};
   const int64_t nstrips = (p.rows + 15) / 16, stride = (int64_t)gridDim.x * kTbWaves;
-  for (int64_t strip = (int64_t)blockIdx.x * kTbWaves + wave; strip < nstrips; strip += stride) {
+  for (int64_t strip = (int64_t)wave * gridDim.x + blockIdx.x; strip < nstrips; strip += stride) {
     const int64_t tok = strip * 16 + c, tl = tok < p.rows ? tok : p.rows - 1;
     long x[S];
 #pragma unroll
@@ -768,7 +770,7 @@ __global__ __launch_bounds__(kTbWaves * 64) void k_train_block(TrainBlock p) {
   const uint64_t *f1l = (const uint64_t *)(smem + of1), *f2l = (const uint64_t *)(smem + of2);
   const float *vl = (const float *)(smem + ov);       // vl[k D + 16 t + i]: vector k, feature 16 t + 4 g + i
   const int64_t nstrips = (p.rows + 15) / 16, stride = (int64_t)gridDim.x * kTbWaves;
-  for (int64_t strip = (int64_t)blockIdx.x * kTbWaves + wave; strip < nstrips; strip += stride) {
+  for (int64_t strip = (int64_t)wave * gridDim.x + blockIdx.x; strip < nstrips; strip += stride) {
     const int64_t tok = strip * 16 + c;
     const bool ok = tok < p.rows;
     const int64_t tl = ok ? tok : p.rows - 1;          // padding columns: a copy, never stored
@@ -925,8 +927,8 @@ __global__ __launch_bounds__(kTbWaves * 64) void k_train_block(TrainBlock p) {
 // one selector byte each and become bf16 by byte permutes, eight per eight entries, behind the three
 // MFMAs they feed; as bf16 they would not fit, and from the L2 their 18 d^2 bytes a strip were what
 // k_gemm_tern spent most of its time on.  Separate kernels passed dX1, dR and dG through memory twice
-// more and read X-hat twice (LDPC(256,128), 256 words: 385 us a layer against 512 MB of inputs and outputs,
-// 100 us at the copy's rate).
+// more and read X-hat twice (LDPC(256,128), 256 words: 385 us a layer; this one 134, its 512 MB of inputs and
+// outputs 98 at the copy's rate).
 // ------------------------------------------------------------------------------------------
 template <int D>
 constexpr size_t bwd_lds() { return (size_t)9 * D * D + (size_t)2 * D * 4; }
@@ -967,7 +969,7 @@ __global__ __launch_bounds__(kTbWaves * 64) void k_train_bwd(TrainBwd p) {
   // column sums over this wavefront's tokens: lane c of a row of 16 keeps the features v with v mod 16 = c
   float cs[4][NC] = {};
   const int64_t nstrips = (p.rows + 15) / 16, stride = (int64_t)gridDim.x * kTbWaves;
-  for (int64_t strip = (int64_t)blockIdx.x * kTbWaves + wave; strip < nstrips; strip += stride) {
+  for (int64_t strip = (int64_t)wave * gridDim.x + blockIdx.x; strip < nstrips; strip += stride) {
     const int64_t tok = strip * 16 + c;
     const bool ok = tok < p.rows;
     const int64_t tl = ok ? tok : p.rows - 1;   // padding columns: a copy, never stored or summed
@@ -1392,13 +1394,12 @@ __global__ __launch_bounds__(kThreads) void k_attn_bwd_kv(AttnT p) {
 
 // ------------------------------------------------------------------------------------------
 // The same attention with what a row gathers in LDS: one block per word and 16-dimension head group
-// (16 / d_h heads), one lane per (row, head) of it.  The keys and values of the group (for the key and value
+// (16 / d_h heads), a lane or several per (row, head) of it.  The keys and values of the group (for the key and value
 // gradients: the queries and output gradients) sit in 144-byte rows, 16 different 16-byte bank groups
 // apart.  A pair costs its 128 bytes of LDS reads and about 50 multiply-adds instead of two gathers from
 // the L2 in a chain (training steps: LDPC(256,128), 256 words 12.20 -> 11.26 ms, with the blocks of a word
 // on one XCD 10.55 ms; BCH(31,16), 128 words 0.81 -> 0.66 ms); what binds is the one read of Q | K | V, O
-// and dO and the one write of the results, in 64-byte pieces.  Sums run over a row's list in
-// the same order as above.
+// and dO and the one write of the results, in 64-byte pieces.
 // ------------------------------------------------------------------------------------------
 constexpr int kAlRow = 36;   // floats per LDS row: two 16-float halves and padding
 
@@ -1440,9 +1441,33 @@ __device__ __forceinline__ void attn_word_group(const AttnT &p, int G, int64_t &
   }
 }
 
+// Lanes per row: a row of a short code is a chain of up to 28 dependent steps on a block of three
+// wavefronts, so its list goes round robin over four adjacent lanes at d_h = 4 and two at d_h = 8 (the
+// pieces' sums combined at the end); with 16-dimension heads the rows alone fill the block.  Steps:
+// BCH(31,16), 128 words 0.49 -> 0.42 ms, LDPC(128,64), 125 words 0.91 -> 0.88.
+template <int DH>
+constexpr int attn_split() { return 16 / DH; }
+// v of the row's next lane (o = 1) or of its other pair (o = 2)
+template <int O>
+__device__ __forceinline__ float quad_other(float v) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), O == 1 ? 0xB1 : 0x4E, 0xf, 0xf, true));
+}
+template <int SP>
+__device__ __forceinline__ float row_lanes_sum(float v) {
+  if constexpr (SP >= 2) v += quad_other<1>(v);
+  if constexpr (SP >= 4) v += quad_other<2>(v);
+  return v;
+}
+template <int SP>
+__device__ __forceinline__ float row_lanes_max(float v) {
+  if constexpr (SP >= 2) v = fmaxf(v, quad_other<1>(v));
+  if constexpr (SP >= 4) v = fmaxf(v, quad_other<2>(v));
+  return v;
+}
+
 template <int DH>
 __global__ __launch_bounds__(1024) void k_attn_fwd_lds(AttnT p) {
-  constexpr int HPG = 16 / DH;
+  constexpr int HPG = 16 / DH, SP = attn_split<DH>();
   extern __shared__ __attribute__((aligned(16))) float sm_[];
   const int d = p.d, G = d / 16, ld = 3 * d, L = p.L;
   int64_t w;
@@ -1452,17 +1477,18 @@ __global__ __launch_bounds__(1024) void k_attn_fwd_lds(AttnT p) {
   attn_stage(base + d, ld, base + 2 * d, ld, L, sm_);
   __syncthreads();
   const float kappa = 1.0f / sqrtf((float)DH);
-  for (int r = threadIdx.x; r < L * HPG; r += blockDim.x) {
+  const int part = threadIdx.x % SP;
+  for (int r = threadIdx.x / SP; r < L * HPG; r += blockDim.x / SP) {
     const int hh = r / L, i = r - hh * L, h = hg * HPG + hh;
     const int32_t *ptr = h < p.hf ? p.m1_ptr : p.m2_ptr, *idx = h < p.hf ? p.m1_idx : p.m2_idx;
     const float *kb = sm_ + hh * DH;
     float q[DH], k[DH], v[DH];
     attn_vec<DH>(q, base + (int64_t)i * ld + hh * DH);
-    const int beg = ptr[i], end = ptr[i + 1];
+    const int beg = ptr[i] + part, end = ptr[i + 1];
     float mu = -INFINITY, S = 0.0f, acc[DH] = {};
     int j = beg < end ? idx[beg] : 0;
-    for (int e = beg; e < end; ++e) {
-      const int jn = e + 1 < end ? idx[e + 1] : 0;
+    for (int e = beg; e < end; e += SP) {
+      const int jn = e + SP < end ? idx[e + SP] : 0;
       attn_vec<DH>(k, kb + j * kAlRow);
       attn_vec<DH>(v, kb + j * kAlRow + 16);
       const float s = dot_dh<DH>(q, k) * kappa;
@@ -1479,16 +1505,25 @@ __global__ __launch_bounds__(1024) void k_attn_fwd_lds(AttnT p) {
       for (int t = 0; t < DH; ++t) acc[t] = fmaf(pe, v[t], acc[t]);
       j = jn;
     }
+    if constexpr (SP > 1) {   // the row's pieces on its largest score (a list is never empty)
+      const float top = row_lanes_max<SP>(mu), c = expf(mu - top);   // 0 in a lane without an entry
+      mu = top;
+      S = row_lanes_sum<SP>(S * c);
 #pragma unroll
-    for (int t = 0; t < DH; ++t) acc[t] /= S;
-    attn_put<DH>(p.o + (w * L + i) * d + h * DH, acc);
-    p.lse[(w * L + i) * p.heads + h] = mu + logf(S);
+      for (int t = 0; t < DH; ++t) acc[t] = row_lanes_sum<SP>(acc[t] * c);
+    }
+    if (part == 0) {
+#pragma unroll
+      for (int t = 0; t < DH; ++t) acc[t] /= S;
+      attn_put<DH>(p.o + (w * L + i) * d + h * DH, acc);
+      p.lse[(w * L + i) * p.heads + h] = mu + logf(S);
+    }
   }
 }
 
 template <int DH>
 __global__ __launch_bounds__(1024) void k_attn_bwd_lds(AttnT p) {
-  constexpr int HPG = 16 / DH;
+  constexpr int HPG = 16 / DH, SP = attn_split<DH>();
   extern __shared__ __attribute__((aligned(16))) float sm_[];
   const int d = p.d, G = d / 16, ld = 3 * d, L = p.L;
   float *ls = sm_ + (size_t)L * kAlRow, *Ds = ls + L * HPG;   // [HPG][L] log-sum-exp, dO . O
@@ -1498,10 +1533,11 @@ __global__ __launch_bounds__(1024) void k_attn_bwd_lds(AttnT p) {
   const float *base = p.qkv + w * L * ld + 16 * hg, *dob = p.dout + w * L * d + 16 * hg, *ob = p.o + w * L * d + 16 * hg;
   float *gb = p.dqkv + w * L * ld + 16 * hg;
   const float kappa = 1.0f / sqrtf((float)DH);
+  const int part = threadIdx.x % SP;
   // query gradients: each row over its keys and values
   attn_stage(base + d, ld, base + 2 * d, ld, L, sm_);
   __syncthreads();
-  for (int r = threadIdx.x; r < L * HPG; r += blockDim.x) {
+  for (int r = threadIdx.x / SP; r < L * HPG; r += blockDim.x / SP) {
     const int hh = r / L, i = r - hh * L, h = hg * HPG + hh;
     const int32_t *ptr = h < p.hf ? p.m1_ptr : p.m2_ptr, *idx = h < p.hf ? p.m1_idx : p.m2_idx;
     const float *kb = sm_ + hh * DH;
@@ -1510,12 +1546,14 @@ __global__ __launch_bounds__(1024) void k_attn_bwd_lds(AttnT p) {
     attn_vec<DH>(go, dob + (int64_t)i * d + hh * DH);
     attn_vec<DH>(v, ob + (int64_t)i * d + hh * DH);
     const float D = dot_dh<DH>(go, v), lse = p.lse[(w * L + i) * p.heads + h];
-    ls[hh * L + i] = lse;
-    Ds[hh * L + i] = D;
-    const int beg = ptr[i], end = ptr[i + 1];
+    if (part == 0) {
+      ls[hh * L + i] = lse;
+      Ds[hh * L + i] = D;
+    }
+    const int beg = ptr[i] + part, end = ptr[i + 1];
     int j = beg < end ? idx[beg] : 0;
-    for (int e = beg; e < end; ++e) {
-      const int jn = e + 1 < end ? idx[e + 1] : 0;
+    for (int e = beg; e < end; e += SP) {
+      const int jn = e + SP < end ? idx[e + SP] : 0;
       attn_vec<DH>(k, kb + j * kAlRow);
       attn_vec<DH>(v, kb + j * kAlRow + 16);
       const float pij = expf(dot_dh<DH>(q, k) * kappa - lse);
@@ -1524,23 +1562,25 @@ __global__ __launch_bounds__(1024) void k_attn_bwd_lds(AttnT p) {
       for (int t = 0; t < DH; ++t) dq[t] = fmaf(ds, k[t], dq[t]);
       j = jn;
     }
-    attn_put<DH>(gb + (int64_t)i * ld + hh * DH, dq);
+#pragma unroll
+    for (int t = 0; t < DH; ++t) dq[t] = row_lanes_sum<SP>(dq[t]);
+    if (part == 0) attn_put<DH>(gb + (int64_t)i * ld + hh * DH, dq);
   }
   __syncthreads();
   // key and value gradients: each key row over the rows whose list holds it (symmetric masks)
   attn_stage(base, ld, dob, d, L, sm_);
   __syncthreads();
-  for (int r = threadIdx.x; r < L * HPG; r += blockDim.x) {
+  for (int r = threadIdx.x / SP; r < L * HPG; r += blockDim.x / SP) {
     const int hh = r / L, j = r - hh * L, h = hg * HPG + hh;
     const int32_t *ptr = h < p.hf ? p.m1_ptr : p.m2_ptr, *idx = h < p.hf ? p.m1_idx : p.m2_idx;
     const float *qb = sm_ + hh * DH;
     float k[DH], v[DH], q[DH], go[DH], dk[DH] = {}, dv[DH] = {};
     attn_vec<DH>(k, base + (int64_t)j * ld + d + hh * DH);
     attn_vec<DH>(v, base + (int64_t)j * ld + 2 * d + hh * DH);
-    const int beg = ptr[j], end = ptr[j + 1];
+    const int beg = ptr[j] + part, end = ptr[j + 1];
     int i = beg < end ? idx[beg] : 0;
-    for (int e = beg; e < end; ++e) {
-      const int in = e + 1 < end ? idx[e + 1] : 0;
+    for (int e = beg; e < end; e += SP) {
+      const int in = e + SP < end ? idx[e + SP] : 0;
       attn_vec<DH>(q, qb + i * kAlRow);
       attn_vec<DH>(go, qb + i * kAlRow + 16);
       const float pij = expf(dot_dh<DH>(q, k) * kappa - ls[hh * L + i]);
@@ -1552,8 +1592,15 @@ __global__ __launch_bounds__(1024) void k_attn_bwd_lds(AttnT p) {
       }
       i = in;
     }
-    attn_put<DH>(gb + (int64_t)j * ld + d + hh * DH, dk);
-    attn_put<DH>(gb + (int64_t)j * ld + 2 * d + hh * DH, dv);
+#pragma unroll
+    for (int t = 0; t < DH; ++t) {
+      dk[t] = row_lanes_sum<SP>(dk[t]);
+      dv[t] = row_lanes_sum<SP>(dv[t]);
+    }
+    if (part == 0) {
+      attn_put<DH>(gb + (int64_t)j * ld + d + hh * DH, dk);
+      attn_put<DH>(gb + (int64_t)j * ld + 2 * d + hh * DH, dv);
+    }
   }
 }
 
@@ -1850,7 +1897,7 @@ namespace {
 template <int D>
 hipError_t qkv_go(const TrainQkv &a, int cu_count, size_t lds_max, hipStream_t s) {
   constexpr size_t lds = train::qkv_lds<D>();
-  const int64_t groups = ((a.rows + 15) / 16 + train::kTbWaves - 1) / train::kTbWaves;
+  const int64_t strips = (a.rows + 15) / 16, groups = std::max<int64_t>((strips + train::kTbWaves - 1) / train::kTbWaves, std::min<int64_t>(strips, cu_count));
   const int64_t per_cu = std::max<int64_t>(1, std::min<int64_t>(2, (int64_t)(lds_max / lds)));
   hipLaunchKernelGGL(train::k_train_qkv<D>, dim3((unsigned)std::min<int64_t>(groups, cu_count * per_cu)),
                      dim3(train::kTbWaves * 64), lds, s, a);
@@ -1859,7 +1906,7 @@ hipError_t qkv_go(const TrainQkv &a, int cu_count, size_t lds_max, hipStream_t s
 template <int D>
 hipError_t block_go(const TrainBlock &a, int cu_count, size_t lds_max, hipStream_t s) {
   constexpr size_t lds = train::block_lds<D>();
-  const int64_t groups = ((a.rows + 15) / 16 + train::kTbWaves - 1) / train::kTbWaves;
+  const int64_t strips = (a.rows + 15) / 16, groups = std::max<int64_t>((strips + train::kTbWaves - 1) / train::kTbWaves, std::min<int64_t>(strips, cu_count));
   const int64_t per_cu = std::max<int64_t>(1, std::min<int64_t>(2, (int64_t)(lds_max / lds)));
   hipLaunchKernelGGL(train::k_train_block<D>, dim3((unsigned)std::min<int64_t>(groups, cu_count * per_cu)),
                      dim3(train::kTbWaves * 64), lds, s, a);
@@ -1892,7 +1939,7 @@ hipError_t bwd_go(const TrainBwd &a, int blocks, hipStream_t s) {
 }  // namespace
 
 int train_bwd_blocks(int64_t rows, int cu_count) {
-  return (int)std::max<int64_t>(1, std::min<int64_t>(((rows + 15) / 16 + train::kTbWaves - 1) / train::kTbWaves, cu_count));
+  return (int)std::max<int64_t>(1, std::min<int64_t>((rows + 15) / 16, cu_count));
 }
 
 hipError_t train_bwd(int d, const TrainBwd &a, int cu_count, hipStream_t s) {
@@ -1976,8 +2023,7 @@ static hipError_t attention_go(bool backward, const TrainAttn &p, size_t lds_max
   const size_t lds = train::attn_lds_bytes<DH>(p.L);
   const int64_t blocks = p.rows / p.L * (p.d / 16);
   if (lds <= lds_max && p.d % 16 == 0 && blocks <= INT32_MAX) {
-    // a lane per row and head of the group, up to 1024
-    const unsigned threads = (unsigned)std::min(1024, (p.L * (16 / DH) + 63) / 64 * 64);
+    const unsigned threads = (unsigned)std::min(1024, (p.L * (16 / DH) * train::attn_split<DH>() + 63) / 64 * 64);
     if (!backward) hipLaunchKernelGGL(train::k_attn_fwd_lds<DH>, dim3((unsigned)blocks), dim3(threads), lds, s, p);
     else hipLaunchKernelGGL(train::k_attn_bwd_lds<DH>, dim3((unsigned)blocks), dim3(threads), lds, s, p);
     return hipGetLastError();
