@@ -91,7 +91,7 @@ TrainWs train_ws(const aecct_trainer &T, int64_t batch) {
   w.part_floats = std::max<size_t>(
       w.part_floats, (size_t)aecct::train_dw_splits((int)d, (int64_t)R, kDwTiles, T.cu_count) * kDwTiles * d * (d + 1));
   w.part = take(w.part_floats);
-  w.total_bytes = off;
+  w.total_bytes = off + kAlign;   // the regions start at the workspace's first multiple of kAlign
   return w;
 }
 
@@ -210,7 +210,7 @@ aecct_status aecct_train_grad(const aecct_trainer *tr, const aecct_train_params 
 
   const aecct_trainer &T = *tr;
   hipStream_t s = (hipStream_t)stream;
-  float *ws = (float *)workspace;
+  float *ws = (float *)align_up((size_t)(uintptr_t)workspace);
   const int64_t R = batch * T.L, B = batch;
   const int d = T.d, dff = T.dff, N = T.N;
   const int64_t K_in[6] = {d, d, d, d, d, dff}, K_out[6] = {d, d, d, d, dff, d};

@@ -59,3 +59,20 @@ def test_train_step_at_awkward_sizes(n, d, layers, batch, attention, pos):
     assert abs(loss.item() - loss64) <= 1e-3 * abs(loss64)
     assert np.median(list(errs.values())) <= 1e-3 and max(errs.values()) <= 5e-2, errs
     tr.close()
+
+
+def test_train_step_takes_any_workspace_alignment():
+    """The step reads its workspace in 16-byte pieces; a workspace at any 4-byte boundary gives the same bits."""
+    import paper_2410_05911_amd as P
+    H = hamming_7_4()
+    p = _to_dev(random_qat_params(7, 3, 64, 2, seed=5))
+    y = _dev(1.0 + 0.7 * np.random.default_rng(5).standard_normal((4, 7)))
+    tr = P.Trainer(H, 64, 2)
+    loss, g = tr.grad(p, y)
+    for shift in (4, 20, 128):
+        tr._ws = torch.empty(tr.workspace_size(4) + shift, dtype=torch.uint8, device="cuda")[shift:]
+        loss2, g2 = tr.grad(p, y)
+        torch.cuda.synchronize()
+        assert torch.equal(loss, loss2) and all(torch.equal(g["w"][k], g2["w"][k]) for k in KINDS)
+        assert torch.equal(g["embed"], g2["embed"]) and torch.equal(g["delta"], g2["delta"])
+    tr.close()
