@@ -2,9 +2,9 @@
 // in which the encoder's in-block linear maps are AAP linear layers (Section 4.1) over latent
 // fp32 weights.  Forward with Eq. 1 ternarisation of the current weights and Eq. 2 absmax int8
 // activations (both passing gradients straight through their rounding), the cross entropy of the
-// multiplicative noise, and the backward pass to every parameter.  fp32 throughout; every
-// reduction runs in a fixed order (split partial sums reduced in index order), so a step is
-// deterministic.
+// multiplicative noise, and the backward pass to every parameter.  fp32 throughout, except that a map's
+// input is held as what Eq. 2 makes of it, int8 codes and a row scale; every reduction runs in a fixed
+// order (split partial sums reduced in index order), so a step is deterministic.
 //
 // Layouts: activations row-major [rows][features] with row b * L + r for token r of word b;
 // weights [in][out] as in the inference ABI.
