@@ -96,17 +96,18 @@ __device__ __forceinline__ uint32_t quant_bits(float x, float inv) {
 }
 __device__ __forceinline__ int8_t quant_code(float x, float inv) { return (int8_t)quant_bits(x, inv); }
 
-// Eq. 2 codes of four ReLU outputs from the code patterns of the pre-activations: the low 16
-// bits of a quant_bits pattern are the code as an int16 (1.5 * 2^23 + c for |c| <= 127), so
-// max(code, 0) on two codes at a time (v_pk_max_i16) equals the code of max(x, 0) (inv >= 0, and
-// rounding is monotone); returns the four codes as bytes 0..3.
-typedef short short2_t __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ uint32_t pack4_relu(uint32_t b0, uint32_t b1, uint32_t b2, uint32_t b3) {
-  short2_t lo = __builtin_bit_cast(short2_t, __builtin_amdgcn_perm(b1, b0, 0x05040100u));
-  short2_t hi = __builtin_bit_cast(short2_t, __builtin_amdgcn_perm(b3, b2, 0x05040100u));
-  lo = __builtin_elementwise_max(lo, (short2_t){0, 0});
-  hi = __builtin_elementwise_max(hi, (short2_t){0, 0});
-  return __builtin_amdgcn_perm(__builtin_bit_cast(uint32_t, hi), __builtin_bit_cast(uint32_t, lo), 0x06040200u);
+// Byte 0 of four Eq. 2 code patterns into one dword (byte i from b[i]).
+__device__ __forceinline__ uint32_t pack4(uint32_t b0, uint32_t b1, uint32_t b2, uint32_t b3) {
+  const uint32_t lo = __builtin_amdgcn_perm(b1, b0, 0x0c0c0400u);
+  const uint32_t hi = __builtin_amdgcn_perm(b3, b2, 0x0c0c0400u);
+  return __builtin_amdgcn_perm(hi, lo, 0x05040100u);
+}
+// Eq. 2 codes of four ReLU outputs max(x, 0) as bytes 0..3, alpha (behind inv) the maximum of the ReLU outputs
+// only.  The ReLU comes before the code: nothing bounds x inv from below (a row with one barely positive unit has
+// pre-activations of many thousand alphas), and quant_bits is a code's bits for |x inv| < 2^22 at most.
+__device__ __forceinline__ uint32_t relu_codes4(float x0, float x1, float x2, float x3, float inv) {
+  return pack4(quant_bits(fmaxf(x0, 0.0f), inv), quant_bits(fmaxf(x1, 0.0f), inv), quant_bits(fmaxf(x2, 0.0f), inv),
+               quant_bits(fmaxf(x3, 0.0f), inv));
 }
 
 // 2^x for the base-2 attention softmax: clamp to [-125, 128] (the result stays a normal

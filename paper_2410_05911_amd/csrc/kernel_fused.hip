@@ -92,13 +92,6 @@ __device__ __forceinline__ float token_max_abs(const float (&x)[8]) {
   return cross_max_nonneg(a);
 }
 
-// Byte 0 of four Eq. 2 code patterns into one dword (byte i from b[i]).
-__device__ __forceinline__ uint32_t pack4(uint32_t b0, uint32_t b1, uint32_t b2, uint32_t b3) {
-  const uint32_t lo = __builtin_amdgcn_perm(b1, b0, 0x0c0c0400u);
-  const uint32_t hi = __builtin_amdgcn_perm(b3, b2, 0x0c0c0400u);
-  return __builtin_amdgcn_perm(hi, lo, 0x05040100u);
-}
-
 // Eq. 2 over a token's 32 values held 8 per lane; returns alpha, writes the 8 codes
 // (value v in byte v) to two dwords.
 __device__ __forceinline__ float quant8(const float (&x)[8], uint32_t &lo, uint32_t &hi) {
@@ -433,7 +426,7 @@ __global__ __launch_bounds__(WAVES * 64, 1) void k_fused_decode(FusedArgs p) {
 #pragma unroll
         for (int o = 0; o < 8; ++o) acc[o] = mfma_i8_16x16x32((long)F[(fz::F_FF1 + o) * 64], bop, v4i{0, 0, 0, 0});
         const float sc = al[t] * sq_1;
-        // F1 pre-activations; the ReLU is applied to the maximum (max(0, F...)) and to the codes
+        // F1 pre-activations; the ReLU is applied to the maximum (max(0, F...)) and before the codes
         float G[8][4];
         float amax = 0.0f;
 #pragma unroll
@@ -447,9 +440,7 @@ __global__ __launch_bounds__(WAVES * 64, 1) void k_fused_decode(FusedArgs p) {
         const float inv = inv127(amax);
         uint32_t gb[8];
 #pragma unroll
-        for (int o = 0; o < 8; ++o)
-          gb[o] = pack4_relu(quant_bits(G[o][0], inv), quant_bits(G[o][1], inv), quant_bits(G[o][2], inv),
-                             quant_bits(G[o][3], inv));
+        for (int o = 0; o < 8; ++o) gb[o] = relu_codes4(G[o][0], G[o][1], G[o][2], G[o][3], inv);
         const auto gop = [&](int s) { return as_long(gb[2 * s], gb[2 * s + 1]); };
         const v4i b0 = mfma_i8_steps<4>([&](int s) { return (long)F[(fz::F_FF2 + s) * 64]; }, gop, v4i{0, 0, 0, 0});
         const v4i b1 = mfma_i8_steps<4>([&](int s) { return (long)F[(fz::F_FF2 + 4 + s) * 64]; }, gop, v4i{0, 0, 0, 0});

@@ -887,8 +887,7 @@ __global__ __launch_bounds__(kTbWaves * 64) void k_train_block(TrainBlock p) {
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
           const int o = 2 * (st + j) + h;
-          w[h] = pack4_relu(quant_bits(hid[o][0], invh), quant_bits(hid[o][1], invh), quant_bits(hid[o][2], invh),
-                            quant_bits(hid[o][3], invh));
+          w[h] = relu_codes4(hid[o][0], hid[o][1], hid[o][2], hid[o][3], invh);
           if (ok) *(uint32_t *)(p.gq + tok * 4 * D + 16 * o + 4 * g) = w[h];
         }
         gb[j] = (long)(((uint64_t)w[1] << 32) | w[0]);
