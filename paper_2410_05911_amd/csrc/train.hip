@@ -528,16 +528,38 @@ __device__ __forceinline__ bf16x8 bf16_hi8(const float (&v)[8]) {
   return __builtin_bit_cast(bf16x8, w);
 }
 
-// the three bf16 parts of eight fp32 values as MFMA operands
+// the three bf16 parts of eight fp32 values as MFMA operands.  INF: an infinity is its leading part alone, so that
+// its products are what the fp32 product gives (infinite, or NaN with a zero); otherwise Inf - Inf makes its
+// other parts, and every sum it enters, NaN.  The weight gradients take it, and the input gradients at d = 32:
+// 0.2 % of a step at d = 128, 0.5 % at 32 and 64.
+template <bool INF>
 __device__ __forceinline__ void split_bf16x3(const float4 &x0, const float4 &x1, bf16x8 &ph, bf16x8 &pm, bf16x8 &pl) {
   const float a[8] = {x0.x, x0.y, x0.z, x0.w, x1.x, x1.y, x1.z, x1.w};
   float hi[8], mid[8], lo[8];
-#pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    hi[e] = __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, a[e]) & 0xFFFF0000u);
-    const float rm = a[e] - hi[e];
+  const auto rest = [&](int e, float rm) {
     mid[e] = __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, rm) & 0xFFFF0000u);
     lo[e] = rm - mid[e];
+  };
+  if constexpr (INF) {
+    float rm[8], top = 0.0f;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      hi[e] = __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, a[e]) & 0xFFFF0000u);
+      rm[e] = a[e] - hi[e];
+      top = fmaxf(top, fabsf(a[e]));
+    }
+    if (__builtin_expect(__any(top == INFINITY), 0)) {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) rm[e] = a[e] == hi[e] ? 0.0f : rm[e];
+    }
+#pragma unroll
+    for (int e = 0; e < 8; ++e) rest(e, rm[e]);
+  } else {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      hi[e] = __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, a[e]) & 0xFFFF0000u);
+      rest(e, a[e] - hi[e]);
+    }
   }
   ph = bf16_hi8(hi);
   pm = bf16_hi8(mid);
@@ -586,7 +608,7 @@ __global__ __launch_bounds__(kThreads) void k_gemm_tern(GemmTern g) {
       if (kt >= KT) break;
       if (kt + S - 1 < KT) issue(kt + S - 1, a[(s + S - 1) % S], b[(s + S - 1) % S]);
       bf16x8 ph, pm, pl;
-      split_bf16x3(a[s][0], a[s][1], ph, pm, pl);
+      split_bf16x3<NJ == 2>(a[s][0], a[s][1], ph, pm, pl);
 #pragma unroll
       for (int j = 0; j < NJ; ++j) {
         const bf16x8 bb = __builtin_bit_cast(bf16x8, b[s][j]);
@@ -1009,8 +1031,8 @@ __global__ __launch_bounds__(kTbWaves * 64) void k_train_bwd(TrainBwd p) {
     auto parts = [&](const float (&x)[V], bf16x8 (&b)[S][3]) {
 #pragma unroll
       for (int s = 0; s < S; ++s)
-        split_bf16x3(make_float4(x[8 * s], x[8 * s + 1], x[8 * s + 2], x[8 * s + 3]),
-                     make_float4(x[8 * s + 4], x[8 * s + 5], x[8 * s + 6], x[8 * s + 7]), b[s][0], b[s][1], b[s][2]);
+        split_bf16x3<D == 32>(make_float4(x[8 * s], x[8 * s + 1], x[8 * s + 2], x[8 * s + 3]),
+                              make_float4(x[8 * s + 4], x[8 * s + 5], x[8 * s + 6], x[8 * s + 7]), b[s][0], b[s][1], b[s][2]);
     };
     auto mac = [&](uint64_t w, const bf16x8 (&b)[3], f32x4 acc) {
       const bf16x8 a = sel_bf16(w);
@@ -1046,7 +1068,7 @@ __global__ __launch_bounds__(kTbWaves * 64) void k_train_bwd(TrainBwd p) {
         if (ok) *(float4 *)(p.dg + tok * 4 * D + 16 * (2 * st + k) + 4 * g) = h[k];
       }
       bf16x8 hb[3];
-      split_bf16x3(h[0], h[1], hb[0], hb[1], hb[2]);
+      split_bf16x3<D == 32>(h[0], h[1], hb[0], hb[1], hb[2]);
 #pragma unroll
       for (int o = 0; o < TO; ++o) {
         acc2[o] = mac(f1l[(o * SH + st) * 64], hb, acc2[o]);
@@ -1155,7 +1177,7 @@ __global__ __launch_bounds__(kThreads, 2) void k_train_dw(TrainDwJobs J) {
       }
       As[rg][2 * cp + f] = __builtin_bit_cast(uint4, bf16_hi8(a));
       bf16x8 ph, pm, pl;
-      split_bf16x3(make_float4(v[0], v[1], v[2], v[3]), make_float4(v[4], v[5], v[6], v[7]), ph, pm, pl);
+      split_bf16x3<true>(make_float4(v[0], v[1], v[2], v[3]), make_float4(v[4], v[5], v[6], v[7]), ph, pm, pl);
       Bs[0][rg][2 * cp + f] = __builtin_bit_cast(uint4, ph);
       Bs[1][rg][2 * cp + f] = __builtin_bit_cast(uint4, pm);
       Bs[2][rg][2 * cp + f] = __builtin_bit_cast(uint4, pl);
