@@ -11,6 +11,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cfloat>
 #include <cmath>
 
 #include "aecct_internal.h"
@@ -1273,8 +1274,10 @@ __global__ __launch_bounds__(kThreads) void k_train_dw_reduce(TrainDwJobs J) {
 // the row's neighbour list (first ring for heads below h_f, else the second-ring list, which
 // holds the union of both rings under CASA); natural-base softmax of q.k / sqrt(d_h) with the
 // maximum subtracted.  Forward stores O and the row's log-sum-exp; the backward recomputes
-// p_ij = exp(s_ij - lse_i).  The masks are symmetric, so the key and value gradients are gathered
-// per key row over its own list, without atomics.
+// p_ij = exp(s_ij - lse_i).  The running maximum starts at the lowest finite value: started at -Inf, a first
+// key (of a row, or of one of the lanes that share it) whose score is -Inf would give exp(-Inf + Inf) = NaN where its
+// weight is 0.  The masks are symmetric, so the key and value gradients are gathered per key row over its
+// own list, without atomics.
 // ------------------------------------------------------------------------------------------
 using AttnT = TrainAttn;
 
@@ -1322,7 +1325,7 @@ __global__ __launch_bounds__(kThreads) void k_attn_fwd(AttnT p) {
   // one pass with a running maximum: when a score raises it, the sum and the accumulated values so
   // far are rescaled by exp(old - new) (each key read once instead of once for the maximum and once
   // for the weights)
-  float mu = -INFINITY, S = 0.0f, acc[DH] = {};
+  float mu = -FLT_MAX, S = 0.0f, acc[DH] = {};
   for (int e = ptr[i]; e < ptr[i + 1]; ++e) {
     const int64_t j = base + idx[e];
     const float s = dot_dh<DH>(q, p.qkv + j * ld + d + h * DH) * kappa;
@@ -1506,7 +1509,7 @@ __global__ __launch_bounds__(1024) void k_attn_fwd_lds(AttnT p) {
     float q[DH], k[DH], v[DH];
     attn_vec<DH>(q, base + (int64_t)i * ld + hh * DH);
     const int beg = ptr[i] + part, end = ptr[i + 1];
-    float mu = -INFINITY, S = 0.0f, acc[DH] = {};
+    float mu = -FLT_MAX, S = 0.0f, acc[DH] = {};
     int j = beg < end ? idx[beg] : 0;
     for (int e = beg; e < end; e += SP) {
       const int jn = e + SP < end ? idx[e + SP] : 0;
