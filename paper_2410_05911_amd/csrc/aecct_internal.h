@@ -301,7 +301,7 @@ hipError_t train_gemm(bool ta, bool tb, const float *A, int64_t lda, const float
                       int64_t M, int64_t N, int64_t K, const float *scale, const float *bias, bool accumulate,
                       float *part, int64_t part_floats, int cu_count, hipStream_t s);
 // forward (o, lse) or backward (dqkv from dout, o and lse; Dv scratch)
-hipError_t train_attention(bool backward, int dh, const TrainAttn &a, size_t lds_max, hipStream_t s);
+hipError_t train_attention(bool backward, int dh, const TrainAttn &a, int cu_count, size_t lds_max, hipStream_t s);
 // out[c] = sum_r A[r][c] (w[r] if w), rows of A lda apart
 hipError_t train_colsum(const float *A, int64_t lda, const float *w, int64_t rows, int C, float *out, float *part,
                         int64_t part_floats, hipStream_t s);

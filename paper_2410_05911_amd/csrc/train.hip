@@ -2042,17 +2042,30 @@ hipError_t train_weight_grads(int d, TrainDwJobs &J, int cu_count, float *part, 
   return hipGetLastError();
 }
 
+// The LDS form where a word fits (930, 1024 and 1077 tokens at d_h = 4, 8 and 16 with 160 KB) and one block per
+// word and head group is no longer than the whole card's gathers.  A block's time goes with the tokens it stages and
+// the 16 / d_h rows of each, so short words always take it; longer ones once there is a block for every second
+// compute unit, but not at d_h = 4 and d > 32, where the gathers of a row's many heads share cache lines.  Steps of
+// two layers, gathers / LDS, us: 384 tokens, d = 64, d_h = 4, 1 word 249 / 265, 32 words 342 / 333; 900 tokens,
+// d = 32, d_h = 4, 1 word 222 / 337, 64 words 528 / 528, 160 words 1188 / 1091; d = 64, d_h = 4, 160 words 1584 / 1778;
+// d = 64, d_h = 8, 4 words 306 / 350, 64 words 739 / 677; d = 128, d_h = 16, 1074 tokens, 4 words 476 / 501, 64
+// words 1728 / 1396.
 template <int DH>
-static hipError_t attention_go(bool backward, const TrainAttn &p, size_t lds_max, hipStream_t s) {
+static bool attention_in_lds(const TrainAttn &p, int64_t blocks, int cu_count, size_t lds_max) {
+  if (train::attn_lds_bytes<DH>(p.L) > lds_max || p.d % 16 || blocks > INT32_MAX) return false;
+  return p.L * (1 + 16 / DH) <= 1920 || (2 * blocks >= cu_count && (DH > 4 || p.d == 32));
+}
+
+template <int DH>
+static hipError_t attention_go(bool backward, const TrainAttn &p, int cu_count, size_t lds_max, hipStream_t s) {
   const size_t lds = train::attn_lds_bytes<DH>(p.L);
   const int64_t blocks = p.rows / p.L * (p.d / 16);
-  if (lds <= lds_max && p.d % 16 == 0 && blocks <= INT32_MAX) {
+  if (attention_in_lds<DH>(p, blocks, cu_count, lds_max)) {
     const unsigned threads = (unsigned)std::min(1024, (p.L * (16 / DH) * train::attn_split<DH>() + 63) / 64 * 64);
     if (!backward) hipLaunchKernelGGL(train::k_attn_fwd_lds<DH>, dim3((unsigned)blocks), dim3(threads), lds, s, p);
     else hipLaunchKernelGGL(train::k_attn_bwd_lds<DH>, dim3((unsigned)blocks), dim3(threads), lds, s, p);
     return hipGetLastError();
   }
-  // words too long for LDS (more than about 1070 tokens): gathers from device memory
   const dim3 grid(blocks_for(p.rows * p.heads, train::kThreads));
   if (!backward) {
     hipLaunchKernelGGL(train::k_attn_fwd<DH>, grid, dim3(train::kThreads), 0, s, p);
@@ -2063,12 +2076,12 @@ static hipError_t attention_go(bool backward, const TrainAttn &p, size_t lds_max
   return hipGetLastError();
 }
 
-hipError_t train_attention(bool backward, int dh, const TrainAttn &p, size_t lds_max, hipStream_t s) {
+hipError_t train_attention(bool backward, int dh, const TrainAttn &p, int cu_count, size_t lds_max, hipStream_t s) {
   if (p.rows <= 0) return hipSuccess;
   switch (dh) {
-    case 4: return attention_go<4>(backward, p, lds_max, s);
-    case 8: return attention_go<8>(backward, p, lds_max, s);
-    case 16: return attention_go<16>(backward, p, lds_max, s);
+    case 4: return attention_go<4>(backward, p, cu_count, lds_max, s);
+    case 8: return attention_go<8>(backward, p, cu_count, lds_max, s);
+    case 16: return attention_go<16>(backward, p, cu_count, lds_max, s);
   }
   return hipErrorInvalidValue;
 }

@@ -284,7 +284,7 @@ aecct_status aecct_train_grad(const aecct_trainer *tr, const aecct_train_params 
     AECCT_TRY(train_qkv(d, qa, T.cu_count, T.lds_max, s));
     TrainAttn at{ws + q.qkv, R, T.L, d, T.heads, T.hf, T.m1_ptr, T.m1_idx, T.m2_ptr, T.m2_idx, ws + q.o, ws + q.lse,
                  nullptr, nullptr, nullptr};
-    AECCT_TRY(train_attention(false, T.dh, at, T.lds_max, s));
+    AECCT_TRY(train_attention(false, T.dh, at, T.cu_count, T.lds_max, s));
     TrainBlock tb{};
     tb.o = ws + q.o;
     tb.res = l ? ws + W.layer[l - 1].xn2 : X;
@@ -357,7 +357,7 @@ aecct_status aecct_train_grad(const aecct_trainer *tr, const aecct_train_params 
     // attention, then the query, key and value maps: one product over their packed gradient
     TrainAttn at{ws + q.qkv, R, T.L, d, T.heads, T.hf, T.m1_ptr, T.m1_idx, T.m2_ptr, T.m2_idx, ws + q.o, ws + q.lse,
                  dO, dQKV, ws + W.dv};
-    AECCT_TRY(train_attention(true, T.dh, at, T.lds_max, s));
+    AECCT_TRY(train_attention(true, T.dh, at, T.cu_count, T.lds_max, s));
     const void *fq[3] = {tpk(l, 0, true), tpk(l, 1, true), tpk(l, 2, true)};
     const float *sq[3] = {sc + 6 * l, sc + 6 * l + 1, sc + 6 * l + 2};
     AECCT_TRY(train_gemm_tern(dQKV, 3 * d, fq, 3, d, sq, dR1, dX, d, R, d, s));

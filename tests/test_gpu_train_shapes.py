@@ -34,22 +34,49 @@ KINDS = ("q", "k", "v", "o", "ff1", "ff2")
     (1024, 32, 1, 1, "hpsa", False),   # 1536 tokens: the attention's gathers from device memory (above 930,
     (1024, 64, 1, 1, "casa", False),   # 1024 and 1077 tokens at d_h = 4, 8 and 16)
     (1024, 128, 1, 1, "hpsa", True),
-    (620, 32, 1, 1, "hpsa", False),    # 930 tokens: the longest word in LDS at d_h = 4, several rows a lane
+    (620, 32, 1, 1, "hpsa", False),    # 930 tokens, one word: the gathers by their measured line
 ])
 def test_train_step_at_awkward_sizes(n, d, layers, batch, attention, pos):
+    _step_against_oracle(n, d, layers, batch, attention=attention, pos=pos)
+
+
+@pytest.mark.parametrize("n,d,heads,repeat", [
+    (256, 32, 8, 1),     # 384 tokens at d_h = 4: in LDS in any batch
+    (258, 32, 8, 1),     # 387: the gathers in small batches
+    (258, 32, 8, 21),    # 126 blocks (two a word): still
+    (258, 32, 8, 22),    # 132 blocks: LDS
+    (258, 64, 16, 11),   # 132 blocks at d = 64: the gathers
+    (620, 32, 8, 22),    # 930 tokens: the longest word in LDS at d_h = 4
+    (426, 64, 8, 1),     # 639 tokens at d_h = 8: LDS
+    (428, 64, 8, 1),     # 642: the gathers
+    (682, 64, 8, 11),    # 1023 tokens, 132 blocks: LDS, rows in four passes
+    (640, 128, 8, 1),    # 960 tokens at d_h = 16: LDS
+    (642, 128, 8, 1),    # 963: the gathers
+    (718, 128, 8, 6),    # 1077 tokens, 144 blocks: the longest word in LDS at d_h = 16, rows in two passes
+])
+def test_long_words_in_both_attention_forms(n, d, heads, repeat):
+    """Either side of each line between the two forms of the attention (on 256 compute units), three words repeated to
+    reach the batch: a mean over them, which the oracle takes once.  Words this long have a few codes that fp32
+    decides the other way in any batch; a flip shifts its rows by at most a code step, 1 / 127 of the row's maximum,
+    so the median error stays below 8e-3.  Rows left out of a last pass (5 % of the longest word's) or staged from a
+    wrong token would change it by far more."""
+    _step_against_oracle(n, d, 1, 3, heads=heads, repeat=repeat, median=8e-3)
+
+
+def _step_against_oracle(n, d, layers, batch, heads=8, attention="hpsa", pos=False, repeat=1, median=1e-3):
     import oracle.qat as Q
     import paper_2410_05911_amd as P
     H = hamming_7_4() if n == 7 else regular_ldpc_3_6(n, seed=1000 + n)
     m = H.shape[0]
-    print(f"[train] n {n} d {d} layers {layers} batch {batch} {attention}", flush=True)
+    print(f"[train] n {n} d {d} heads {heads} layers {layers} batch {batch} x {repeat} {attention}", flush=True)
     p = random_qat_params(n, m, d, layers, seed=n + d + layers)
     rng = np.random.default_rng(n + batch)
     if pos:
         p["pos"] = (0.5 * rng.standard_normal((n + m, d))).astype(np.float32)
     y = (1.0 + 0.7 * rng.standard_normal((batch, n))).astype(np.float32)
-    loss64, _, g64 = Q.forward_backward(H, p, y, None, heads=8, attention=attention)
-    tr = P.Trainer(H, d, layers, heads=8, attention=attention)
-    loss, g = tr.grad(_to_dev(p), _dev(y))
+    loss64, _, g64 = Q.forward_backward(H, p, y, None, heads=heads, attention=attention)
+    tr = P.Trainer(H, d, layers, heads=heads, attention=attention)
+    loss, g = tr.grad(_to_dev(p), _dev(np.tile(y, (repeat, 1))))
     torch.cuda.synchronize()
     errs = {"w_" + k: _rel(g["w"][k].cpu().numpy(), g64["w"][k]) for k in KINDS}
     errs.update({"b_" + k: _rel(g["b"][k].cpu().numpy(), g64["b"][k]) for k in KINDS if k != "k"})
@@ -57,7 +84,7 @@ def test_train_step_at_awkward_sizes(n, d, layers, batch, attention, pos):
         errs[k] = _rel(g[k].cpu().numpy(), g64[k])
     print(" ".join(f"{k}={v:.1e}" for k, v in sorted(errs.items())), flush=True)
     assert abs(loss.item() - loss64) <= 1e-3 * abs(loss64)
-    assert np.median(list(errs.values())) <= 1e-3 and max(errs.values()) <= 5e-2, errs
+    assert np.median(list(errs.values())) <= median and max(errs.values()) <= 5e-2, errs
     tr.close()
 
 
