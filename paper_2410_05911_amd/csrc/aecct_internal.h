@@ -295,11 +295,11 @@ struct TrainDwJobs {
 };
 int train_dw_splits(int d, int64_t rows, int tiles, int cu_count);   // at most; scratch: splits x tiles x d (d + 1) floats
 hipError_t train_weight_grads(int d, TrainDwJobs &jobs, int cu_count, float *part, int64_t part_floats, hipStream_t s);
-// C[M][N] = (accumulate ? C : 0) + scale (op(A) op(B)) + bias; ta: A stored [K][M]; tb: B stored [N][K].
+// C[M][N] = op(A) op(B) + bias (or null); ta: A stored [K][M]; tb: B stored [N][K]; not both.
 // part: scratch of part_floats floats for split reductions over K.
 hipError_t train_gemm(bool ta, bool tb, const float *A, int64_t lda, const float *B, int64_t ldb, float *C, int64_t ldc,
-                      int64_t M, int64_t N, int64_t K, const float *scale, const float *bias, bool accumulate,
-                      float *part, int64_t part_floats, int cu_count, hipStream_t s);
+                      int64_t M, int64_t N, int64_t K, const float *bias, float *part, int64_t part_floats, int cu_count,
+                      hipStream_t s);
 // forward (o, lse) or backward (dqkv from dout, o and lse; Dv scratch)
 hipError_t train_attention(bool backward, int dh, const TrainAttn &a, int cu_count, size_t lds_max, hipStream_t s);
 // out[c] = sum_r A[r][c] (w[r] if w), rows of A lda apart

@@ -206,7 +206,7 @@ __global__ __launch_bounds__(kThreads) void k_embed(const float *y, int64_t rows
 }
 
 // ------------------------------------------------------------------------------------------
-// fp32 GEMM: C[M][N] = beta C + scale (op(A) op(B)) + bias[N], op(A) = A [M][K] (lda) or, with TA,
+// fp32 GEMM of the head: C[M][N] = op(A) op(B) + bias[N], op(A) = A [M][K] (lda) or, with TA,
 // the transpose of A stored [K][M]; op(B) = B [K][N] (ldb) or, with TB, the transpose of B stored
 // [N][K].  64 x 64 output tiles, 64-deep K steps through LDS (the head's short products take one or two:
 // 16-deep steps, each with a memory latency of its own, took 39 us in all on BCH(31,16), 128 words),
@@ -221,9 +221,7 @@ struct GemmF32 {
   int64_t M, N, K;
   int64_t lda, ldb, ldc;
   int64_t kchunk;
-  const float *scale;   // device scalar or null (1)
   const float *bias;    // [N] or null
-  int beta;             // 1: accumulate into C
   float *part;          // [splits][M][N] when split
 };
 
@@ -270,7 +268,6 @@ __global__ __launch_bounds__(kThreads) void k_gemm(GemmF32 g) {
     __syncthreads();
   }
   const bool split = gridDim.z > 1;
-  const float sc = g.scale ? *g.scale : 1.0f;
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     const int64_t r = m0 + 4 * ty + i;
@@ -282,23 +279,22 @@ __global__ __launch_bounds__(kThreads) void k_gemm(GemmF32 g) {
       if (split) {
         g.part[((int64_t)blockIdx.z * g.M + r) * g.N + c] = acc[i][j];
       } else {
-        float v = sc * acc[i][j] + (g.bias ? g.bias[c] : 0.0f);
-        if (g.beta) v += g.C[r * g.ldc + c];
-        g.C[r * g.ldc + c] = v;
+        g.C[r * g.ldc + c] = acc[i][j] + (g.bias ? g.bias[c] : 0.0f);
       }
     }
   }
 }
 
 // The same product on v_mfma_f32_16x16x4_f32 for operands whose contiguous dimension and leading
-// dimensions are multiples of 4 floats (16-byte loads): blocks of BM x 128 outputs (BM = 128, or 64
-// for short reductions, which then get twice the blocks), four wavefronts of BM / 2 x 64
-// (BM / 32 x 4 MFMA tiles), k-steps of 32 staged through LDS, the next step's operands loaded into
-// registers while the current one is multiplied.  LDS rows of BM + 16 and 144 floats put the four k
-// rows an MFMA fragment reads 16 banks apart.  MFMA layout (lane l): A row l & 15 at k = l >> 4,
+// dimensions are multiples of 4 floats (16-byte loads): blocks of 64 x 128 outputs, four wavefronts of
+// 32 x 64 (2 x 4 MFMA tiles), k-steps of 32 staged through LDS, the next step's operands loaded into
+// registers while the current one is multiplied.  What binds is the number of blocks: tiles of 128 x 128 were
+// slower on all three products from LDPC(64,32) to LDPC(1024,512) and 64 to 16384 words (logits of LDPC(256,128), 512
+// words 27.3 us, these 18.0; LDPC(1024,512), 2048 words 108.2, these 88.5).  LDS rows of 80 and 144 floats put the
+// four k rows an MFMA fragment reads 16 banks apart.  MFMA layout (lane l): A row l & 15 at k = l >> 4,
 // B column l & 15 at k = l >> 4, D rows 4 (l >> 4) + i, column l & 15.
 typedef float v4f __attribute__((ext_vector_type(4)));
-constexpr int kMfTile = 128, kMfK = 32;
+constexpr int kMfRows = 64, kMfTile = 128, kMfK = 32;
 
 __device__ __forceinline__ float4 load4_if(const float *p, bool ok) {
   float4 v = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
@@ -306,9 +302,9 @@ __device__ __forceinline__ float4 load4_if(const float *p, bool ok) {
   return v;
 }
 
-template <bool TA, bool TB, int BM>
+template <bool TA, bool TB>
 __global__ __launch_bounds__(kThreads) void k_gemm_mfma(GemmF32 g) {
-  constexpr int BN = kMfTile, AP = BM / 32, BP = BN / 32, TM = BM / 32;
+  constexpr int BM = kMfRows, BN = kMfTile, AP = BM / 32, BP = BN / 32, TM = BM / 32;
   __shared__ __attribute__((aligned(16))) float As[kMfK][BM + 16];
   __shared__ __attribute__((aligned(16))) float Bs[kMfK][BN + 16];
   const float *__restrict__ A = g.A;
@@ -318,7 +314,7 @@ __global__ __launch_bounds__(kThreads) void k_gemm_mfma(GemmF32 g) {
   const int wm = (wave >> 1) * (BM / 2), wn = (wave & 1) * 64;
   const int64_t m0 = (int64_t)blockIdx.y * BM, n0 = (int64_t)blockIdx.x * BN;
   const int64_t kb = (int64_t)blockIdx.z * g.kchunk, ke = std::min<int64_t>(g.K, kb + g.kchunk);
-  // Thread t stages float4 number t + 256 u of each 32 x W operand tile (W = BM or 128).  Stored
+  // Thread t stages float4 number t + 256 u of each 32 x W operand tile (W = 64 or 128).  Stored
   // k-major ([k][m] or [k][n]): k row t / (W / 4) + u 1024 / W, columns 4 (t mod W / 4) .. +3.
   // Stored with k contiguous: tile row (t >> 3) + 32 u, k offsets 4 (t & 7) .. +3.
   const int kmA_r = tid / (BM / 4), kmA_c = (tid % (BM / 4)) * 4, kmB_r = tid >> 5, kmB_c = (tid & 31) * 4;
@@ -410,12 +406,10 @@ __global__ __launch_bounds__(kThreads) void k_gemm_mfma(GemmF32 g) {
     }
     __syncthreads();
   }
-  // split partial sums raw into their slice of part, else scale, bias and the optional C
+  // split partial sums raw into their slice of part, else with the bias
   const bool split = gridDim.z > 1;
   float *const P = split ? g.part + (int64_t)blockIdx.z * M * N : g.C;
   const int64_t ld = split ? N : g.ldc;
-  const float sc = (!split && g.scale) ? *g.scale : 1.0f;
-  const bool beta = !split && g.beta;
   const float *bias = split ? nullptr : g.bias;
   const bool full = m0 + BM <= M && n0 + BN <= N;
   float bj[4];
@@ -434,9 +428,7 @@ __global__ __launch_bounds__(kThreads) void k_gemm_mfma(GemmF32 g) {
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         if (!full && n0 + wn + 16 * j + fc >= N) continue;
-        float o = sc * acc[i][j][v] + bj[j];
-        if (beta) o += prow[16 * j];
-        prow[16 * j] = o;
+        prow[16 * j] = acc[i][j][v] + bj[j];
       }
     }
 }
@@ -669,9 +661,7 @@ __global__ __launch_bounds__(kThreads) void k_gemm_reduce(GemmF32 g, int splits)
   if (rl != 0 || e >= MN) return;
   const float s = ((red[0][cl] + red[1][cl]) + red[2][cl]) + red[3][cl];
   const int64_t r = e / g.N, c = e - r * g.N;
-  float v = (g.scale ? *g.scale : 1.0f) * s + (g.bias ? g.bias[c] : 0.0f);
-  if (g.beta) v += g.C[r * g.ldc + c];
-  g.C[r * g.ldc + c] = v;
+  g.C[r * g.ldc + c] = s + (g.bias ? g.bias[c] : 0.0f);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1833,17 +1823,17 @@ hipError_t train_embed(const float *y, int64_t rows, int n, int L, int d, const 
 }
 
 hipError_t train_gemm(bool ta, bool tb, const float *A, int64_t lda, const float *B, int64_t ldb, float *C, int64_t ldc,
-                      int64_t M, int64_t N, int64_t K, const float *scale, const float *bias, bool accumulate,
-                      float *part, int64_t part_floats, int cu_count, hipStream_t s) {
+                      int64_t M, int64_t N, int64_t K, const float *bias, float *part, int64_t part_floats, int cu_count,
+                      hipStream_t s) {
   if (M <= 0 || N <= 0) return hipSuccess;
-  train::GemmF32 g{A, B, C, M, N, K, lda, ldb, ldc, K, scale, bias, accumulate ? 1 : 0, part};
+  if (ta && tb) return hipErrorInvalidValue;
+  train::GemmF32 g{A, B, C, M, N, K, lda, ldb, ldc, K, bias, part};
   // the MFMA kernel reads 16-byte vectors along each operand's contiguous dimension
   auto al16 = [](const float *p) { return ((uintptr_t)p & 15u) == 0; };
   const bool mfma = al16(A) && al16(B) && lda % 4 == 0 && ldb % 4 == 0 && (ta ? M : K) % 4 == 0 &&
                     (tb ? K : N) % 4 == 0;
-  // reductions of at most 256, and products of at most 128 x 512 outputs, get 64-row tiles: twice
-  // the blocks to cover their short k loops, or the compute units
-  const int64_t tm = mfma ? (K <= 256 || M * N <= 128 * 512 ? 64 : train::kMfTile) : 64, tn = mfma ? train::kMfTile : 64;
+  const int64_t tm = 64, tn = mfma ? train::kMfTile : 64;
+  static_assert(train::kMfRows == 64, "rows of a block of either kernel");
   const int64_t tiles = ((M + tm - 1) / tm) * ((N + tn - 1) / tn);
   // split long reductions over k so that about two blocks per compute unit are busy (k chunks of at
   // least 128)
@@ -1857,18 +1847,9 @@ hipError_t train_gemm(bool ta, bool tb, const float *A, int64_t lda, const float
   if (splits < 1) splits = 1;
   const dim3 grid((unsigned)((N + tn - 1) / tn), (unsigned)((M + tm - 1) / tm), (unsigned)splits);
   if (mfma) {
-#define AECCT_MF_GO(TA_, TB_)                                                                          \
-  do {                                                                                                 \
-    if (tm == 64) hipLaunchKernelGGL((train::k_gemm_mfma<TA_, TB_, 64>), grid, dim3(train::kThreads), 0, s, g); \
-    else hipLaunchKernelGGL((train::k_gemm_mfma<TA_, TB_, 128>), grid, dim3(train::kThreads), 0, s, g);        \
-  } while (0)
-    if (ta && tb) AECCT_MF_GO(true, true);
-    else if (ta) AECCT_MF_GO(true, false);
-    else if (tb) AECCT_MF_GO(false, true);
-    else AECCT_MF_GO(false, false);
-#undef AECCT_MF_GO
-  } else if (ta && tb) {
-    hipLaunchKernelGGL((train::k_gemm<true, true>), grid, dim3(train::kThreads), 0, s, g);
+    if (ta) hipLaunchKernelGGL((train::k_gemm_mfma<true, false>), grid, dim3(train::kThreads), 0, s, g);
+    else if (tb) hipLaunchKernelGGL((train::k_gemm_mfma<false, true>), grid, dim3(train::kThreads), 0, s, g);
+    else hipLaunchKernelGGL((train::k_gemm_mfma<false, false>), grid, dim3(train::kThreads), 0, s, g);
   } else if (ta) {
     hipLaunchKernelGGL((train::k_gemm<true, false>), grid, dim3(train::kThreads), 0, s, g);
   } else if (tb) {

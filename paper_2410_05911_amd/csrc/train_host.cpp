@@ -270,8 +270,8 @@ aecct_status aecct_train_grad(const aecct_trainer *tr, const aecct_train_params 
   AECCT_TRY(train_embed(y, R, T.n, T.L, d, T.chk_ptr, T.chk_idx, p->embed, p->pos, X, tv, i8(W.layer[0].xq),
                         ws + W.layer[0].tx, s));
   auto gemm = [&](bool ta, bool tb, const float *A, int64_t lda, const float *Bm, int64_t ldb, float *C, int64_t ldc,
-                  int64_t M, int64_t Nn, int64_t K, const float *scale, const float *bias, bool acc) {
-    return train_gemm(ta, tb, A, lda, Bm, ldb, C, ldc, M, Nn, K, scale, bias, acc, part, (int64_t)PF, T.cu_count, s);
+                  int64_t M, int64_t Nn, int64_t K, const float *bias) {
+    return train_gemm(ta, tb, A, lda, Bm, ldb, C, ldc, M, Nn, K, bias, part, (int64_t)PF, T.cu_count, s);
   };
   for (int l = 0; l < N; ++l) {
     const TrainWs::Layer &q = W.layer[l];
@@ -329,7 +329,7 @@ aecct_status aecct_train_grad(const aecct_trainer *tr, const aecct_train_params 
   // head and loss (Section 3, Section 6)
   float *z = ws + W.z, *fo = ws + W.fo, *df = ws + W.df, *dz = ws + W.dz;
   AECCT_TRY(train_rowdot(X, R, d, p->head_w1, p->head_b1, z, s));
-  AECCT_TRY(gemm(false, false, z, T.L, p->head_wo, T.n, fo, T.n, B, T.n, T.L, nullptr, p->head_bo, false));
+  AECCT_TRY(gemm(false, false, z, T.L, p->head_wo, T.n, fo, T.n, B, T.n, T.L, p->head_bo));
   AECCT_TRY(train_loss(fo, y, xs, B * T.n, df, ws + W.lpart, loss, s));
 
   // ---- backward ------------------------------------------------------------------------------
@@ -337,8 +337,8 @@ aecct_status aecct_train_grad(const aecct_trainer *tr, const aecct_train_params 
     return train_colsum(A, lda, wr, rows, C, o, part, (int64_t)PF, s);
   };
   AECCT_TRY(colsum(df, T.n, nullptr, B, T.n, g->head_bo));
-  AECCT_TRY(gemm(true, false, z, T.L, df, T.n, g->head_wo, T.n, T.L, T.n, B, nullptr, nullptr, false));
-  AECCT_TRY(gemm(false, true, df, T.n, p->head_wo, T.n, dz, T.L, B, T.L, T.n, nullptr, nullptr, false));
+  AECCT_TRY(gemm(true, false, z, T.L, df, T.n, g->head_wo, T.n, T.L, T.n, B, nullptr));
+  AECCT_TRY(gemm(false, true, df, T.n, p->head_wo, T.n, dz, T.L, B, T.L, T.n, nullptr));
   AECCT_TRY(colsum(dz, 1, nullptr, R, 1, g->head_b1));
   AECCT_TRY(colsum(X, d, dz, R, d, g->head_w1));
   float *dX = ws + W.dx, *dR2 = ws + W.dr2, *dR1 = ws + W.dr1, *dG = ws + W.dg, *dO = ws + W.dO,
