@@ -196,7 +196,7 @@ struct TrainAttn {
   float *o, *lse;       // [rows][d] output, [rows][heads] log-sum-exp of the scores
   const float *dout;    // [rows][d] gradient of O (backward)
   float *dqkv;          // [rows][3d] gradients of Q | K | V (backward)
-  float *Dv;            // [rows][heads] dO . O (backward)
+  float *Dv;            // [rows][heads] dO . O (backward of the gather form: scratch between its two kernels)
 };
 // the six maps of up to ten layers per launch (one block per matrix, at most 64 Ki entries), passed by value
 constexpr int kTrainJobsPerLaunch = 60;
@@ -300,7 +300,7 @@ hipError_t train_weight_grads(int d, TrainDwJobs &jobs, int cu_count, float *par
 hipError_t train_gemm(bool ta, bool tb, const float *A, int64_t lda, const float *B, int64_t ldb, float *C, int64_t ldc,
                       int64_t M, int64_t N, int64_t K, const float *bias, float *part, int64_t part_floats, int cu_count,
                       hipStream_t s);
-// forward (o, lse) or backward (dqkv from dout, o and lse; Dv scratch)
+// forward (o, lse) or backward (dqkv from dout, o and lse)
 hipError_t train_attention(bool backward, int dh, const TrainAttn &a, int cu_count, size_t lds_max, hipStream_t s);
 // out[c] = sum_r A[r][c] (w[r] if w), rows of A lda apart
 hipError_t train_colsum(const float *A, int64_t lda, const float *w, int64_t rows, int C, float *out, float *part,

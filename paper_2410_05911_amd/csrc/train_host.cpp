@@ -32,7 +32,7 @@ struct TrainWs {
   // attention's output and log-sum-exp, both normalised rows with their 1 / sigma, the ReLU mask
   struct Layer { size_t xq, tx, qkv, lse, o, oq, to, xn1, rho1, x1q, t1, mask, gq, tg, xn2, rho2; };
   std::vector<Layer> layer;
-  size_t t, x, z, fo, df, dz, tw, tpk, gam, sc, lpart, lnpart, dx, dr2, dr1, dg, dO, dqkv, dv, part;
+  size_t t, x, z, fo, df, dz, tw, tpk, gam, sc, lpart, lnpart, dx, dr2, dr1, dg, dO, dqkv, part;
   size_t part_floats, total_bytes;
 };
 
@@ -86,7 +86,6 @@ TrainWs train_ws(const aecct_trainer &T, int64_t batch) {
   w.dg = take(R * dff);
   w.dO = take(R * d);
   w.dqkv = take(R * 3 * d);
-  w.dv = take(R * h);
   w.part_floats = std::max<size_t>(size_t(1) << 22, 4 * std::max<size_t>((size_t)T.L * T.n, d * dff));
   w.part_floats = std::max<size_t>(
       w.part_floats, (size_t)aecct::train_dw_splits((int)d, (int64_t)R, kDwTiles, T.cu_count) * kDwTiles * d * (d + 1));
@@ -355,8 +354,9 @@ aecct_status aecct_train_grad(const aecct_trainer *tr, const aecct_train_params 
                 ws + W.lnpart, R};
     AECCT_TRY(train_bwd(d, bw, T.cu_count, s));
     // attention, then the query, key and value maps: one product over their packed gradient
+    // (dX, read by train_bwd and written again by that product, lends its space to Dv)
     TrainAttn at{ws + q.qkv, R, T.L, d, T.heads, T.hf, T.m1_ptr, T.m1_idx, T.m2_ptr, T.m2_idx, ws + q.o, ws + q.lse,
-                 dO, dQKV, ws + W.dv};
+                 dO, dQKV, dX};
     AECCT_TRY(train_attention(true, T.dh, at, T.cu_count, T.lds_max, s));
     const void *fq[3] = {tpk(l, 0, true), tpk(l, 1, true), tpk(l, 2, true)};
     const float *sq[3] = {sc + 6 * l, sc + 6 * l + 1, sc + 6 * l + 2};
