@@ -1,5 +1,6 @@
 """The training step's row strips, tiles and row ranges at the sizes where they can go wrong: fewer rows
-than a 16-token strip or a wavefront's eight, a last strip that is partly filled, one layer (the first is the last), more layers than a packing or Eq. 1 launch takes, a
+than a 16-token strip or a wavefront's eight, a last strip that is partly filled, several strips a
+wavefront, one layer (the first is the last), more layers than a packing or Eq. 1 launch takes, a
 positional table, odd lengths, words on either side of the lines between the attention's two forms.
 
 Against the float64 oracle, normwise.  fp32 rounding alone gives a few 1e-7 (test_gpu_train.py, TIGHT);
@@ -63,6 +64,18 @@ def test_long_words_in_both_attention_forms(n, d, heads, repeat):
     so the median error stays below 8e-3.  Rows left out of a last pass (5 % of the longest word's) or staged from a
     wrong token would change it by far more."""
     _step_against_oracle(n, d, 1, 3, heads=heads, repeat=repeat, median=8e-3)
+
+
+@pytest.mark.parametrize("d,param_seed,word_seed", [(32, 13, 11), (64, 2, 1), (128, 17, 9)])
+def test_several_strips_a_wavefront(d, param_seed, word_seed):
+    """66030 rows, the last strip partly filled: 4127 strips on 256 compute units give a wavefront of every strip
+    kernel (at most two blocks of eight per unit) a second and third one, and the weight gradients their largest
+    number of row ranges.  Three words repeated; the seeds are ones whose rounding decisions lie farthest
+    from a tie (above 6e-5 code units), so that none flips.  fp32 sums over chains of at most about 1600
+    additions are within 1e-4; a strip left out or taken twice is 1 / 4127 = 2.4e-4 of every gradient."""
+    errs, loss, loss64 = _errors(7, d, 2, 3, repeat=2201, param_seed=param_seed, word_seed=word_seed)
+    assert abs(loss - loss64) <= 1e-4 * abs(loss64)
+    assert max(errs.values()) <= 1e-4, errs
 
 
 def _step_against_oracle(n, d, layers, batch, median=1e-3, **kw):
