@@ -1,7 +1,9 @@
 """GPU tests of the boundary's options and of the path against the plain fp64 definition.
 
 - One alpha per word (aecct_act_scale WORD, the paper-literal reading of Eq. 2): GPU decodes
-  against the oracle in the same mode, bit for bit, and the forms that cannot take it refuse.
+  against the oracle in the same mode, bit for bit, in both forms (AUTO: the fused attention with the maps in
+  stages where the shape allows it, d = 64 and 128; UNFUSED: the separate kernels), and the forms that cannot
+  take it refuse.
 - The logit tolerance rule against the oracle's plain fp64 reference decode (dense masked softmax,
   libm exp, exact division and square root): |f_gpu - f_64| <= 1e-3 and identical bits where
   |f_64| > 1e-3.  The fp64 decode takes the canonical oracle's int8 decision only where its own
@@ -40,14 +42,15 @@ def _np(t):
     return t.cpu().numpy()
 
 
-@pytest.mark.parametrize("c", [1, 2, 3])
-def test_per_word_alpha_against_oracle(P, oracle_mod, c):
-    """Eq. 2 with one alpha per word on the configured batch (the layered path's unfused form):
-    logits and bits equal the oracle's per-word decode bit for bit on a spread sample."""
+@pytest.mark.parametrize("c,form", [(1, -1), (2, -1), (3, -1), (3, 0)])
+def test_per_word_alpha_against_oracle(P, oracle_mod, c, form):
+    """Eq. 2 with one alpha per word on the configured batch (config 3 in its staged form by AUTO and as
+    separate kernels; both are reported as UNFUSED): logits and bits equal the oracle's per-word decode bit for
+    bit on a spread sample."""
     cfg = CONFIGS[c]
-    print(f"[alpha per word] config {c} batch {cfg.batch}", flush=True)
+    print(f"[alpha per word] config {c} batch {cfg.batch} form {form}", flush=True)
     cfg, H, G, w, y, x = build_workload(c, act_scale="word")
-    dec = P.Decoder(H, w)
+    dec = P.Decoder(H, w, layered_attention=form)
     assert dec.path == P.PATH_LAYERED and dec.info.act_scale_mode == P.ACT_SCALE_WORD
     assert dec.info.layered_attention == P.LAYERED_ATTN_UNFUSED
     bits, logits = dec.decode(_dev(y))

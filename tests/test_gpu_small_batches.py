@@ -88,7 +88,7 @@ def test_fused_word_over_wavefronts_matches_one_wavefront(P, n, m, attention, si
 ])
 def test_word_scale_stages_match_separate_kernels(P, n, d, heads, attention, hf, sizes):
     """One alpha per word: the fused attention with the maps in stages between the word maxima, against the
-    separate kernels (pinned to the oracle by test_gpu_parity.py), bit for bit."""
+    separate kernels (pinned to the oracle below and by test_gpu_boundary.py), bit for bit."""
     H = regular_ldpc_3_6(n, seed=1000 + n)
     w = random_weights(n, n // 2, d, 2, heads, seed=n + d, first_ring_heads=hf, attention=attention, act_scale="word",
                        with_pos=hf == 2)
@@ -108,3 +108,32 @@ def test_word_scale_stages_match_separate_kernels(P, n, d, heads, attention, hf,
     assert torch.equal(f, logits) and torch.equal(b, bits)
     staged.close()
     separate.close()
+
+
+@pytest.mark.parametrize("n,d,heads,attention,hf,form", [
+    (66, 64, 4, "casa", 2, -1),        # fp32 K and V, d_h = 16 at d = 64
+    (128, 128, 16, "hpsa", 6, -1),     # d_h = 8 at d = 128
+    (256, 128, 8, "hpsa", 4, -1),      # lane pairs
+    (514, 128, 8, "casa", 2, -1),      # fp32 K, int16 V, 771 tokens
+    (398, 64, 8, "hpsa", 4, -1),       # int16 K and V
+    (256, 128, 8, "hpsa", 4, 0),       # the separate kernels
+    (514, 128, 8, "casa", 2, 0),
+])
+def test_word_scale_against_oracle(P, oracle_mod, n, d, heads, attention, hf, form):
+    """One alpha per word at the widths and lengths of every attention form, staged (AUTO) and as separate kernels:
+    bits and logits of a few words equal the oracle's.  Both are reported as UNFUSED; the staged form is told
+    by its workspace of less than four fp32 rows of d a token, where the separate kernels hold Q, K, V and the
+    hidden row besides."""
+    H = regular_ldpc_3_6(n, seed=1000 + n)
+    w = random_weights(n, n // 2, d, 2, heads, seed=n + d, first_ring_heads=hf, attention=attention, act_scale="word",
+                       with_pos=hf == 2)
+    y, _, _ = awgn_words(generator_from_parity(H), 5, (2.0, 4.0), seed=n)
+    print(f"[word] LDPC({n}) d {d} {attention} form {form} against the oracle", flush=True)
+    dec = P.Decoder(H, w, layered_attention=form)
+    rows = 5 * dec.L
+    assert (dec.workspace_size(5) < 4 * rows * 4 * d) == (form == -1)
+    bits, logits = dec.decode(torch.from_numpy(y).cuda())
+    torch.cuda.synchronize()
+    bo, fo = oracle_mod.OracleModel(H, w).decode(y, n_threads=5)
+    assert np.array_equal(logits.cpu().numpy(), fo) and np.array_equal(bits.cpu().numpy(), bo)
+    dec.close()
