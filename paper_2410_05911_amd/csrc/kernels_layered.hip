@@ -1713,24 +1713,24 @@ __global__ __launch_bounds__(kTbWaves * 64) void k_token_block(TokenBlockArgs p)
     // 10.78 -> 10.64 ms)
     constexpr int N1 = TH * S * 32 / (kTbWaves * 64), NO = (TO * S * 32 + kTbWaves * 64 - 1) / (kTbWaves * 64);
     static_assert(TH * S == TO * SH && N1 * kTbWaves * 64 == TH * S * 32, "fragments per thread");
-    uint4 r1[N1], r2[N1], ro[NO];
+    v4i r1[N1], r2[N1], ro[NO];
 #pragma unroll
-    for (int k = 0; k < N1; ++k) r1[k] = ((const uint4 *)p.f1)[threadIdx.x + k * kTbWaves * 64];
+    for (int k = 0; k < N1; ++k) r1[k] = ((const v4i *)p.f1)[threadIdx.x + k * kTbWaves * 64];
 #pragma unroll
-    for (int k = 0; k < N1; ++k) r2[k] = ((const uint4 *)p.f2)[threadIdx.x + k * kTbWaves * 64];
+    for (int k = 0; k < N1; ++k) r2[k] = ((const v4i *)p.f2)[threadIdx.x + k * kTbWaves * 64];
 #pragma unroll
     for (int k = 0; k < NO; ++k) {
       const int u = threadIdx.x + k * kTbWaves * 64;
-      if (u < TO * S * 32) ro[k] = ((const uint4 *)p.fo)[u];
+      if (u < TO * S * 32) ro[k] = ((const v4i *)p.fo)[u];
     }
 #pragma unroll
-    for (int k = 0; k < N1; ++k) ((uint4 *)f1)[threadIdx.x + k * kTbWaves * 64] = r1[k];
+    for (int k = 0; k < N1; ++k) ((v4i *)f1)[threadIdx.x + k * kTbWaves * 64] = r1[k];
 #pragma unroll
-    for (int k = 0; k < N1; ++k) ((uint4 *)f2)[threadIdx.x + k * kTbWaves * 64] = r2[k];
+    for (int k = 0; k < N1; ++k) ((v4i *)f2)[threadIdx.x + k * kTbWaves * 64] = r2[k];
 #pragma unroll
     for (int k = 0; k < NO; ++k) {
       const int u = threadIdx.x + k * kTbWaves * 64;
-      if (u < TO * S * 32) ((uint4 *)fo)[u] = ro[k];
+      if (u < TO * S * 32) ((v4i *)fo)[u] = ro[k];
     }
   }
   float *lv = (float *)(smem + frag_bytes);

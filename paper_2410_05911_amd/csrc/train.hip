@@ -685,16 +685,17 @@ constexpr size_t qkv_lds() { return (size_t)3 * D * D + (size_t)3 * D * 4; }
 template <int D>
 constexpr size_t block_lds() { return (size_t)9 * D * D + (size_t)12 * D * 4; }
 
-// `words` 16-byte words to LDS, four loads of a thread in flight at a time
+// `words` 16-byte words to LDS, four loads of a thread in flight at a time (as v4i: a HIP uint4 stored under a
+// condition goes through scratch memory with this compiler)
 __device__ __forceinline__ void stage16(const void *src, void *dst, int words, int tid) {
   constexpr int NT = kTbWaves * 64;
   for (int u = tid; u < words; u += 4 * NT) {
-    uint4 r[4];
+    v4i r[4];
 #pragma unroll
-    for (int k = 0; k < 4; ++k) r[k] = ((const uint4 *)src)[std::min(u + k * NT, words - 1)];
+    for (int k = 0; k < 4; ++k) r[k] = ((const v4i *)src)[std::min(u + k * NT, words - 1)];
 #pragma unroll
     for (int k = 0; k < 4; ++k)
-      if (u + k * NT < words) ((uint4 *)dst)[u + k * NT] = r[k];
+      if (u + k * NT < words) ((v4i *)dst)[u + k * NT] = r[k];
   }
 }
 __device__ __forceinline__ void stage_vec(const float *src, float *dst, int n, int tid) {
