@@ -41,8 +41,9 @@ __device__ __forceinline__ float wave_max(float v) {
 // statistics come from a radix selection over the bit patterns of |W| (non-negative floats order
 // like their bits) in digits of 12, 10 and 9 bits: the first takes the exponent and four mantissa bits, as
 // the exponent alone leaves a wavefront's 64 keys in a few counters whose atomics then run one after the
-// other.  A thread holds its keys (up to 64 Ki per matrix) in registers between the passes.  Eight-bit
-// digits read from memory per pass took 95 us on 128 x 512 matrices.
+// other.  A thread holds its keys (up to 64 Ki per matrix, 64 a thread) between the passes, in registers but for
+// 31 of those 64, which do not fit beside the work of 1024 threads and go to scratch.  Eight-bit digits read from
+// memory per pass took 95 us on 128 x 512 matrices.
 // ------------------------------------------------------------------------------------------
 using AapJob = TrainAapJob;
 constexpr int kAapThreads = 1024, kAapWaves = kAapThreads / 64, kAapBins = 4096;
