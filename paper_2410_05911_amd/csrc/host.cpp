@@ -754,14 +754,16 @@ static aecct_status decode_chunks(const Model &M, const float *y, int64_t batch,
   int8_t *xq = (int8_t *)(ws + W.xq), *oq = (int8_t *)(ws + W.oq), *x1q = (int8_t *)(ws + W.x1q);
   int8_t *gq = (int8_t *)(ws + W.gq);
   float *ax = (float *)(ws + W.ax), *ao = (float *)(ws + W.ao), *a1 = (float *)(ws + W.a1), *ag = (float *)(ws + W.ag);
-  float *o32 = M.act_word ? (float *)(ws + W.o32) : nullptr, *h32 = M.act_word ? (float *)(ws + W.h32) : nullptr;
+  const bool wide = M.act_word && !M.word_form;   // fp32 O and hidden rows: the separate word-alpha kernels only
+  float *o32 = wide ? (float *)(ws + W.o32) : nullptr, *h32 = wide ? (float *)(ws + W.h32) : nullptr;
   // With the token block, X and Xq are kept in its lane order from the embedding to the head.
   // The fused projection + attention (keys and values in LDS as fp32, or as int16 accumulators
   // for long words) leaves O in fp32 (in the QKV space); the token block then applies Eq. 2
   // itself. The lane-pair form on words of at most 384 tokens and the unfused attention quantise
   // O as they write it (a quarter of the bytes).  With one
-  // alpha per word every quantisation point is redone over the whole word from the fp32 values
-  // (natural layout, unfused form, no token block).
+  // alpha per word the separate kernels (word_form 0) redo every quantisation point over the whole word
+  // from the fp32 values, in natural layout and without the token block; the staged form (word_form 1
+  // or 2, below) runs the fused attention and keeps the lane order.
   const bool pw = M.act_word != 0;
   const bool tb = !pw && aecct::token_block_supported(M);
   const bool qa = M.lattn == AECCT_LAYERED_ATTN_LDS_F32, qw = M.lattn == AECCT_LAYERED_ATTN_LDS_I16;
