@@ -271,7 +271,9 @@ typedef struct aecct_model_info {
   int32_t attention;         /* aecct_attention (first_ring_heads reads 0 under CASA) */
   int32_t layered_attention; /* resolved aecct_layered_attention (never AUTO): how the layered
                                 path runs a layer's projection and attention (reported whatever
-                                path resolved) */
+                                path resolved).  With one alpha per word UNFUSED stands for both of its
+                                forms, the separate kernels and AUTO's fused attention with the maps in
+                                stages; the workspace sizes differ */
   int32_t act_scale_mode;    /* aecct_act_scale */
   int32_t device;            /* HIP device the model lives on */
   int32_t compute_units;     /* its compute units, and the LDS bytes one workgroup may use on it: */
