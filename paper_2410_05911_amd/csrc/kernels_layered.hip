@@ -2923,6 +2923,8 @@ static size_t qkv_attention_i16_lds(const Model &M) {
 // in units of one group's time, with the split forms' longer rows (lists from the L2 and O in fp32
 // where the whole-word form keeps the lists in LDS and writes codes) priced at a fifth more.
 // Decodes measured: LDPC(256,128), 37 words 665 -> 477 us; LDPC(128,64), one word 139 -> 104 us.
+// Against every divisor, 12 shapes of d = 64 and 128, 99 to 1536 tokens and 1 to 800 words (183 decodes): within 3 % of
+// the best in 170, up to 19 % off just above one round of whole words, never more than 2 % behind whole words.
 int attention_groups_per_block(const Model &M, int form, int64_t words) {
   const int G = M.d / 16;
   if (form != 1 && form != 2) return G;   // fp32 or int16 keys and values in LDS (aecct_layered_attention)
