@@ -1980,11 +1980,12 @@ hipError_t train_block(int d, const TrainBlock &a, int cu_count, size_t lds_max,
   return hipErrorInvalidValue;
 }
 
-int train_dw_splits(int d, int64_t rows, int tiles, int cu_count) {
-  // three blocks per compute unit at d = 128, as many as the register file holds (LDPC(256,128), 256 words:
-  // 7.78 ms a step, with two 8.04), two below (LDPC(128,64), 125 words: 0.93 ms, with three or four 0.94: more
-  // partial sums), at least 128 rows each
-  const int64_t want = ((d == 128 ? 3 : 2) * (int64_t)cu_count + tiles - 1) / tiles;
+int train_dw_splits(int64_t rows, int tiles, int cu_count) {
+  // three blocks per compute unit, as many as the register file holds at d = 128, at least 128 rows each.  Steps of four
+  // layers with one, two, three and four blocks: LDPC(128,64), d = 64, 125 words 685, 632, 625, 634 us, 1024 words
+  // 3837, 3223, 3150, 3187; BCH(31,16), d = 32, 128 words 320, 316, 315, 314, 4096 words 2368, 2077, 2014, 2069;
+  // LDPC(256,128), d = 128, 256 words 4030, 3394, 3292, 3443.
+  const int64_t want = (3 * (int64_t)cu_count + tiles - 1) / tiles;
   return (int)std::max<int64_t>(1, std::min<int64_t>(want, (rows + 127) / 128));
 }
 
@@ -1998,7 +1999,7 @@ hipError_t train_weight_grads(int d, TrainDwJobs &J, int cu_count, float *part, 
   }
   const int tiles = J.tile0[J.n];
   const int rs = 4096 / d;   // rows of one step of the kernel
-  int64_t splits = train_dw_splits(d, J.rows, tiles, cu_count);
+  int64_t splits = train_dw_splits(J.rows, tiles, cu_count);
   if (splits > 8) splits = splits / 8 * 8;
   J.chunk = ((J.rows + splits - 1) / splits + rs - 1) / rs * rs;
   splits = (J.rows + J.chunk - 1) / J.chunk;
