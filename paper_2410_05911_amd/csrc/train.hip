@@ -440,7 +440,8 @@ __global__ __launch_bounds__(kThreads) void k_gemm_mfma(GemmF32 g) {
 // lo (hi the leading 8 significant bits by truncation, mid the next 8, lo the remaining at most 8), each
 // part times a ternary entry is exact, and the three v_mfma_f32_16x16x32_bf16 products accumulate in
 // fp32: the result is an fp32-accumulated sum of exact products, as in the fp32 kernels, at the bf16
-// matrix rate.  T^T comes pre-packed as bf16 MFMA B fragments (k_pack_tern).  A wave computes 16 rows x
+// matrix rate.  (The MFMA reads a subnormal part as 0, so the split is whole for |a| above about 1e-33; with the
+// step's gradients scaled down to 1e-28 the results are the same to 1e-7, at 1e-30 to 1e-4.)  T^T comes pre-packed as bf16 MFMA B fragments (k_pack_tern).  A wave computes 16 rows x
 // 16 NJ columns, a block four waves.
 // ------------------------------------------------------------------------------------------
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
