@@ -254,7 +254,11 @@ def train_bench(c: int, batch: int, steps: int, warmup: int):
     e1.record()
     torch.cuda.synchronize()
     ms = e0.elapsed_time(e1) / steps
-    # fp32 multiply-adds of the step's GEMMs (forward, input gradients, weight gradients) and head
+    # fp32 multiply-adds of the step's GEMMs (forward, input gradients, weight gradients) and head, and the
+    # bytes that the step's eight kernels a layer read and write, each tensor of d floats (4 d bytes), codes (d)
+    # or mask bits once per kernel: per token and layer forward 13 d (Q | K | V from codes), 16 d (attention),
+    # 23.5 d (block), backward 40.5 d (token-local half), 32 d (attention), 20 d (input gradient of Q | K | V), 43 d
+    # (weight gradients)
     R = batch * L
     lin = N * (4 * d * d + 2 * d * 4 * d)
     fma = 3 * R * lin + 3 * batch * L * n
@@ -269,13 +273,10 @@ def train_bench(c: int, batch: int, steps: int, warmup: int):
                       "config": {"workload": f"qat_{cfg.name}_batch{batch}", "tokens": L, "d": d, "layers": N,
                                  "batch": batch},
                       "gemm_fma_per_step": fma, "gemm_fma_rate_T": fma / (ms * 1e-3) / 1e12,
-                      # the step's products as fp32 work against the fp32 MFMA peak: every GEMM flop
-                      # over the whole step time (the forward maps run as exact int8 products, the
-                      # gradients as three exact bf16 products per fp32 one, so this is a rate of work,
-                      # not of one unit)
-                      "roofline": {"bound": "mfma", "kernel": "k_train_qkv + k_train_block + k_train_bwd + k_gemm_tern + k_train_dw (whole-step time)",
-                                   "achieved": 2 * fma / (ms * 1e-3) / 1e12, "peak": 157.3, "unit": "TFLOP/s",
-                                   "frac": 2 * fma / (ms * 1e-3) / 1e12 / 157.3, "traffic": None},
+                      # memory binds the step: those bytes over the whole step time against the HBM peak
+                      "roofline": {"bound": "hbm", "kernel": "the step's layer kernels (whole-step time)",
+                                   "achieved": 188 * d * R * N / (ms * 1e-3) / 1e12, "peak": 8.0, "unit": "TB/s",
+                                   "frac": 188 * d * R * N / (ms * 1e-3) / 8e12, "traffic": None},
                       "cpu_baseline": {"value": k / dt, "unit": "codewords/s", "cores": 1, "kind": "oracle",
                                        "sample": f"{k} words, float64 numpy oracle, {dt:.2f} s"}}), flush=True)
 
