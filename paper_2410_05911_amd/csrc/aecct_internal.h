@@ -293,7 +293,7 @@ struct TrainDwJobs {
   int splits;
   float *part, *cpart;
 };
-int train_dw_splits(int64_t rows, int tiles, int cu_count);   // at most; scratch: splits x tiles x d (d + 1) floats
+int train_dw_splits(int d, int64_t rows, int tiles, int cu_count);   // at most; scratch: splits x tiles x d (d + 1) floats
 hipError_t train_weight_grads(int d, TrainDwJobs &jobs, int cu_count, float *part, int64_t part_floats, hipStream_t s);
 // C[M][N] = op(A) op(B) + bias (or null); ta: A stored [K][M]; tb: B stored [N][K]; not both.
 // part: scratch of part_floats floats for split reductions over K.

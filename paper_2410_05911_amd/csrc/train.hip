@@ -1981,12 +1981,14 @@ hipError_t train_block(int d, const TrainBlock &a, int cu_count, size_t lds_max,
   return hipErrorInvalidValue;
 }
 
-int train_dw_splits(int64_t rows, int tiles, int cu_count) {
-  // three blocks per compute unit, as many as the register file holds at d = 128, at least 128 rows each.  Steps of four
-  // layers with one, two, three and four blocks: LDPC(128,64), d = 64, 125 words 685, 632, 625, 634 us, 1024 words
-  // 3837, 3223, 3150, 3187; BCH(31,16), d = 32, 128 words 320, 316, 315, 314, 4096 words 2368, 2077, 2014, 2069;
-  // LDPC(256,128), d = 128, 256 words 4030, 3394, 3292, 3443.
-  const int64_t want = (3 * (int64_t)cu_count + tiles - 1) / tiles;
+int train_dw_splits(int d, int64_t rows, int tiles, int cu_count) {
+  // Three blocks per compute unit, as many as the register file holds at d = 128, where a block's range is then at
+  // least eight of the kernel's steps (4096 / d rows), else two (a short range is mostly its first loads and its partial
+  // sums); at least 128 rows each.  Steps of four layers with two and three blocks, us: BCH(31,16), d = 32, 1000 words
+  // 663 / 672, LDPC(128,64), d = 32, 160 words 512 / 524, 512 words 1078 / 1043; d = 64, 200 words 927 / 919, 1024 words
+  // 3223 / 3150; BCH(31,16), d = 128, 300 words 923 / 940; LDPC(256,128), d = 128, 256 words 3394 / 3292 (four 3443).
+  const auto ranges = [&](int64_t per_cu) { return (per_cu * cu_count + tiles - 1) / tiles; };
+  const int64_t want = rows >= ranges(3) * 8 * (4096 / d) ? ranges(3) : ranges(2);
   return (int)std::max<int64_t>(1, std::min<int64_t>(want, (rows + 127) / 128));
 }
 
@@ -2000,7 +2002,7 @@ hipError_t train_weight_grads(int d, TrainDwJobs &J, int cu_count, float *part, 
   }
   const int tiles = J.tile0[J.n];
   const int rs = 4096 / d;   // rows of one step of the kernel
-  int64_t splits = train_dw_splits(J.rows, tiles, cu_count);
+  int64_t splits = train_dw_splits(d, J.rows, tiles, cu_count);
   if (splits > 8) splits = splits / 8 * 8;
   J.chunk = ((J.rows + splits - 1) / splits + rs - 1) / rs * rs;
   splits = (J.rows + J.chunk - 1) / J.chunk;

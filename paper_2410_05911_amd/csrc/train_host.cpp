@@ -88,7 +88,7 @@ TrainWs train_ws(const aecct_trainer &T, int64_t batch) {
   w.dqkv = take(R * 3 * d);
   w.part_floats = std::max<size_t>(size_t(1) << 22, 4 * std::max<size_t>((size_t)T.L * T.n, d * dff));
   w.part_floats = std::max<size_t>(
-      w.part_floats, (size_t)aecct::train_dw_splits((int64_t)R, kDwTiles, T.cu_count) * kDwTiles * d * (d + 1));
+      w.part_floats, (size_t)aecct::train_dw_splits((int)d, (int64_t)R, kDwTiles, T.cu_count) * kDwTiles * d * (d + 1));
   w.part = take(w.part_floats);
   w.total_bytes = off + kAlign;   // the regions start at the workspace's first multiple of kAlign
   return w;
